@@ -68,6 +68,11 @@ constexpr int kStripWaves = 4;  // wavefronts (strips) per workgroup
 constexpr int kSimds = 256 * 4;  // MI355X: 256 compute units of 4 SIMDs
 constexpr int kSweepMinRowsPerStage = 4;
 
+// Coefficients of one launch of the grid's Chebyshev series (stage st at [st-1]).
+struct SweepSeries {
+  double a[5], alpha[5], beta[5];
+};
+
 // Strip decomposition of an l1 x l2 grid for S stages per launch.
 struct StripGrid {
   int rows = 0;     // core rows per strip
@@ -141,6 +146,8 @@ struct GraphView {
   const int32_t *marklist = nullptr;   // n_marked
   const uint8_t *tmark = nullptr;      // grid CTQW strips: 1 if a marked vertex lies in the strip's window
   int32_t strip_rows = 0;              // grid CTQW strips: core rows per strip
+  const uint8_t *series_mark = nullptr;  // the same two for the strips of the grid's series
+  int32_t series_rows = 0;
   int32_t two_reg = 0;                 // coined, one workgroup: 1 if every vertex has degree 2 and n <= 64
                                        // (amplitudes in one wavefront's registers), 2 if moreover a cycle in
                                        // direction order (rev[2v] = 2(v+1)+1, rev[2v+1] = 2(v-1), mod n)
@@ -177,11 +184,15 @@ struct Readout {
   double *p_out() const { return p ? p : pscratch; }
 };
 
-// Coefficients of one Horner stage y_out = psi + i*(alpha*sum_nbr y + beta*[marked] y_v),
-// alpha = gamma*dt/k, beta = dt/k (FP64; rounded once for complex64).
+// Coefficients of one stage y_out = base + i*(alpha*sum_nbr y + beta*[marked] y_v).
+// Horner stage: base = psi, alpha = gamma*dt/k, beta = dt/k.  Stage of a
+// Chebyshev series: base = a psi + prev, prev the stage before the last one
+// (null: none), element v of which may be where element v of y_out goes.
 struct StageCoef {
   double alpha;
   double beta;
+  double a = 1.0;
+  const void *prev = nullptr;
 };
 
 // ---- launchers (qw_kernels.hip) -------------------------------------------
@@ -216,7 +227,8 @@ hipError_t vertex_prob(bool c128, const GraphView &g, const void *psi, const Rea
 hipError_t dense_fill(bool c128, const GraphView &g, double gamma, size_t rows_pad, hipStream_t s);
 // Number of k ranges the dense stage splits into (1 = no split; partials then unused).
 int dense_splits(const GraphView &g);
-hipError_t dense_stage(bool c128, const GraphView &g, const void *y, const void *psi, void *out, double c,
+// (c.beta is the stage's dt / k; a series only in complex128)
+hipError_t dense_stage(bool c128, const GraphView &g, const void *y, const void *psi, void *out, const StageCoef &c,
                        hipStream_t s);
 
 // Grid CTQW with temporal blocking: depth S (stages per launch, dividing K;
@@ -227,6 +239,12 @@ int torus_block_depth(bool c128, const GraphView &g, int K);
 StripGrid torus_strips(bool c128, int l1, int l2, int S);
 hipError_t torus_block_stages(bool c128, const GraphView &g, int S, const void *P, const void *Yin, void *Out,
                               int kfirst, const double *alpha, const double *beta, hipStream_t s);
+
+// S stages of a grid's Chebyshev series (complex128) from (P, D1, D2) to (E1,
+// E2), all distinct buffers; D1 null: the series' first launch (D2 unused);
+// E2 null: its last.
+hipError_t torus_series_stages(const GraphView &g, int S, const void *P, const void *D1, const void *D2, void *E1,
+                               void *E2, const SweepSeries &c, hipStream_t s);
 
 // Staggered walk.  stag_small: every step in one workgroup's LDS (descriptors
 // read from g.stag).  stag_tess: one tessellation in place on psi; `mark`
