@@ -755,10 +755,24 @@ __global__ __launch_bounds__(kBlock) void k_ctqw_csr(GraphView g, const T *__res
       sx = t.x;
       sy = t.y;
     } else {
-      for (int a = lo + lane; a < hi; a += G) {
-        double2 x = ld(y, g.col[a]);
-        sx += x.x;
-        sy += x.y;
+      // eight of the lane's arcs at a time: their indices and then their
+      // gathers are all issued before the first add, so a row of up to 8 G
+      // arcs pays two memory latencies instead of two per arc
+      for (int a0 = lo + lane; a0 < hi; a0 += 8 * G) {
+        int c[8];
+#pragma unroll
+        for (int m = 0; m < 8; ++m)
+          if (a0 + m * G < hi) c[m] = g.col[a0 + m * G];
+        T x[8];
+#pragma unroll
+        for (int m = 0; m < 8; ++m)
+          if (a0 + m * G < hi) x[m] = y[c[m]];
+#pragma unroll
+        for (int m = 0; m < 8; ++m)
+          if (a0 + m * G < hi) {
+            sx += cvt(x[m]).x;
+            sy += cvt(x[m]).y;
+          }
       }
     }
   }
