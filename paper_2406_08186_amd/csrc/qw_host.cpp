@@ -849,9 +849,12 @@ int evolve_coined(const qw_plan *p, void *psi, unsigned char *work, int64_t step
   }
   QW_TRY(coined_perm_in(c128, g, psi, w0, s), "layout permutation kernel");
   void *cur = w0, *oth = w1;
-  for (int64_t i = 0; i < steps; ++i) {
-    QW_TRY(coined_struct_step(c128, g, cur, oth, had, s), "coined structured step kernel");
+  for (int64_t i = 0; i < steps;) {
+    const int m = coined_sweep_steps(c128, g, steps - i);
+    if (m > 1) QW_TRY(coined_sweep(c128, g, m, cur, oth, s), "coined grid sweep kernel");
+    else QW_TRY(coined_struct_step(c128, g, cur, oth, had, s), "coined structured step kernel");
     std::swap(cur, oth);
+    i += m;
   }
   QW_TRY(coined_perm_out(c128, g, cur, psi, ro, s), "layout permutation kernel");
   if (ro.any()) QW_TRY(finish_readout(g, readout_partials(g), ro, s), "readout reduction kernel");

@@ -68,6 +68,21 @@ constexpr int kStripWaves = 4;  // wavefronts (strips) per workgroup
 constexpr int kSimds = 256 * 4;  // MI355X: 256 compute units of 4 SIMDs
 constexpr int kSweepMinRowsPerStage = 4;
 
+// Coined grid sweep: steps per launch by type and coin, and rows read ahead.
+// Measured over 2 to 6 steps, 3 to 6 rows ahead and one to two wavefronts per
+// SIMD (us for 50 steps of 1024^2 Fourier complex64, 150 of 707 x 709 Grover
+// complex128, 150 of 700^2 Grover complex64, 50 of 700^2 Fourier complex128):
+//   steps         2      3      4      5      6
+//   Fourier c64   464    442    432    417    430
+//   Grover c128   1006   738    623    536    515
+//   Grover c64    674    522    460    448    469
+//   Fourier c128  479    333    299    346    332
+// More steps move fewer bytes per step but compute more halo: the matrix coin
+// (96 FP64 operations per vertex) pays for that first.  Three rows ahead are
+// best throughout, and one wavefront per SIMD (two: 5-30% slower).
+constexpr int kCoinedSteps64 = 5, kCoinedSteps128 = 6, kCoinedMatrixSteps128 = 4;
+constexpr int kCoinedAhead = 3;
+
 // Coefficients of one launch of the grid's Chebyshev series (stage st at [st-1]).
 struct SweepSeries {
   double a[5], alpha[5], beta[5];
@@ -205,6 +220,10 @@ hipError_t coined_tile_step(bool c128, const GraphView &g, const void *in, void 
                             int hadamard, hipStream_t s);
 hipError_t coined_struct_step(bool c128, const GraphView &g, const void *in, void *out,
                               int hadamard, hipStream_t s);
+// Grid walks: how many of `left` steps the next launch takes (1: one step by
+// coined_struct_step), and a launch of S >= 2 steps.
+int coined_sweep_steps(bool c128, const GraphView &g, int64_t left);
+hipError_t coined_sweep(bool c128, const GraphView &g, int S, const void *in, void *out, hipStream_t s);
 hipError_t coined_perm_in(bool c128, const GraphView &g, const void *psi, void *internal,
                           hipStream_t s);
 hipError_t coined_perm_out(bool c128, const GraphView &g, const void *internal, void *psi,

@@ -99,6 +99,26 @@ __device__ __forceinline__ double2 lane_pull(double2 x, int src) {
 constexpr int kFromLower = 0x138;  // DPP wave_shr:1, lane i receives lane i-1 (lane 0 receives 0)
 constexpr int kFromUpper = 0x130;  // DPP wave_shl:1, lane i receives lane i+1 (lane 63 receives 0)
 
+template <int CTRL>
+__device__ __forceinline__ double lane_shift(double x) {
+  const long long b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(b), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(b >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned int>(lo));
+}
+template <int CTRL>
+__device__ __forceinline__ float lane_shift(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double2 lane_shift(double2 v) {
+  return make_double2(lane_shift<CTRL>(v.x), lane_shift<CTRL>(v.y));
+}
+template <int CTRL>
+__device__ __forceinline__ float2 lane_shift(float2 v) {
+  return make_float2(lane_shift<CTRL>(v.x), lane_shift<CTRL>(v.y));
+}
+
 constexpr int kRotFromUpper = 0x134;  // DPP wave_rol:1, lane i receives lane (i+1) mod 64
 constexpr int kRotFromLower = 0x13C;  // DPP wave_ror:1, lane i receives lane (i-1) mod 64
 
@@ -495,6 +515,27 @@ template <int KIND> __device__ __forceinline__ int rev_slot(int j) {
   return KIND == kCycle ? 1 - j : (KIND == kTorus ? (j ^ 1) : j);
 }
 
+// phi = C x for a d x d coin held as interleaved complex entries, FP64 with
+// the entries read uniformly.
+template <typename T, int D>
+__device__ __forceinline__ void apply_matrix_coin(T (&x)[D], const double *__restrict__ coin) {
+  double2 xin[D];
+#pragma unroll
+  for (int k = 0; k < D; ++k) xin[k] = cvt(x[k]);
+#pragma unroll
+  for (int j = 0; j < D; ++j) {
+    double re = 0.0, im = 0.0;
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+      const double cr = coin[2 * (j * D + k)], ci = coin[2 * (j * D + k) + 1];
+      // fused explicitly, so that every kernel rounds alike
+      re += __fma_rn(cr, xin[k].x, -(ci * xin[k].y));
+      im += __fma_rn(ci, xin[k].x, cr * xin[k].y);
+    }
+    x[j] = pack<T>(make_double2(re, im));
+  }
+}
+
 template <typename T, int KIND, int D>
 __global__ __launch_bounds__(kBlock) void k_coined_struct(GraphView g, const T *__restrict__ in,
                                                           T *__restrict__ out, int dim,
@@ -518,22 +559,8 @@ __global__ __launch_bounds__(kBlock) void k_coined_struct(GraphView g, const T *
     x[0] = pack<T>(scale(add(x0, x1), kInvSqrt2));
     x[1] = pack<T>(scale(sub(x0, x1), kInvSqrt2));
   } else if (KIND != kHypercube && g.coin) {
-    // d x d coin on the slots, which are the rows' (direction) order here:
-    // phi_j = sum_k C[j][k] x_k, FP64, with the entries read uniformly
-    double2 xin[D];
-#pragma unroll
-    for (int k = 0; k < D; ++k) xin[k] = cvt(x[k]);
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-      double re = 0.0, im = 0.0;
-#pragma unroll
-      for (int k = 0; k < D; ++k) {
-        const double cr = g.coin[2 * (j * D + k)], ci = g.coin[2 * (j * D + k) + 1];
-        re += cr * xin[k].x - ci * xin[k].y;
-        im += cr * xin[k].y + ci * xin[k].x;
-      }
-      x[j] = pack<T>(make_double2(re, im));
-    }
+    // on the slots, which are the rows' (direction) order here
+    apply_matrix_coin<T, D>(x, g.coin);
   } else {
     double2 sum = make_double2(0.0, 0.0);
 #pragma unroll
@@ -550,6 +577,127 @@ __global__ __launch_bounds__(kBlock) void k_coined_struct(GraphView g, const T *
 #pragma unroll
   for (int j = 0; j < D; ++j)
     if (j < d) out[static_cast<int64_t>(keep ? j : rev_slot<KIND>(j)) * n + head_of<KIND>(v, j, n, l2)] = x[j];
+}
+
+// ---- coined: grid, streaming temporal blocking --------------------------------
+// S steps of a coined walk on the l1 x l2 torus per launch.  A step touches
+// only nearest neighbours, so a wavefront takes 64 columns (core 64 - 2S) and
+// sweeps a strip of R core rows plus S halo rows above and below from top to
+// bottom, as the CTQW sweep does: at sweep position t the four amplitudes of
+// window row t arrive (read kCoinedAhead rows ahead), and stage st = 1 .. S
+// turns the stage before it's row q = t - st + 1 into its own row q - 1:
+// row q's coin output gives the amplitude that moves up, rows q - 1 and q - 2
+// gave the ones that moved sideways (through one-lane wavefront shifts) and
+// down.  A stage keeps four amplitudes between positions, whatever R is.  Every
+// step rounds to the storage type and computes as the one-step kernel does, so
+// the bits are the same.  The outermost lanes and rows lose one cell per
+// stage; the core is exact after S.  Strips at the right and bottom edges are
+// clamped and overlap their neighbour (duplicate stores write equal values).
+// One step per launch moves the state twice a step at the copy rate (13.2 us
+// at 1024^2 complex64, 11.4 us at 707 x 709 complex128); here the bound is the
+// FP64 arithmetic on core and halo: 7.3 us (Fourier coin) and 3.0 us (Grover)
+// a step.
+template <typename T, int S, bool MATRIX, bool PERS, bool MARK>
+__device__ __forceinline__ void coined_strip(const GraphView &g, const T *__restrict__ in, T *__restrict__ out, int R,
+                                             int rb, int lane, int gcol) {
+  constexpr int AHEAD = kCoinedAhead, W = 64;
+  const int l1 = g.dims[0], l2 = g.dims[1], n_in = R + 2 * S;
+  const int64_t n = g.n;
+  auto row_off = [&](int t) -> int {
+    const int gr = rb + t;  // < 2 l1 since n_in <= l1
+    return (gr >= l1 ? gr - l1 : gr) * l2 + gcol;
+  };
+  T nx[AHEAD][4];
+  uint32_t nm[AHEAD];
+  auto fetch = [&](int i, int t) {
+    const int o = row_off(min(t, n_in - 1));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) nx[i][j] = in[j * n + o];
+    if (MARK) nm[i] = g.markbits[o >> 5] >> (o & 31);
+  };
+  // stage st's queue: amplitudes that moved sideways out of the last row (slots
+  // 0 and 1 of the row they reached) and those that move down, of the last two rows
+  T side0[S], side1[S], down1[S], down2[S];
+  const T zero{};
+#pragma unroll
+  for (int s = 0; s < S; ++s) side0[s] = side1[s] = down1[s] = down2[s] = zero;
+  uint32_t mr = 0;  // bit k: window row t - k is marked
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) fetch(i, i);
+  auto body = [&](int t0, auto full_tag) {
+    constexpr bool FULL = decltype(full_tag)::value;
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) {
+      const int t = t0 + i;
+      if (!FULL && t >= n_in) break;
+      T x[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[j] = nx[i][j];
+      if (MARK) mr = (mr << 1) | (nm[i] & 1u);
+      fetch(i, t + AHEAD);
+#pragma unroll
+      for (int st = 1; st <= S; ++st) {
+        if (!FULL && t < 2 * st - 2) break;  // rows above what stage st needs
+        T y[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) y[j] = x[j];
+        if (MATRIX) {
+          apply_matrix_coin<T, 4>(y, g.coin);
+        } else {
+          double2 sum = make_double2(0.0, 0.0);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) sum = add(sum, cvt(x[j]));
+          const double2 m = grover_mean(sum, 4);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) y[j] = pack<T>(sub(add(m, m), cvt(x[j])));
+        }
+        if (MARK && ((mr >> (st - 1)) & 1u)) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) y[j] = pack<T>(scale(cvt(x[j]), -1.0));
+        }
+        // row q - 1 of this stage: persistent keeps the slot, flip-flop takes the reverse one
+        x[0] = side0[st - 1];
+        x[1] = side1[st - 1];
+        x[PERS ? 3 : 2] = y[3];
+        x[PERS ? 2 : 3] = down2[st - 1];
+        side0[st - 1] = PERS ? lane_shift<kFromLower>(y[0]) : lane_shift<kFromUpper>(y[1]);
+        side1[st - 1] = PERS ? lane_shift<kFromUpper>(y[1]) : lane_shift<kFromLower>(y[0]);
+        down2[st - 1] = down1[st - 1];
+        down1[st - 1] = y[2];
+        if (st == S && (FULL || t >= 2 * S) && lane >= S && lane < W - S) {
+          const int o = row_off(t - S);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) out[j * n + o] = x[j];
+        }
+      }
+    }
+  };
+  int t0 = 0;
+  for (; t0 < 2 * S; t0 += AHEAD) body(t0, std::false_type{});
+  for (; t0 + AHEAD <= n_in; t0 += AHEAD) body(t0, std::true_type{});
+  if (t0 < n_in) body(t0, std::false_type{});
+}
+
+template <typename T, int S, bool MATRIX, bool PERS>
+__global__ __launch_bounds__(64 * kStripWaves) void k_coined_sweep(GraphView g, const T *__restrict__ in,
+                                                                   T *__restrict__ out, int R) {
+  constexpr int CORE = 64 - 2 * S;
+  const int l1 = g.dims[0], l2 = g.dims[1];
+  const int tiles_c = (l2 + CORE - 1) / CORE, tiles_r = (l1 + R - 1) / R;
+  const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  const int tile = xcd_remap(blockIdx.x, gridDim.x) * kStripWaves + wv;
+  if (tile >= tiles_r * tiles_c) return;  // whole wavefront
+  const int lane = threadIdx.x & 63;
+  const int tr = tile / tiles_c, tc = tile - tr * tiles_c;
+  int rb = min(tr * R, l1 - R) - S, cb = min(tc * CORE, l2 - CORE) - S;
+  rb += rb < 0 ? l1 : 0;
+  cb += cb < 0 ? l2 : 0;
+  int gcol = cb + lane;  // < 2 l2 since 64 <= l2
+  gcol -= gcol >= l2 ? l2 : 0;
+  if (g.n_marked > 0)
+    coined_strip<T, S, MATRIX, PERS, true>(g, in, out, R, rb, lane, gcol);
+  else
+    coined_strip<T, S, MATRIX, PERS, false>(g, in, out, R, rb, lane, gcol);
 }
 
 // internal[i] = psi[perm[i]]
@@ -1082,27 +1230,6 @@ struct CoefsF32 {
   float ahi[64], alo[64];
   float bhi[64], blo[64];
 };
-
-// ---- one-lane wavefront shifts ---------------------------------------------------------
-template <int CTRL>
-__device__ __forceinline__ double lane_shift(double x) {
-  const long long b = __double_as_longlong(x);
-  const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(b), CTRL, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(b >> 32), CTRL, 0xf, 0xf, true);
-  return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned int>(lo));
-}
-template <int CTRL>
-__device__ __forceinline__ float lane_shift(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
-}
-template <int CTRL>
-__device__ __forceinline__ double2 lane_shift(double2 v) {
-  return make_double2(lane_shift<CTRL>(v.x), lane_shift<CTRL>(v.y));
-}
-template <int CTRL>
-__device__ __forceinline__ float2 lane_shift(float2 v) {
-  return make_float2(lane_shift<CTRL>(v.x), lane_shift<CTRL>(v.y));
-}
 
 // ---- grid CTQW, streaming temporal blocking ----------------------------------------
 // One wavefront sweeps a strip of the l1 x l2 torus from top to bottom: 64
@@ -2614,6 +2741,35 @@ void launch_struct(const GraphView &g, const void *in, void *out, int dim, int h
                      static_cast<const T *>(in), static_cast<T *>(out), dim, hadamard);
 }
 
+// Core rows of a strip of the coined sweep (0: the grid is too small for it):
+// one wavefront per SIMD, and at least as many core rows as halo rows.
+int coined_strip_rows(int l1, int l2, int S) {
+  if (l2 < 64) return 0;
+  const int core = 64 - 2 * S, want = std::max(1, kSimds / ((l2 + core - 1) / core));
+  return std::max(0, std::min(std::max((l1 + want - 1) / want, 2 * S), l1 - 2 * S));
+}
+
+template <typename T, int S, bool MATRIX>
+void launch_coined_sweep(const GraphView &g, const T *in, T *out, hipStream_t s) {
+  const int R = coined_strip_rows(g.dims[0], g.dims[1], S);
+  const int64_t strips = static_cast<int64_t>((g.dims[0] + R - 1) / R) * ((g.dims[1] + 64 - 2 * S - 1) / (64 - 2 * S));
+  const dim3 grid(static_cast<unsigned>((strips + kStripWaves - 1) / kStripWaves)), block(64 * kStripWaves);
+  if (g.persistent)
+    hipLaunchKernelGGL((k_coined_sweep<T, S, MATRIX, true>), grid, block, 0, s, g, in, out, R);
+  else
+    hipLaunchKernelGGL((k_coined_sweep<T, S, MATRIX, false>), grid, block, 0, s, g, in, out, R);
+}
+
+template <typename T, int S>
+void launch_coined_sweep(const GraphView &g, const void *in, void *out, hipStream_t s) {
+  const T *x = static_cast<const T *>(in);
+  T *y = static_cast<T *>(out);
+  if constexpr (sizeof(T) != 16 || S <= kCoinedMatrixSteps128) {
+    if (g.coin) return launch_coined_sweep<T, S, true>(g, x, y, s);
+  }
+  launch_coined_sweep<T, S, false>(g, x, y, s);
+}
+
 template <typename T>
 hipError_t launch_coined_struct(const GraphView &g, const void *in, void *out, int hadamard, hipStream_t s) {
   switch (g.structure) {
@@ -2824,6 +2980,28 @@ hipError_t coined_struct_step(bool c128, const GraphView &g, const void *in, voi
   if (g.n == 0) return hipSuccess;
   return c128 ? launch_coined_struct<double2>(g, in, out, hadamard, s)
               : launch_coined_struct<float2>(g, in, out, hadamard, s);
+}
+
+int coined_sweep_steps(bool c128, const GraphView &g, int64_t left) {
+  if (g.structure != kTorus) return 1;
+  const int most = !c128 ? kCoinedSteps64 : g.coin ? kCoinedMatrixSteps128 : kCoinedSteps128;
+  const int S = static_cast<int>(std::min<int64_t>(left, most));
+  return S >= 2 && coined_strip_rows(g.dims[0], g.dims[1], S) > 0 ? S : 1;
+}
+
+hipError_t coined_sweep(bool c128, const GraphView &g, int S, const void *in, void *out, hipStream_t s) {
+  switch (S) {
+    case 2: c128 ? launch_coined_sweep<double2, 2>(g, in, out, s) : launch_coined_sweep<float2, 2>(g, in, out, s); break;
+    case 3: c128 ? launch_coined_sweep<double2, 3>(g, in, out, s) : launch_coined_sweep<float2, 3>(g, in, out, s); break;
+    case 4: c128 ? launch_coined_sweep<double2, 4>(g, in, out, s) : launch_coined_sweep<float2, 4>(g, in, out, s); break;
+    case 5: c128 ? launch_coined_sweep<double2, 5>(g, in, out, s) : launch_coined_sweep<float2, 5>(g, in, out, s); break;
+    case 6:
+      if (!c128) return hipErrorInvalidValue;
+      launch_coined_sweep<double2, 6>(g, in, out, s);
+      break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
 }
 
 hipError_t coined_perm_in(bool c128, const GraphView &g, const void *psi, void *internal, hipStream_t s) {
