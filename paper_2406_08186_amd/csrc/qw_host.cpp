@@ -619,11 +619,26 @@ int build_plan(const qw_csr *g, const qw_walk_desc *w, qw_plan *p) {
   // values and with them FP64 readouts that differ at 1e-7: it keeps the
   // stages of single steps.  So does a regular graph's walk (ELL) below a
   // whole group: its bits there are those of the same walk in a batch.
-  if (ctqw && c128 && structure != kSmall) {
+  // One-workgroup walk with its tables in registers.  Its three vectors have a
+  // pad entry each, in the LDS room of the tables that it does without.
+  std::vector<int32_t> by_degree;
+  if (ctqw && structure == kSmall && p->K >= 2 && n <= 4096 && n + na >= 12) {
+    by_degree.resize(static_cast<size_t>(n));
+    std::iota(by_degree.begin(), by_degree.end(), 0);
+    std::stable_sort(by_degree.begin(), by_degree.end(),
+                     [&](int32_t x, int32_t y) { return rp[x + 1] - rp[x] > rp[y + 1] - rp[y]; });
+    const int per = n <= 1024 ? 1 : n <= 2048 ? 2 : 4;
+    p->small_regs = true;
+    for (int i = 0; i < per && 1024 * i < n; ++i) {
+      const int32_t v = by_degree[1024 * i];
+      p->small_regs = p->small_regs && rp[v + 1] - rp[v] <= small_row(c128, per, i);
+    }
+  }
+  if (ctqw && c128 && (structure != kSmall || p->small_regs)) {
     for (int m = structure == kTorus ? kSeriesMaxSteps : kSeriesGroup; m >= kSeriesMinSteps; m /= 2)
       if (chebyshev_series(p->dt * p->h_bound, p->K, m, &p->series)) break;
     if (p->series.terms >= p->K * p->series.steps) p->series = Series();
-    p->series_rest = structure != kEll;
+    p->series_rest = structure != kEll && structure != kSmall;
   }
 
   // grid CTQW: stages per launch, of single steps and of the series
@@ -687,6 +702,7 @@ int build_plan(const qw_csr *g, const qw_walk_desc *w, qw_plan *p) {
     p->two_reg = deg2 ? (ring ? 2 : 1) : 0;
   }
   if (p->has_sqrtp) p->off_sqrtp = section(sizeof(double) * p->sqrt_p.size());
+  if (p->small_regs) p->off_order = section(sizeof(int32_t) * n);
   for (size_t k = 0; k < tess.size(); ++k) {
     StagHost &h = tess[k];
     StagTess &t = p->stag[k];
@@ -723,6 +739,7 @@ int build_plan(const qw_csr *g, const qw_walk_desc *w, qw_plan *p) {
   } else if (p->has_col) {
     put(p->image, p->off_col, col, static_cast<size_t>(na));
   }
+  if (p->small_regs) put(p->image, p->off_order, by_degree.data(), by_degree.size());
   if (p->has_rev) put(p->image, p->off_rev, rev.data(), rev.size());
   if (p->has_tiles) put(p->image, p->off_tiles, tiles.data(), tiles.size());
   if (p->has_perm) put(p->image, p->off_perm, perm.data(), perm.size());
@@ -945,7 +962,7 @@ int evolve_ctqw(const qw_plan *p, void *psi, unsigned char *work, int64_t steps,
     alpha[k - 1] = p->gamma * p->dt / k;
   }
   if (p->structure == kSmall) {
-    QW_TRY(ctqw_small(c128, g, psi, alpha.data(), beta.data(), K, steps, ro, s), "CTQW small-graph kernel");
+    QW_TRY(ctqw_small(c128, g, psi, alpha.data(), beta.data(), K, p->small_series(), steps, ro, s), "CTQW small-graph kernel");
     return QW_OK;
   }
   if (steps == 0) return readout_only(p, psi, ro, s);
@@ -1051,6 +1068,17 @@ int evolve_ctqw(const qw_plan *p, void *psi, unsigned char *work, int64_t steps,
 }
 
 }  // namespace
+
+qwk::SmallSeries qw_plan::small_series() const {
+  qwk::SmallSeries s;
+  if (series.terms == 0) return s;
+  s.terms = series.terms;
+  s.steps = static_cast<int32_t>(series.steps);
+  s.beta = 2.0 / h_bound;
+  s.alpha = gamma * s.beta;
+  for (int k = 0; k <= series.terms; ++k) s.a[k] = series.a[k];
+  return s;
+}
 
 namespace qwk {
 
@@ -1175,6 +1203,7 @@ int qw_plan_upload(qw_plan *p, void *d_graph, size_t graph_bytes, void *stream) 
   if (p->series_depth > 1) g.series_mark = reinterpret_cast<const uint8_t *>(base + p->off_smark);
   g.series_rows = p->series_rows;
   g.two_reg = p->two_reg;
+  if (p->small_regs) g.order = reinterpret_cast<const int32_t *>(base + p->off_order);
   g.persistent = p->shift == QW_PERSISTENT;
   if (p->has_coin) g.coin = reinterpret_cast<const double *>(base + p->off_coin);
   if (p->has_sqrtp) g.sqrtp = reinterpret_cast<const double *>(base + p->off_sqrtp);
@@ -1303,6 +1332,7 @@ int qw_small_many(const qw_plan *const *plans, void *const *d_psi, const int64_t
       w.beta[k - 1] = p->dt / k;
       w.alpha[k - 1] = p->gamma * p->dt / k;
     }
+    if (p->kind == QW_CTQW) w.series = p->small_series();
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
   const size_t bytes = qw_small_many_desc_bytes(count);

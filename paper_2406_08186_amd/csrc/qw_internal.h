@@ -46,6 +46,15 @@ constexpr int kTileMaxVerts = 1024;
 constexpr int kBlock = 256;
 // LDS budget of the one-workgroup whole-walk kernels.
 constexpr size_t kSmallLdsBytes = 156 * 1024;  // dynamic LDS of the one-workgroup path (of 160 KiB)
+// The one-workgroup CTQW keeps the neighbours of a thread's vertices in
+// registers.  Of `per_thread` vertices (1, 2 or 4, the i-th of rank
+// i * 1024 + thread in falling degree) the i-th may have this many: 128
+// registers a thread hold no more.
+constexpr int small_row(bool c128, int per_thread, int i) {
+  if (per_thread == 1) return c128 ? 24 : 32;
+  if (per_thread == 2) return c128 ? (i == 0 ? 16 : 8) : (i == 0 ? 24 : 16);
+  return c128 ? 8 : (i == 0 ? 16 : 8);
+}
 // Largest hypercube dimension the structured kernels handle.
 constexpr int kMaxHypercubeDim = 30;
 
@@ -166,6 +175,7 @@ struct GraphView {
   int32_t two_reg = 0;                 // coined, one workgroup: 1 if every vertex has degree 2 and n <= 64
                                        // (amplitudes in one wavefront's registers), 2 if moreover a cycle in
                                        // direction order (rev[2v] = 2(v+1)+1, rev[2v+1] = 2(v-1), mod n)
+  const int32_t *order = nullptr;      // CTQW, one workgroup, tables in registers: vertices by falling degree
   int32_t persistent = 0;              // coined on a lattice: persistent shift
   const double *coin = nullptr;        // coined on a lattice: d x d complex coin (row-major), else null
   const double *sqrtp = nullptr;       // Szegedy coin: sqrt(P) per arc, else null
@@ -185,6 +195,7 @@ struct SmallWalk {
   int64_t steps = 0;
   double alpha[64] = {};  // CTQW stage coefficients gamma dt / k, dt / k
   double beta[64] = {};
+  SmallSeries series;
 };
 
 // Readout request: any pointer may be null.  `pscratch` (n doubles) and
@@ -234,7 +245,8 @@ hipError_t coined_prob_csr(bool c128, const GraphView &g, const void *psi, const
 
 hipError_t small_many(bool c128, const SmallWalk *d_walks, int count, size_t lds, int threads, hipStream_t s);
 hipError_t ctqw_small(bool c128, const GraphView &g, void *psi, const double *alpha,
-                      const double *beta, int K, int64_t steps, const Readout &ro, hipStream_t s);
+                      const double *beta, int K, const SmallSeries &se, int64_t steps, const Readout &ro,
+                      hipStream_t s);
 size_t ctqw_small_lds(bool c128, int n, int n_arcs);
 hipError_t ctqw_stage(bool c128, const GraphView &g, const void *y, const void *psi, void *out,
                       StageCoef c, const Readout *fused, hipStream_t s);

@@ -1547,11 +1547,173 @@ __global__ __launch_bounds__(64 * kStripWaves) void k_ctqw_torus_series(GraphVie
     series_strip<S, FIRST, false>(g, P, D1, D2, E1, E2, c, R, rb, lane, gcol, boff);
 }
 
+// FP64 readout of a one-workgroup vertex walk whose final state is ps (LDS).
+template <typename T>
+__device__ void small_vertex_readout(const GraphView &g, const T *ps, const Readout &ro, double *red) {
+  if (!(ro.p || ro.norm || ro.pmarked)) return;
+  double *pout = ro.p ? ro.p : ro.pscratch;
+  double acc = 0.0;
+  for (int v = threadIdx.x; v < g.n; v += blockDim.x) {
+    const double pv = abs2(cvt(ps[v]));
+    pout[v] = pv;
+    acc += pv;
+  }
+  const double tot = block_sum(acc, red);
+  __syncthreads();
+  double pm = 0.0;
+  for (int i = threadIdx.x; i < g.n_marked; i += blockDim.x) pm += abs2(cvt(ps[g.marklist[i]]));
+  const double ptot = block_sum(pm, red);
+  if (threadIdx.x == 0) {
+    if (ro.norm) *ro.norm = tot;
+    if (ro.pmarked) *ro.pmarked = ptot;
+  }
+}
+
+// s plus the D neighbours at byte offsets c[0 .. D-1] of y, in that order, all
+// read before the first add.
+template <typename T, int D>
+__device__ __forceinline__ double2 lds_gather_sum(double2 s, const T *y, const int *c) {
+  T x[D];
+#pragma unroll
+  for (int j = 0; j < D; ++j) x[j] = *reinterpret_cast<const T *>(reinterpret_cast<const char *>(y) + c[j]);
+#pragma unroll
+  for (int j = 0; j < D; ++j) s = add(s, cvt(x[j]));
+  return s;
+}
+
+// The double that lane k of the wavefront holds, in every lane (k uniform).
+__device__ __forceinline__ double lane_value(double x, int k) {
+  const long long b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_readlane(static_cast<int>(b), k);
+  const int hi = __builtin_amdgcn_readlane(static_cast<int>(b >> 32), k);
+  return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned int>(lo));
+}
+
+// CTQW small graphs of moderate degree: a thread keeps its VPT vertices'
+// neighbour offsets, marks, psi and last stage values in registers and the
+// wavefront the stage coefficients in its lanes, so a stage is the neighbours'
+// LDS reads, one LDS write and one barrier.  Threads take the vertices by
+// falling degree (g.order), so a wavefront's rows are alike: they are padded to
+// a multiple of 4 with offsets of an entry holding (-0, -0), which changes no
+// bit of a sum.  What bounds it is the random LDS reads on large walks and the chain
+// of dependent FP64 adds on small ones: 0.22 us per stage on 49 vertices of
+// degree 4, 0.35 on 25 of degree up to 10, 0.6 on 869 of degree up to 15, where
+// loops over row pointers and columns in LDS took 1.6 there.  Measured against
+// it and dropped: FP64 elements in LDS for complex64 (no conversions; 0.78 on
+// the large walk), two vectors at a constant or interleaved distance with two
+// copies of the stage (0.60 to 0.72).
+template <typename T, int VPT>
+__device__ void ctqw_small_regs(const GraphView &g, T *psi, const double *alpha, const double *beta, int K,
+                                const SmallSeries &se, int64_t steps, const Readout &ro, unsigned char *smem,
+                                double *red) {
+  const int n = g.n, lane = threadIdx.x & 63;
+  T *ps = reinterpret_cast<T *>(smem), *ya = ps + n + 1, *yb = ya + n + 1;
+  constexpr bool C128 = sizeof(T) == 16;
+  constexpr int D0 = small_row(C128, VPT, 0);
+  int c[VPT][D0], vert[VPT], quads[VPT];  // quads: the wavefront's longest row, in fours
+  bool mk[VPT];
+  T own[VPT], d1[VPT], d2[VPT];  // psi and the last two stages' values of the own vertices
+#pragma unroll
+  for (int i = 0; i < VPT; ++i) {
+    const int r = threadIdx.x + i * blockDim.x;
+    const int v = r < n ? g.order[r] : n;
+    const int lo = r < n ? g.rp[v] : 0, hi = r < n ? g.rp[v + 1] : 0;
+#pragma unroll
+    for (int j = 0; j < small_row(C128, VPT, i); ++j) c[i][j] = (lo + j < hi ? g.col[lo + j] : n) * static_cast<int>(sizeof(T));
+    // vertices fall in degree, so a wavefront's longest row is its first lane's
+    quads[i] = (__builtin_amdgcn_readfirstlane(hi - lo) + 3) >> 2;
+    vert[i] = v;
+    mk[i] = r < n && marked(g.markbits, v);
+    own[i] = psi[r < n ? v : 0];
+    if (r < n) ps[v] = own[i];
+  }
+  if (threadIdx.x == 0) {
+    T pad;
+    pad.x = -0.0;
+    pad.y = -0.0;
+    ps[n] = ya[n] = yb[n] = pad;
+  }
+  const double la = lane < K ? alpha[lane] : 0.0, lb = lane < K ? beta[lane] : 0.0;  // K <= 64
+  const double ls = se.terms > 0 && lane < se.terms ? se.a[lane] : 0.0, top = se.terms > 0 ? se.a[se.terms] : 0.0;
+  __syncthreads();
+  // d1 = base + i (a2 nsum + b2 [marked] d1) on every own vertex, also to yout
+  auto stage = [&](const T *yin, T *yout, double a2, double b2, auto base) {
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) {
+      if (vert[i] >= n) continue;  // idle wavefronts leave the others their issue slots
+      double2 sum = make_double2(0.0, 0.0);
+      if (quads[i] <= 1) {
+        sum = lds_gather_sum<T, 4>(sum, yin, c[i]);
+      } else {
+        sum = lds_gather_sum<T, 8>(sum, yin, c[i]);
+#pragma unroll
+        for (int j = 8; j < small_row(C128, VPT, i); j += 8) {
+          if (4 * quads[i] > j + 4) sum = lds_gather_sum<T, 8>(sum, yin, c[i] + j);
+          else if (4 * quads[i] > j) sum = lds_gather_sum<T, 4>(sum, yin, c[i] + j);
+        }
+      }
+      const double2 yv = mk[i] ? cvt(d1[i]) : make_double2(0.0, 0.0);
+      const T r = pack<T>(horner_out(base(i), sum, yv, mk[i], a2, b2));
+      yout[vert[i]] = r;
+      d2[i] = d1[i];
+      d1[i] = r;
+    }
+    __syncthreads();
+  };
+  // (only complex128 plans have a series)
+  for (; C128 && se.terms > 0 && steps >= se.steps; steps -= se.steps) {
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) d1[i] = own[i];
+    T *in = ps, *out = ya;
+    for (int k = se.terms - 1; k >= 0; --k) {
+      const bool first = k == se.terms - 1, second = k == se.terms - 2;
+      const double h = (k ? 1.0 : 0.5) * (first ? top : 1.0);
+      const double ak = lane_value(ls, k);
+      const double a = second ? ak + top : ak;  // d_M = a_M psi is folded into the first two stages
+      if (k == 0) out = ps;
+      stage(in, out, h * se.alpha, h * se.beta, [&](int i) {
+        const double2 x = cvt(own[i]), q = first || second ? make_double2(0.0, 0.0) : cvt(d2[i]);
+        return make_double2(__fma_rn(a, x.x, q.x), __fma_rn(a, x.y, q.y));
+      });
+      in = out;
+      out = in == ya ? yb : ya;
+    }
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) own[i] = d1[i];
+  }
+  for (int64_t s = 0; s < steps; ++s) {
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) d1[i] = own[i];
+    T *in = ps, *out = ya;
+    for (int k = K; k >= 1; --k) {
+      if (k == 1) out = ps;  // K >= 2: this stage reads another vector
+      stage(in, out, lane_value(la, k - 1), lane_value(lb, k - 1), [&](int i) { return cvt(own[i]); });
+      in = out;
+      out = in == ya ? yb : ya;
+    }
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) own[i] = d1[i];
+  }
+#pragma unroll
+  for (int i = 0; i < VPT; ++i)
+    if (vert[i] < n) psi[vert[i]] = own[i];
+  small_vertex_readout<T>(g, ps, ro, red);
+}
+
 // CTQW small graphs: every stage of every step in one workgroup, vectors in LDS.
 template <typename T>
 __device__ void ctqw_small_walk(const GraphView &g, T *psi, const double *alpha, const double *beta, int K,
-                                int64_t steps, const Readout &ro, unsigned char *smem, double *red) {
+                                const SmallSeries &se, int64_t steps, const Readout &ro, unsigned char *smem,
+                                double *red) {
   const int n = g.n, na = g.n_arcs;
+  if (g.order) {
+    // the plan has checked degree, size and K; a workgroup has min(n, 1024) threads at least
+    const int bd = static_cast<int>(blockDim.x);
+    if (n <= bd) ctqw_small_regs<T, 1>(g, psi, alpha, beta, K, se, steps, ro, smem, red);
+    else if (n <= 2 * bd) ctqw_small_regs<T, 2>(g, psi, alpha, beta, K, se, steps, ro, smem, red);
+    else ctqw_small_regs<T, 4>(g, psi, alpha, beta, K, se, steps, ro, smem, red);
+    return;
+  }
   T *ps = reinterpret_cast<T *>(smem);
   T *ya = ps + n;
   T *yb = ya + n;
@@ -1586,32 +1748,15 @@ __device__ void ctqw_small_walk(const GraphView &g, T *psi, const double *alpha,
     }
   }
   for (int v = threadIdx.x; v < n; v += blockDim.x) psi[v] = ps[v];
-  if (ro.p || ro.norm || ro.pmarked) {
-    double *pout = ro.p ? ro.p : ro.pscratch;
-    double acc = 0.0;
-    for (int v = threadIdx.x; v < n; v += blockDim.x) {
-      double pv = abs2(cvt(ps[v]));
-      pout[v] = pv;
-      acc += pv;
-    }
-    double tot = block_sum(acc, red);
-    __syncthreads();
-    double pm = 0.0;
-    for (int i = threadIdx.x; i < g.n_marked; i += blockDim.x) pm += abs2(cvt(ps[g.marklist[i]]));
-    double ptot = block_sum(pm, red);
-    if (threadIdx.x == 0) {
-      if (ro.norm) *ro.norm = tot;
-      if (ro.pmarked) *ro.pmarked = ptot;
-    }
-  }
+  small_vertex_readout<T>(g, ps, ro, red);
 }
 
 template <typename T>
 __global__ __launch_bounds__(1024) void k_ctqw_small(GraphView g, T *psi, Coefs c, int K,
-                                                     int64_t steps, Readout ro) {
+                                                     SmallSeries se, int64_t steps, Readout ro) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ double red[16];
-  ctqw_small_walk<T>(g, psi, c.alpha, c.beta, K, steps, ro, smem, red);
+  ctqw_small_walk<T>(g, psi, c.alpha, c.beta, K, se, steps, ro, smem, red);
 }
 
 // ---- staggered walk -----------------------------------------------------------
@@ -1785,24 +1930,7 @@ __device__ void stag_small_walk(const GraphView &g, T *psi, int64_t steps, const
     }
   }
   for (int v = threadIdx.x; v < n; v += blockDim.x) psi[v] = a[v];
-  if (ro.p || ro.norm || ro.pmarked) {
-    double *pout = ro.p ? ro.p : ro.pscratch;
-    double acc = 0.0;
-    for (int v = threadIdx.x; v < n; v += blockDim.x) {
-      const double pv = abs2(cvt(a[v]));
-      pout[v] = pv;
-      acc += pv;
-    }
-    const double tot = block_sum(acc, red);
-    __syncthreads();
-    double pm = 0.0;
-    for (int i = threadIdx.x; i < g.n_marked; i += blockDim.x) pm += abs2(cvt(a[g.marklist[i]]));
-    const double ptot = block_sum(pm, red);
-    if (threadIdx.x == 0) {
-      if (ro.norm) *ro.norm = tot;
-      if (ro.pmarked) *ro.pmarked = ptot;
-    }
-  }
+  small_vertex_readout<T>(g, a, ro, red);
 }
 
 template <typename T>
@@ -1989,7 +2117,7 @@ __global__ __launch_bounds__(1024) void k_small_many(const SmallWalk *__restrict
   else if (w.coined)
     coined_small_walk<T>(w.g, static_cast<T *>(w.psi), w.hadamard, w.steps, none, smem, red);
   else
-    ctqw_small_walk<T>(w.g, static_cast<T *>(w.psi), w.alpha, w.beta, w.K, w.steps, none, smem, red);
+    ctqw_small_walk<T>(w.g, static_cast<T *>(w.psi), w.alpha, w.beta, w.K, w.series, w.steps, none, smem, red);
 }
 
 // ---- batched launch over many walks -------------------------------------------
@@ -2712,18 +2840,18 @@ template <typename T> hipError_t launch_coined_small(const GraphView &g, void *p
 }
 
 template <typename T> hipError_t launch_ctqw_small(const GraphView &g, void *psi, const double *alpha,
-                                                   const double *beta, int K, int64_t steps,
-                                                   const Readout &ro, hipStream_t s) {
+                                                   const double *beta, int K, const SmallSeries &se,
+                                                   int64_t steps, const Readout &ro, hipStream_t s) {
   Coefs c;
   for (int k = 0; k < 64; ++k) {
     c.alpha[k] = k < K ? alpha[k] : 0.0;
     c.beta[k] = k < K ? beta[k] : 0.0;
   }
-  size_t lds = ctqw_small_lds(sizeof(T) == 16, g.n, g.n_arcs);
+  const size_t lds = ctqw_small_lds(sizeof(T) == 16, g.n, g.n_arcs);
   if (hipError_t e = allow_lds(&k_ctqw_small<T>, lds); e != hipSuccess) return e;
   int threads = 64;
   while (threads < 1024 && threads < g.n) threads *= 2;
-  hipLaunchKernelGGL(k_ctqw_small<T>, dim3(1), dim3(threads), lds, s, g, static_cast<T *>(psi), c, K,
+  hipLaunchKernelGGL(k_ctqw_small<T>, dim3(1), dim3(threads), lds, s, g, static_cast<T *>(psi), c, K, se,
                      steps, ro);
   return hipGetLastError();
 }
@@ -3068,9 +3196,9 @@ hipError_t coined_prob_csr(bool c128, const GraphView &g, const void *psi, const
 }
 
 hipError_t ctqw_small(bool c128, const GraphView &g, void *psi, const double *alpha, const double *beta,
-                      int K, int64_t steps, const Readout &ro, hipStream_t s) {
-  return c128 ? launch_ctqw_small<double2>(g, psi, alpha, beta, K, steps, ro, s)
-              : launch_ctqw_small<float2>(g, psi, alpha, beta, K, steps, ro, s);
+                      int K, const SmallSeries &se, int64_t steps, const Readout &ro, hipStream_t s) {
+  return c128 ? launch_ctqw_small<double2>(g, psi, alpha, beta, K, se, steps, ro, s)
+              : launch_ctqw_small<float2>(g, psi, alpha, beta, K, se, steps, ro, s);
 }
 
 hipError_t ctqw_stage(bool c128, const GraphView &g, const void *y, const void *psi, void *out, StageCoef c,

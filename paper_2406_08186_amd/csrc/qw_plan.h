@@ -74,6 +74,9 @@ struct qw_plan {
   int32_t series_depth = 1;    // grid CTQW: stages of the series per launch (> 1: blocked)
   int32_t series_rows = 0;
   size_t off_smark = 0, off_w3 = 0;
+  bool small_regs = false;  // one-workgroup CTQW with its tables in registers (GraphView::order)
+  size_t off_order = 0;
+  qwk::SmallSeries small_series() const;
   int32_t block_depth = 1;  // grid CTQW: Horner stages per launch (temporal blocking)
   // out-of-core binding (qw_plan_upload_streamed): the CSR neighbour table stays
   // in caller-pinned host memory.  Ring mode streams it, tile by tile, through

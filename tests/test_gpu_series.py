@@ -94,3 +94,54 @@ def test_series_groups_are_resumable():
                 pl.evolve(b, part)
             torch.cuda.synchronize()
             assert torch.equal(a, b)
+
+
+def _ring_plus(n, d, seed):
+    """A cycle with a d-2-regular random graph over it (degree <= d), d >= 2."""
+    v = np.arange(n)
+    e = [np.stack([v, (v + 1) % n], 1)]
+    if d > 2:
+        rng = np.random.default_rng(seed)
+        for _ in range(d - 2):
+            p = rng.permutation(n)[: n // 2 * 2].reshape(-1, 2)
+            e.append(p)
+    e = np.sort(np.concatenate(e), axis=1)
+    return I.from_edges(n, np.unique(e, axis=0), f"ring{n}d{d}")
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("n,d,steps,rho,K", [(4, 2, 16, 0.5, 9), (63, 4, 37, 1.0, 13), (1023, 3, 16, 0.2, 6),
+                                             (1025, 6, 33, 1.0, 12), (1030, 15, 18, 0.7, 11), (1600, 9, 17, 0.4, 10),
+                                             (2049, 5, 16, 1.0, 13), (2500, 3, 20, 0.3, 2), (90, 16, 40, 2.0, 20), (200, 32, 17, 1.0, 13),
+                                             (200, 33, 17, 1.0, 13), (1400, 24, 16, 1.0, 13)])
+def test_small_walk_registers(n, d, steps, rho, K, dtype):
+    """The one-workgroup walk with its tables in registers: one, two and four vertices per
+    thread, rows padded to 4, 8 and up to 32, degrees beyond, whole groups and single steps, alone and in one
+    launch with others."""
+    from paper_2406_08186_amd.walk import Plan, evolve_many
+    g = _ring_plus(n, d, n)
+    marked = [0, n - 1]
+    gamma = 1.0 / int(np.diff(g.row_ptr).max())
+    print(f"[case] small registers {g.name} {dtype} steps={steps} K={K}", flush=True)
+    pl = Plan(g, "ctqw", dtype=dtype, gamma=gamma, dt=rho / 2.0, taylor_order=K, marked=marked)
+    es = 16 if dtype == "c128" else 8
+    fits = 3 * es * n + 4 * (n + 1 + g.n_arcs) + 4 * ((n + 31) // 32) <= 156 * 1024
+    assert pl.structure == ("small" if fits else "cycle" if d == 2 else "general")
+    psi0 = I.random_state(n, steps)
+    psi = pl.state(psi0)
+    p, norm, pm = pl.evolve(psi, steps, readout=True)
+    torch.cuda.synchronize()
+    ref = oracle.ctqw_evolve(g.row_ptr, g.col, psi0, steps, gamma=gamma, dt=rho / 2.0, K=K, marked=marked)
+    got = psi.cpu().numpy().astype(np.complex128)
+    if dtype == "c128":
+        assert np.abs(got - ref).max() < 1e-12
+        assert np.abs(p.cpu().numpy() - np.abs(ref) ** 2).max() < 1e-12
+    else:
+        assert np.linalg.norm(got - ref) < 1e-5
+    if pl.structure == "small":
+        other = Plan(I.torus(30, 31), "ctqw", dtype=dtype, gamma=0.25, dt=0.1, taylor_order=8)
+        many = [pl.state(psi0), other.state(I.random_state(930, 1))]
+        desc = evolve_many([pl, other], many, [steps, 5])
+        torch.cuda.synchronize()
+        assert torch.equal(many[0], psi)
+        del desc
