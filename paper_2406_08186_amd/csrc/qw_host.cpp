@@ -1212,6 +1212,9 @@ int qw_plan_upload(qw_plan *p, void *d_graph, size_t graph_bytes, void *stream) 
   if (!p->stag.empty()) {
     g.stag = reinterpret_cast<const StagTess *>(base + p->off_stag);
     g.n_tess = static_cast<int32_t>(p->stag.size());
+    g.stag_regs = p->structure == kSmall && g.n_tess <= 2;
+    for (const StagTess &t : p->stag)
+      g.stag_regs = g.stag_regs && t.n_big == 0 && t.max_small <= kStagRegSize && t.n_small <= 1024;
   }
   if (p->structure == kDense) {
     g.ld = p->ld;

@@ -114,6 +114,7 @@ struct StripGrid {
 constexpr int kStagThreadMax = 16;
 constexpr int kStagChunk = 2048;
 constexpr int kStagMaxTess = 64;
+constexpr int kStagRegSize = 4;  // one-workgroup walks: polygons up to this size fit a thread's registers
 
 // One tessellation of a staggered walk as the kernels see it.  Offsets are
 // bytes from the start of the plan's device buffer (-1: absent).
@@ -182,6 +183,15 @@ struct GraphView {
   const unsigned char *base = nullptr; // start of the plan's device buffer
   const StagTess *stag = nullptr;      // staggered: device array of n_tess descriptors
   int32_t n_tess = 0;
+  int32_t stag_regs = 0;               // staggered, one workgroup: polygons kept in registers
+};
+
+// A Chebyshev series of a one-workgroup CTQW walk (terms == 0: none).
+struct SmallSeries {
+  int32_t terms = 0;
+  int32_t steps = 0;
+  double alpha = 0.0, beta = 0.0;
+  double a[66] = {};
 };
 
 // One walk of a many-small-walks launch (the whole walk in one workgroup's LDS).
