@@ -802,7 +802,7 @@ int build_plan(const qw_csr *g, const qw_walk_desc *w, qw_plan *p) {
     GraphView dv;
     dv.n = static_cast<int32_t>(n);
     dv.columns = p->columns;
-    const int sp = dense_splits(dv);
+    const int sp = dense_splits(c128, dv);
     if (sp > 1) p->off_dpartial = wsec(sizeof(double) * static_cast<size_t>(sp) * n * 2 * p->columns);
   }
   p->work_bytes = w_off;

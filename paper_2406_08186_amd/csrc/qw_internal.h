@@ -267,7 +267,7 @@ hipError_t vertex_prob(bool c128, const GraphView &g, const void *psi, const Rea
 // marked diagonal), and one Horner stage y_out = psi + (-i c) H y_in on MFMA.
 hipError_t dense_fill(bool c128, const GraphView &g, double gamma, size_t rows_pad, hipStream_t s);
 // Number of k ranges the dense stage splits into (1 = no split; partials then unused).
-int dense_splits(const GraphView &g);
+int dense_splits(bool c128, const GraphView &g);
 // (c.beta is the stage's dt / k; a series only in complex128)
 hipError_t dense_stage(bool c128, const GraphView &g, const void *y, const void *psi, void *out, const StageCoef &c,
                        hipStream_t s);

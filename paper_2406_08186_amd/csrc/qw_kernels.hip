@@ -2607,6 +2607,32 @@ __device__ __forceinline__ double dense_base(const R *psi, const R *prev, double
   return prev ? __fma_rn(a, x, static_cast<double>(prev[i])) : a * x;
 }
 
+// A wavefront's 16 x 16 NT results z(t, r): y_out = base + c (b - i a), or the
+// raw products where k is split over workgroups.
+template <typename R, int NT, typename Z>
+__device__ __forceinline__ void dense_store(Z z_of, int row0, int col0, int l, int n, int c2, int split, const R *psi,
+                                            R *out, double c, double base_a, const R *prev, double *partial) {
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const double z = z_of(t, r);
+      const double zp = __shfl_xor(z, 1, 64);
+      const int row = row0 + Mfma<R>::row(l, r);
+      const int col = col0 + t * 16 + (l & 15);
+      if (partial) {  // split k: hand the raw product to the reduction kernel
+        if (row < n && col < c2) partial[(static_cast<int64_t>(split) * n + row) * c2 + col] = z;
+        continue;
+      }
+      if (row < n && col < c2) {
+        const int64_t idx = static_cast<int64_t>(row) * c2 + col;
+        const double ps = dense_base(psi, prev, base_a, idx);
+        out[idx] = static_cast<R>((col & 1) ? ps - c * zp : ps + c * zp);
+      }
+    }
+  }
+}
+
 template <typename R, int NT, int KC>
 __global__ __launch_bounds__(256) void k_dense_stage(const R *__restrict__ H, int ld, int n, int c2,
                                                      const R *__restrict__ yin, const R *psi, R *out,
@@ -2687,25 +2713,113 @@ __global__ __launch_bounds__(256) void k_dense_stage(const R *__restrict__ H, in
       }
     }
   }
+  dense_store<R, NT>([&](int t, int r) { return wide[t][r] + static_cast<double>(acc[t][r]); }, row0 + wave * 16, 0, l,
+                     n, c2, split, psi, out, c, base_a, prev, partial);
+}
+
+// FP64 H times 33 or more real columns: bound by the FP64 matrix rate (78.6
+// TFLOP/s) and, near it, by streaming H.  A wavefront's 16 rows of H are its own
+// (and its twin's for the other half of the columns), so they go from memory
+// straight to registers, a lane taking four consecutive k of one row: the k
+// that an MFMA's four operand groups stand for may be any, as long as both
+// operands agree, so group q takes k = 4q + i in MFMA i of sixteen k.  Only the
+// state block goes through LDS, in chunks of KC rows whose stride of NC + 4 puts
+// the rows of neighbouring groups on different banks.  Eight wavefronts, two
+// per SIMD; a chunk's state rows are loaded while the chunk before multiplies,
+// H's two chunks ahead, an MFMA's state values one MFMA step ahead.  Per stage,
+// with the reduction, against the LDS-staged kernel below: N = 2500, 32 walks
+// 29.4 us (37.7 before), N = 5000, 32 walks 83 (94), N = 4000, 128 walks 154
+// (235); 16 walks 58 (53), so those stay there.
+template <int NT, int KC>
+__global__ __launch_bounds__(512) void k_dense_stage_f64(const double *__restrict__ H, int ld, int n, int c2,
+                                                         const double *__restrict__ yin, const double *psi,
+                                                         double *out, double c, double base_a, const double *prev,
+                                                         int ksplit, double *partial) {
+  using M = Mfma<double>;
+  constexpr int NC = NT * 16, STR = NC + 4, SUB = KC / 16;
+  constexpr int NW = NT / 2;              // tiles of 16 real columns per wavefront
+  constexpr int XP = KC * NC / 2 / 512;  // pairs of state values each thread stages per chunk
+  static_assert(KC % 16 == 0 && kDenseK % KC == 0 && (KC * NC / 2) % 512 == 0, "whole pieces");
+  __shared__ __align__(16) double xs[2][KC][STR];
+  const int wave = (threadIdx.x >> 6) & 3, half = threadIdx.x >> 8, l = threadIdx.x & 63, q = l >> 4;
+  const int rblocks = (n + kDenseRows - 1) / kDenseRows;
+  const int split = blockIdx.x / rblocks;
+  const int row0 = (blockIdx.x - split * rblocks) * kDenseRows + wave * 16;
+  const int kbeg = split * ksplit, kend = min(n, kbeg + ksplit);
+  typename M::acc acc[NW];
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
+  for (int t = 0; t < NW; ++t) acc[t] = M::zero();
+  // rows and columns of H are padded with zeros to kDenseRows and kDenseK, and k ranges are whole kDenseK
+  const double *hrow = H + static_cast<int64_t>(row0 + (l & 15)) * ld + 4 * q;
+  double2 hn[2][SUB][2], xn[XP];
+  // Both fetches are unconditional, from a valid place past the range's end,
+  // so that the compiler can count the loads in flight.
+  auto fetch_h = [&](int b, int k0) {
+    const double *p = hrow + min(k0, ld - KC);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const double z = wide[t][r] + static_cast<double>(acc[t][r]);
-      const double zp = __shfl_xor(z, 1, 64);
-      const int row = row0 + wave * 16 + M::row(l, r);
-      const int col = t * 16 + (l & 15);
-      if (partial) {  // split k: hand the raw product to the reduction kernel
-        if (row < n && col < c2) partial[(static_cast<int64_t>(split) * n + row) * c2 + col] = z;
-        continue;
-      }
-      if (row < n && col < c2) {
-        const int64_t idx = static_cast<int64_t>(row) * c2 + col;
-        const double ps = dense_base(psi, prev, base_a, idx);
-        out[idx] = static_cast<R>((col & 1) ? ps - c * zp : ps + c * zp);
-      }
+    for (int s = 0; s < SUB; ++s) {
+      hn[b][s][0] = *reinterpret_cast<const double2 *>(p + 16 * s);
+      hn[b][s][1] = *reinterpret_cast<const double2 *>(p + 16 * s + 2);
     }
+  };
+  auto fetch_x = [&](int k0) {
+#pragma unroll
+    for (int p = 0; p < XP; ++p) {
+      const int e = threadIdx.x + p * 512, i = e / (NC / 2), j = 2 * (e % (NC / 2));
+      xn[p] = *reinterpret_cast<const double2 *>(yin + static_cast<int64_t>(min(k0 + i, n - 1)) * c2 + min(j, c2 - 2));
+    }
+  };
+  // rows of the state block past the range and columns past the block count as zero
+  auto stage_x = [&](int b, int k0) {
+#pragma unroll
+    for (int p = 0; p < XP; ++p) {
+      const int e = threadIdx.x + p * 512, i = e / (NC / 2), j = 2 * (e % (NC / 2));
+      const bool in = k0 + i < kend && j < c2;
+      *reinterpret_cast<double2 *>(&xs[b][i][j]) = make_double2(in ? xn[p].x : 0.0, in ? xn[p].y : 0.0);
+    }
+  };
+  auto chunk = [&](auto which, int k0) {
+    constexpr int b = decltype(which)::value;
+    stage_x(b, k0);
+    // a wave past this barrier has finished its MMAs of the chunk before the
+    // last, whose buffer the next chunk writes
+    __syncthreads();
+    fetch_x(k0 + KC);
+    __builtin_amdgcn_sched_barrier(0);
+    // one MFMA step's state values are read while the step before multiplies
+    double y[2][NW];
+    auto read = [&](int m) {
+#pragma unroll
+      for (int t = 0; t < NW; ++t) y[m & 1][t] = xs[b][16 * (m >> 2) + 4 * q + (m & 3)][(half * NW + t) * 16 + (l & 15)];
+    };
+    read(0);
+    __builtin_amdgcn_sched_group_barrier(0x100, (NW + 1) / 2, 0);
+#pragma unroll
+    for (int m = 0; m < 4 * SUB; ++m) {
+      if (m + 1 < 4 * SUB) read(m + 1);
+      const double2 hp = hn[b][m >> 2][(m >> 1) & 1];
+      const double h = (m & 1) ? hp.y : hp.x;
+#pragma unroll
+      for (int t = 0; t < NW; ++t) acc[t] = M::mma(h, y[m & 1][t], acc[t]);
+      if (m + 1 < 4 * SUB) __builtin_amdgcn_sched_group_barrier(0x100, (NW + 1) / 2, 0);  // LDS reads of the next step,
+      __builtin_amdgcn_sched_group_barrier(0x008, NW, 0);            // then this step's MFMAs
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // into the registers just read, two chunks on: loads return in order, so
+    // these stay in flight when the next chunk waits for its state rows
+    fetch_h(b, k0 + 2 * KC);
+  };
+  if (kbeg < kend) {
+    fetch_h(0, kbeg);
+    fetch_x(kbeg);
+    fetch_h(1, kbeg + KC);
   }
+  for (int k0 = kbeg; k0 < kend; k0 += 2 * KC) {
+    chunk(std::integral_constant<int, 0>{}, k0);
+    if (k0 + KC < kend) chunk(std::integral_constant<int, 1>{}, k0 + KC);
+  }
+  dense_store<double, NW>([&](int t, int r) { return acc[t][r]; }, row0, half * NW * 16, l, n, c2, split, psi, out, c, base_a, prev,
+                          partial);
 }
 
 // One walk with FP32 H: H y is bound by streaming H once, so it runs on the
@@ -2834,19 +2948,24 @@ template <typename R, int NT>
 void launch_dense(const GraphView &g, const void *y, const void *psi, void *out, double c, double a,
                   const void *prev, hipStream_t s) {
   const int rblocks = (g.n + kDenseRows - 1) / kDenseRows;
-  const int splits = dense_splits(g);
+  const int splits = dense_splits(sizeof(R) == 8, g);
   const int ksplit = ((g.n + splits - 1) / splits + kDenseK - 1) / kDenseK * kDenseK;
   const int used = (g.n + ksplit - 1) / ksplit;  // splits that own at least one k
   const dim3 grid(rblocks * used);
   double *partial = used > 1 ? g.dense_partial : nullptr;
   // 32-k chunks halve the barriers per byte of H where the stage streams H
-  // (one 16-column tile) and for FP32 from 64 columns; the FP64 tiles of 32
-  // and more columns measured faster with 16 (and with 256 columns 32 would
-  // not fit LDS twice)
+  // (one 16-column tile) and for FP32 from 64 columns; the FP64 tile of 32
+  // columns measured faster with 16
   constexpr int KC = (NT == 1 || (sizeof(R) == 4 && (NT == 4 || NT == 16))) ? 32 : 16;
-  hipLaunchKernelGGL((k_dense_stage<R, NT, KC>), grid, dim3(256), 0, s, static_cast<const R *>(g.dense), g.ld, g.n,
-                     2 * g.columns, static_cast<const R *>(y), static_cast<const R *>(psi), static_cast<R *>(out),
-                     c, a, static_cast<const R *>(prev), ksplit, partial);
+  if constexpr (sizeof(R) == 8 && NT >= 4)
+    hipLaunchKernelGGL((k_dense_stage_f64<NT, NT <= 8 ? 32 : 16>), grid, dim3(512), 0, s,
+                       static_cast<const double *>(g.dense), g.ld, g.n, 2 * g.columns, static_cast<const double *>(y),
+                       static_cast<const double *>(psi), static_cast<double *>(out), c, a,
+                       static_cast<const double *>(prev), ksplit, partial);
+  else
+    hipLaunchKernelGGL((k_dense_stage<R, NT, KC>), grid, dim3(256), 0, s, static_cast<const R *>(g.dense), g.ld, g.n,
+                       2 * g.columns, static_cast<const R *>(y), static_cast<const R *>(psi), static_cast<R *>(out),
+                       c, a, static_cast<const R *>(prev), ksplit, partial);
   if (partial) {
     const int64_t total = static_cast<int64_t>(g.n) * g.columns;
     hipLaunchKernelGGL(k_dense_reduce<R>, dim3(blocks_for(total, kBlock)), dim3(kBlock), 0, s, partial, used,
@@ -3359,12 +3478,26 @@ hipError_t batch_ell_lds(bool c128, BatchCtl *ctl, const WalkSlot *slots, const 
   return hipGetLastError();
 }
 
-int dense_splits(const GraphView &g) {
+int dense_splits(bool c128, const GraphView &g) {
   const int rblocks = (g.n + kDenseRows - 1) / kDenseRows;
   int sp = (512 + rblocks - 1) / rblocks;
   sp = std::min(sp, kMaxDenseSplits);
-  sp = std::min(sp, std::max(1, g.n / (4 * kDenseK)));
-  return std::max(sp, 1);
+  sp = std::max(1, std::min(sp, std::max(1, g.n / (4 * kDenseK))));
+  if (!c128 || 2 * g.columns <= 32) return sp;
+  // k_dense_stage_f64: the matrix cores are the bound and one
+  // workgroup per compute unit fills them, so what counts is the rounds of 256
+  // workgroups times the k range of one (and a little for each partial sum)
+  int best = 1;
+  double least = 0.0;
+  for (int k = 1; k <= sp; ++k) {
+    const int range = ((g.n + k - 1) / k + kDenseK - 1) / kDenseK * kDenseK;
+    const double cost = static_cast<double>((rblocks * ((g.n + range - 1) / range) + 255) / 256) * range + 16.0 * k;
+    if (k == 1 || cost < least) {
+      least = cost;
+      best = k;
+    }
+  }
+  return best;
 }
 
 hipError_t dense_fill(bool c128, const GraphView &g, double gamma, size_t rows_pad, hipStream_t s) {
