@@ -194,7 +194,7 @@ int build_table(qw_batch *b) {
     const qw_plan *p = b->plans[s];
     if (w.kind == QW_CTQW) {
       const bool lds = lds_slot(b, w);
-      const int R = lds ? (b->dtype == QW_C128 ? kLdsTileRows128 : kLdsTileRows64) : b->rows_per_tile;
+      const int R = lds ? lds_tile_rows(b->dtype == QW_C128, w.ell_d) : b->rows_per_tile;
       for (int64_t r = 0; r < p->n; r += R)
         it.tiles.push_back({s, static_cast<int32_t>(r), static_cast<int32_t>(std::min<int64_t>(p->n, r + R)), 0});
       it.load = p->n_arcs + 3 * p->n;

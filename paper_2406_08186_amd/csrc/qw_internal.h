@@ -13,17 +13,24 @@ namespace qwk {
 // one workgroup's LDS tile are processed together.
 constexpr int kTileArcs = 2048;
 constexpr int kTileThreads = 256;
-// The LDS-staged batch stage, per state type: workgroup size, rows per tile
-// (a whole number per thread) and the LDS block of the input vector it
-// stages (whole rounds of 1 KiB direct loads by every wavefront).  complex64:
-// 768 threads x 9 rows, 156 KiB blocks; complex128 (whose sum registers are
-// twice as wide): 1024 threads x 6 rows, 144 KiB blocks.
+// The LDS-staged batch stage, per state type: workgroup size, the LDS block of
+// the input vector it stages (whole rounds of 1 KiB direct loads by every
+// wavefront) and rows per thread for walks of degree d (1..8).  A row takes d
+// index and four sum registers, so sparser walks fit more rows; one row more
+// than here spills (96 walks of one degree, complex64, ms a pass: degree 3 with
+// 12, 13, 14 rows 7.7, 8.6, 9.2; degree 4 with 11, 12 8.4, 8.7; degree 5 with
+// 10, 11, 12 10.0, 9.4, 9.7).
 constexpr int kLdsTileThreads64 = 768;
-constexpr int kLdsTileRows64 = 6912;
 constexpr int kLdsBlockBytes64 = 156 * 1024;
 constexpr int kLdsTileThreads128 = 1024;
-constexpr int kLdsTileRows128 = 6144;
 constexpr int kLdsBlockBytes128 = 144 * 1024;
+constexpr int lds_rows_per_thread(bool c128, int d) {
+  constexpr int r64[9] = {12, 12, 12, 12, 11, 11, 10, 9, 9}, r128[9] = {8, 8, 8, 8, 8, 7, 7, 6, 6};
+  return c128 ? r128[d] : r64[d];
+}
+constexpr int lds_tile_rows(bool c128, int d) {
+  return lds_rows_per_thread(c128, d) * (c128 ? kLdsTileThreads128 : kLdsTileThreads64);
+}
 // single-walk ELL stage: vectors above kEllSliceFrom bytes are gathered in
 // slices of kEllSliceEntries entries (measured best on 2^20 vertices for both
 // types, against 64Ki and 256Ki: 1 MiB complex64, 2 MiB complex128).  The
@@ -368,9 +375,8 @@ hipError_t ctqw_direct_stage(bool c128, const GraphView &g, const int32_t *wg_ro
                              const int32_t *hcol, int64_t split, const void *y, const void *psi, void *out,
                              double alpha, double beta, hipStream_t s);
 // The LDS-staged stage of the batch's CTQW walks on the ELL layout (degree
-// <= 8): tiles of kLdsTileRows64/128 rows, one workgroup of
-// kLdsTileThreads64/128 each, the input vector staged in blocks of
-// kLdsBlockBytes64/128.  The last workgroup
+// <= 8): tiles of lds_tile_rows rows, one workgroup of kLdsTileThreads64/128
+// each, the input vector staged in blocks of kLdsBlockBytes64/128.  The last workgroup
 // advances the launch counter when `advance` is nonzero.
 hipError_t batch_ell_lds(bool c128, BatchCtl *ctl, const WalkSlot *slots, const TileEntry *tiles,
                          const int32_t *n_tiles, int grid, int advance, hipStream_t s);

@@ -876,10 +876,12 @@ __device__ __forceinline__ double2 horner_out(double2 psi, double2 nsum, double2
 }
 
 // What a stage adds H y to (StageCoef): a psi + prev, or a psi where there is
-// no prev.  A Horner stage has a = 1 and no prev: 1 * psi is psi bit for bit.
+// no prev.  A Horner stage has a = 1 and no prev: 1 * psi is psi bit for bit
+// (complex64 walks have no other stages).
 template <typename T>
 __device__ __forceinline__ double2 stage_base(const T *psi, const T *prev, double a, int64_t v) {
   const double2 x = ld(psi, v);
+  if constexpr (sizeof(T) == 8) return x;
   if (!prev) return scale(x, a);
   const double2 q = ld(prev, v);
   return make_double2(__fma_rn(a, x.x, q.x), __fma_rn(a, x.y, q.y));
@@ -2403,28 +2405,134 @@ __global__ __launch_bounds__(kTileThreads) void k_batch_stage(BatchCtl *ctl, con
 // (global_load_lds_dwordx4: each lane's 16 bytes land at the wave's LDS base
 // plus 16 * lane, 1 KiB per wave instruction), which need no registers and no
 // LDS write instructions; the registers that a prefetch would hold carry more
-// rows per thread (complex64: 9 of 768 threads; complex128: 6 of 1024; the
-// register-prefetching form fitted 4), so a walk has fewer tiles to pass over
-// its vector.  Every lane visits all 8 neighbour slots of its rows in
-// every block (branch-free; a slot outside the block adds -0), so the sum loop
-// costs 8 LDS reads per row and block: the kernel pays for walks whose vector
-// spans many blocks.  Memory is reached through global-address-space views of
+// rows per thread, so a walk has fewer tiles to pass over its vector.  The
+// degree D is a template constant of the tile's code: every lane visits its
+// rows' D neighbour slots in every block (branch-free; a slot outside the block
+// adds -0), and the registers that shorter rows leave hold more rows
+// (lds_rows_per_thread).  With eight slots and 9 rows (complex64) for every
+// degree, 96 walks of up to 2e5 vertices took, ms for 4 steps by degree 3 to 8,
+// 11.0 11.3 11.6 12.0 12.4 12.7; so, and on the balanced table, 7.3 8.3 9.3
+// 10.7 11.7 12.5.  Memory is reached through global-address-space views of
 // the slot table's pointers, and every load is unconditional (indices clamped
 // into range, unused values dropped by a select).  Tiles are taken
 // grid-stride (the host lays out the table by XCD); the last workgroup of the
 // launch advances the launch counter when `advance` is set.  The host sends
 // only walks whose state holds at least 16 bytes and whose psi and work
 // buffers are 16-byte aligned.
-template <typename T, int NT, int RPL, int BLK>
-__global__ __launch_bounds__(NT) void k_batch_ell_lds(BatchCtl *ctl, const WalkSlot *slots,
-                                                      const TileEntry *tiles, const int32_t *n_tiles,
-                                                      int advance) {
+template <typename T, int NT, int D, int BLK>
+__device__ __forceinline__ void ell_lds_tile(T *xs, const WalkSlot &w, const TileEntry &te, int64_t u) {
+  constexpr int RPL = lds_rows_per_thread(sizeof(T) == 16, D);
   constexpr int kWaves = NT / 64;
   constexpr int EPL = 16 / static_cast<int>(sizeof(T));  // entries per lane of one direct load
   constexpr int EPW = 64 * EPL;                           // entries per wave load (1 KiB)
   static_assert(NT % 64 == 0 && BLK % (kWaves * EPW) == 0, "a block is whole rounds of wave loads");
   constexpr int LPW = BLK / (kWaves * EPW);  // direct loads per wave and block
   constexpr unsigned kPadByte = static_cast<unsigned>(BLK) * static_cast<unsigned>(sizeof(T));
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int K = w.K;
+  const int64_t step = u / K;
+  const int k = K - static_cast<int>(u % K);
+  const T *yin_p = (k == K) ? static_cast<const T *>(w.psi) : static_cast<const T *>(((K - k - 1) & 1) ? w.w1 : w.w0);
+  const gptr<T> psi = as_global(static_cast<const T *>(w.psi));
+  const gptr<T> yin = as_global(yin_p);
+  const gmut<T> yout = as_global_mut(static_cast<T *>((k == 1) ? w.psi : (((K - k) & 1) ? w.w1 : w.w0)));
+  const gptr<int32_t> col = as_global(w.col);
+  const gptr<uint32_t> bits = as_global(w.markbits);
+  const double alpha = as_global(w.alpha)[k - 1], beta = as_global(w.beta)[k - 1];
+  const int n = w.n, d = w.ell_d;  // d <= D
+  // the last whole group of EPL entries: a lane whose group runs past the
+  // vector loads it instead (those LDS entries are never read, but for n-1
+  // when n is odd in complex64, written in place below)
+  const int last_group = (n - EPL) / EPL * EPL;
+  // neighbour indices of this lane's rows; missing neighbours and rows past the
+  // tile (their loads read a valid entry) become the pad offset below.
+  int c[RPL][D];
+  double2 acc[RPL];
+#pragma unroll
+  for (int i = 0; i < RPL; ++i) {
+    const int r = te.begin + tid + i * NT;
+    const int rc = r < te.end ? r : te.end - 1;
+#pragma unroll
+    for (int j = 0; j < D; ++j) c[i][j] = col[static_cast<int64_t>(j < d ? j : d - 1) * n + rc];
+    acc[i] = make_double2(0.0, 0.0);
+  }
+  // held as byte offsets into the vector (the host keeps n * sizeof(T) below 2^31);
+  // a pad is 0xffffffff, whose offset from any block start (below 2^31) is at
+  // least 2^31 and so always clamps to the pad entry
+#pragma unroll
+  for (int i = 0; i < RPL; ++i) {
+    const bool ok = te.begin + tid + i * NT < te.end;
+#pragma unroll
+    for (int j = 0; j < D; ++j) c[i][j] = (ok && j < d) ? c[i][j] * static_cast<int>(sizeof(T)) : -1;
+  }
+  for (int base = 0; base < n; base += BLK) {
+    __syncthreads();  // the previous block (or tile) is no longer read
+#pragma unroll
+    for (int e = 0; e < LPW; ++e) {
+      const int lbase = (e * kWaves + wave) * EPW;  // first entry of this wave load
+      const int idx = base + lbase + EPL * lane;
+      const int src = idx + EPL <= n ? idx : last_group;
+      __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)(yin_p + src),
+                                       (void __attribute__((address_space(3))) *)(xs + lbase), 16, 0, 0);
+    }
+    __syncthreads();  // the direct loads have landed (the barrier waits for them)
+    if constexpr (EPL == 2) {
+      // odd n: entry n-1 sits in a group that runs past the vector
+      if ((n & 1) && n - 1 >= base && n - 1 < base + BLK) {
+        if (tid == 0) xs[n - 1 - base] = gld(yin, n - 1);
+        __syncthreads();
+      }
+    }
+    // up to four LDS reads in flight per group, then their adds in neighbour order;
+    // a byte offset outside the block (below it, it wraps) clamps to the pad
+    const unsigned base_b = static_cast<unsigned>(base) * static_cast<unsigned>(sizeof(T));
+    const char *xs_b = reinterpret_cast<const char *>(xs);
+#pragma unroll
+    for (int i = 0; i < RPL; ++i)
+#pragma unroll
+      for (int h = 0; h < D; h += 4) {
+        T xv[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (h + j < D) {
+            const unsigned off = min(static_cast<unsigned>(c[i][h + j]) - base_b, kPadByte);
+            xv[j] = *reinterpret_cast<const T *>(xs_b + off);
+          }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (h + j < D) acc[i] = add(acc[i], cvt(xv[j]));
+      }
+  }
+  T pv[RPL], yv[RPL];
+  uint32_t mw[RPL];
+#pragma unroll
+  for (int i = 0; i < RPL; ++i) {
+    const int r = te.begin + tid + i * NT;
+    const int rc = r < te.end ? r : te.end - 1;
+    pv[i] = gld(psi, rc);
+    yv[i] = gld(yin, rc);
+    mw[i] = bits[rc >> 5];
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < RPL; ++i) {
+    const int r = te.begin + tid + i * NT;
+    const int rc = r < te.end ? r : te.end - 1;
+    const bool mk = (mw[i] >> (rc & 31)) & 1u;
+    const double2 y_self = mk ? cvt(yv[i]) : make_double2(0.0, 0.0);
+    const T o = pack<T>(horner_out(cvt(pv[i]), acc[i], y_self, mk, alpha, beta));
+    if (r < te.end) {
+      gst(yout, r, o);
+      if (k == 1 && mk && w.hist) atomicAdd(&w.hist[step], abs2(cvt(o)));
+    }
+  }
+}
+
+template <typename T, int NT, int BLK>
+__global__ __launch_bounds__(NT) void k_batch_ell_lds(BatchCtl *ctl, const WalkSlot *slots,
+                                                      const TileEntry *tiles, const int32_t *n_tiles,
+                                                      int advance) {
   // xs[BLK] is a pad entry holding (-0, -0): a neighbour outside the current
   // block reads it, and adding -0 leaves every value (either zero included)
   // bit for bit unchanged, so the sum loop has no branch
@@ -2436,115 +2544,26 @@ __global__ __launch_bounds__(NT) void k_batch_ell_lds(BatchCtl *ctl, const WalkS
   const int64_t L = static_cast<int64_t>(ctl->L);
   const bool probe = ctl->probe != 0;
   const int nt = *n_tiles;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
   for (int t = blockIdx.x; t < nt; t += gridDim.x) {
     const TileEntry te = tiles[t];
     if (te.slot < 0) continue;
     const WalkSlot &w = slots[te.slot];
-    if (w.kind != 1 || w.ell_d <= 0 || w.ell_d > 8 || w.n < EPL) continue;
+    if (w.kind != 1 || w.ell_d <= 0 || w.ell_d > 8 || w.n < 16 / static_cast<int>(sizeof(T))) continue;
     const int64_t u = probe ? 0 : L - w.L0;
     if (u < 0 || u >= w.units) continue;
-    const int K = w.K;
-    const int64_t step = u / K;
-    const int k = K - static_cast<int>(u % K);
-    const T *yin_p = (k == K) ? static_cast<const T *>(w.psi) : static_cast<const T *>(((K - k - 1) & 1) ? w.w1 : w.w0);
-    const gptr<T> psi = as_global(static_cast<const T *>(w.psi));
-    const gptr<T> yin = as_global(yin_p);
-    const gmut<T> yout = as_global_mut(static_cast<T *>((k == 1) ? w.psi : (((K - k) & 1) ? w.w1 : w.w0)));
-    const gptr<int32_t> col = as_global(w.col);
-    const gptr<uint32_t> bits = as_global(w.markbits);
-    const double alpha = as_global(w.alpha)[k - 1], beta = as_global(w.beta)[k - 1];
-    const int n = w.n, d = w.ell_d;
-    // the last whole group of EPL entries: a lane whose group runs past the
-    // vector loads it instead (those LDS entries are never read, but for n-1
-    // when n is odd in complex64, written in place below)
-    const int last_group = (n - EPL) / EPL * EPL;
-    // neighbour indices of this lane's rows; missing neighbours and rows past the
-    // tile (their loads read a valid entry) become the pad offset below.
-    int c[RPL][8];
-    double2 acc[RPL];
-#pragma unroll
-    for (int i = 0; i < RPL; ++i) {
-      const int r = te.begin + tid + i * NT;
-      const int rc = r < te.end ? r : te.end - 1;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) c[i][j] = col[static_cast<int64_t>(j < d ? j : d - 1) * n + rc];
-      acc[i] = make_double2(0.0, 0.0);
-    }
-    // held as byte offsets into the vector (the host keeps n * sizeof(T) below 2^31);
-    // a pad is 0xffffffff, whose offset from any block start (below 2^31) is at
-    // least 2^31 and so always clamps to the pad entry
-#pragma unroll
-    for (int i = 0; i < RPL; ++i) {
-      const bool ok = te.begin + tid + i * NT < te.end;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) c[i][j] = (ok && j < d) ? c[i][j] * static_cast<int>(sizeof(T)) : -1;
-    }
-    for (int base = 0; base < n; base += BLK) {
-      __syncthreads();  // the previous block (or tile) is no longer read
-#pragma unroll
-      for (int e = 0; e < LPW; ++e) {
-        const int lbase = (e * kWaves + wave) * EPW;  // first entry of this wave load
-        const int idx = base + lbase + EPL * lane;
-        const int src = idx + EPL <= n ? idx : last_group;
-        __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)(yin_p + src),
-                                         (void __attribute__((address_space(3))) *)(xs + lbase), 16, 0, 0);
-      }
-      __syncthreads();  // the direct loads have landed (the barrier waits for them)
-      if constexpr (EPL == 2) {
-        // odd n: entry n-1 sits in a group that runs past the vector
-        if ((n & 1) && n - 1 >= base && n - 1 < base + BLK) {
-          if (tid == 0) xs[n - 1 - base] = gld(yin, n - 1);
-          __syncthreads();
-        }
-      }
-      // four LDS reads in flight per group, then their adds in neighbour order;
-      // a byte offset outside the block (below it, it wraps) clamps to the pad
-      const unsigned base_b = static_cast<unsigned>(base) * static_cast<unsigned>(sizeof(T));
-      const char *xs_b = reinterpret_cast<const char *>(xs);
-#pragma unroll
-      for (int i = 0; i < RPL; ++i)
-#pragma unroll
-        for (int h = 0; h < 8; h += 4) {
-          T xv[4];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const unsigned off = min(static_cast<unsigned>(c[i][h + j]) - base_b, kPadByte);
-            xv[j] = *reinterpret_cast<const T *>(xs_b + off);
-          }
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[i] = add(acc[i], cvt(xv[j]));
-        }
-    }
-    T pv[RPL], yv[RPL];
-    uint32_t mw[RPL];
-#pragma unroll
-    for (int i = 0; i < RPL; ++i) {
-      const int r = te.begin + tid + i * NT;
-      const int rc = r < te.end ? r : te.end - 1;
-      pv[i] = gld(psi, rc);
-      yv[i] = gld(yin, rc);
-      mw[i] = bits[rc >> 5];
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < RPL; ++i) {
-      const int r = te.begin + tid + i * NT;
-      const int rc = r < te.end ? r : te.end - 1;
-      const bool mk = (mw[i] >> (rc & 31)) & 1u;
-      const double2 y_self = mk ? cvt(yv[i]) : make_double2(0.0, 0.0);
-      const T o = pack<T>(horner_out(cvt(pv[i]), acc[i], y_self, mk, alpha, beta));
-      if (r < te.end) {
-        gst(yout, r, o);
-        if (k == 1 && mk && w.hist) atomicAdd(&w.hist[step], abs2(cvt(o)));
-      }
+    switch (w.ell_d) {  // the tile has NT * lds_rows_per_thread(degree) rows at most
+      case 8: ell_lds_tile<T, NT, 8, BLK>(xs, w, te, u); break;
+      case 7: ell_lds_tile<T, NT, 7, BLK>(xs, w, te, u); break;
+      case 6: ell_lds_tile<T, NT, 6, BLK>(xs, w, te, u); break;
+      case 5: ell_lds_tile<T, NT, 5, BLK>(xs, w, te, u); break;
+      case 4: ell_lds_tile<T, NT, 4, BLK>(xs, w, te, u); break;
+      default: ell_lds_tile<T, NT, 3, BLK>(xs, w, te, u); break;
     }
   }
   if (probe || !advance) return;
   // launch ticket, as in k_batch_stage
   __syncthreads();
-  if (tid == 0) {
+  if (threadIdx.x == 0) {
     const unsigned int prev = atomicAdd(&ctl->done, 1u);
     if (prev == gridDim.x - 1) {
       atomicExch(&ctl->done, 0u);
@@ -3465,16 +3484,12 @@ hipError_t ctqw_direct_stage(bool c128, const GraphView &g, const int32_t *wg_ro
 hipError_t batch_ell_lds(bool c128, BatchCtl *ctl, const WalkSlot *slots, const TileEntry *tiles,
                          const int32_t *n_tiles, int grid, int advance, hipStream_t s) {
   if (grid <= 0) return hipSuccess;
-  static_assert(kLdsTileRows64 % kLdsTileThreads64 == 0 && kLdsTileRows128 % kLdsTileThreads128 == 0,
-                "whole rows per thread");
   if (c128)
-    hipLaunchKernelGGL((k_batch_ell_lds<double2, kLdsTileThreads128, kLdsTileRows128 / kLdsTileThreads128,
-                                        kLdsBlockBytes128 / 16>),
-                       dim3(grid), dim3(kLdsTileThreads128), 0, s, ctl, slots, tiles, n_tiles, advance);
+    hipLaunchKernelGGL((k_batch_ell_lds<double2, kLdsTileThreads128, kLdsBlockBytes128 / 16>), dim3(grid),
+                       dim3(kLdsTileThreads128), 0, s, ctl, slots, tiles, n_tiles, advance);
   else
-    hipLaunchKernelGGL((k_batch_ell_lds<float2, kLdsTileThreads64, kLdsTileRows64 / kLdsTileThreads64,
-                                        kLdsBlockBytes64 / 8>),
-                       dim3(grid), dim3(kLdsTileThreads64), 0, s, ctl, slots, tiles, n_tiles, advance);
+    hipLaunchKernelGGL((k_batch_ell_lds<float2, kLdsTileThreads64, kLdsBlockBytes64 / 8>), dim3(grid),
+                       dim3(kLdsTileThreads64), 0, s, ctl, slots, tiles, n_tiles, advance);
   return hipGetLastError();
 }
 

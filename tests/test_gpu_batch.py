@@ -375,3 +375,42 @@ def test_batch_lds_history_and_probe():
                                marked=params["marked"])
         assert abs(hist[s].item() - abs(x[19999]) ** 2) < 1e-12, s
     b.close()
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+def test_batch_lds_tiles_by_degree(dtype):
+    """Tiles of the LDS-staged kernel hold a number of rows that falls with the degree: walks one
+    row longer than one and two tiles of every degree, in one batch, equal the gather kernel
+    bitwise; and so they do with a tile table that has no room for the padding of the balanced
+    layout (one walk of many tiles beside them)."""
+    from paper_2406_08186_amd.walk import Batch
+    rows = {"c64": {3: 9216, 4: 8448, 5: 8448, 6: 7680, 7: 6912, 8: 6912},
+            "c128": {3: 8192, 4: 8192, 5: 7168, 6: 7168, 7: 6144, 8: 6144}}[dtype]
+    entries = []
+    for d, r in rows.items():
+        for n in (r + 1 + (r + 1) * d % 2, 2 * r + 2):
+            g = I.random_regular(n, d, seed=n)
+            pl = _plan(g, "ctqw", dict(gamma=1.0 / d, dt=0.5, taylor_order=9, marked=sorted({n - 1, r}), layout="structured"),
+                       dtype)
+            entries.append((pl, _psi0(pl, n), 2))
+    big = I.random_regular(500000, 6, seed=1)
+    entries.append((_plan(big, "ctqw", dict(gamma=1 / 6, dt=0.5, taylor_order=9, marked=[7], layout="structured"),
+                          dtype), I.uniform(big.n), 1))
+    print(f"[case] batch lds tiles by degree {dtype}", flush=True)
+
+    def run(kernel, max_tiles):
+        b = Batch(capacity=len(entries), max_tiles=max_tiles, dtype=dtype)
+        b.set_stage_kernel(kernel)
+        states = [pl.state(psi0) for pl, psi0, _ in entries]
+        for i, (pl, _, steps) in enumerate(entries):
+            b.set_slot(i, pl, states[i], steps)
+        b.commit()
+        b.run_to_completion()
+        torch.cuda.synchronize()
+        b.close()
+        return states
+
+    want = run("gather", 8192)
+    for max_tiles in (8192, 8 * (500000 // rows[6] + 2)):
+        for i, (x, y) in enumerate(zip(run("lds", max_tiles), want)):
+            assert torch.equal(x, y), (max_tiles, i)
