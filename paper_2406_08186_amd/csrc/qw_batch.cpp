@@ -13,6 +13,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <map>
 #include <mutex>
 #include <new>
@@ -183,6 +184,52 @@ std::vector<TileEntry> lay_out(std::vector<Item> &items, bool xcd_aware) {
   return table;
 }
 
+// Table of the LDS-staged kernel for a grid of `*grid` workgroups, one per
+// compute unit, that take entries grid-stride: every walk's tiles on one XCD
+// (or anywhere, without placement), each tile on the workgroup that has the
+// least to do so far, dearest tiles first.  A tile costs its passes over the
+// vector (staging, then the sums) and a constant, whatever its rows.  Taken in
+// turn instead, 192 walks kept the fullest workgroup busy 1.25 times as long as
+// the mean one (1.04 so), and a few walks left most units idle.
+std::vector<TileEntry> lay_out_lds(std::vector<Item> &items, bool xcd_aware, int *grid) {
+  const int groups = xcd_aware ? 8 : 1, most = kLdsMaxGrid / groups;
+  std::vector<std::vector<const Item *>> of(static_cast<size_t>(groups));
+  std::vector<int64_t> load(static_cast<size_t>(groups), 0);
+  std::vector<size_t> count(static_cast<size_t>(groups), 0);
+  std::sort(items.begin(), items.end(), [](const Item &x, const Item &y) {
+    return x.load * static_cast<int64_t>(x.tiles.size()) > y.load * static_cast<int64_t>(y.tiles.size());
+  });
+  for (const Item &it : items) {
+    const size_t x = static_cast<size_t>(std::min_element(load.begin(), load.end()) - load.begin());
+    load[x] += it.load * static_cast<int64_t>(it.tiles.size());
+    count[x] += it.tiles.size();
+    of[x].push_back(&it);
+  }
+  const int per = static_cast<int>(
+      std::min<size_t>(static_cast<size_t>(most), std::max<size_t>(1, *std::max_element(count.begin(), count.end()))));
+  *grid = std::max(8, groups * per);  // a multiple of 8 with placement
+  std::vector<std::vector<TileEntry>> lists(static_cast<size_t>(*grid));
+  for (int x = 0; x < groups; ++x) {
+    std::sort(of[x].begin(), of[x].end(), [](const Item *p, const Item *q) { return p->load > q->load; });
+    std::vector<std::pair<int64_t, int>> heap;  // (load, workgroup), the least first
+    for (int j = 0; j < per; ++j) heap.emplace_back(0, groups * j + x);
+    const auto more = std::greater<std::pair<int64_t, int>>();
+    for (const Item *it : of[x])
+      for (const TileEntry &t : it->tiles) {
+        std::pop_heap(heap.begin(), heap.end(), more);
+        lists[static_cast<size_t>(heap.back().second)].push_back(t);
+        heap.back().first += it->load;
+        std::push_heap(heap.begin(), heap.end(), more);
+      }
+  }
+  size_t rounds = 0;
+  for (const auto &l : lists) rounds = std::max(rounds, l.size());
+  std::vector<TileEntry> table(rounds * lists.size(), TileEntry{-1, 0, 0, 0});
+  for (size_t b = 0; b < lists.size(); ++b)
+    for (size_t r = 0; r < lists[b].size(); ++r) table[r * lists.size() + b] = lists[b][r];
+  return table;
+}
+
 // Rebuild the tile tables from the active slots.
 int build_table(qw_batch *b) {
   std::vector<Item> items, litems;
@@ -199,6 +246,10 @@ int build_table(qw_batch *b) {
         it.tiles.push_back({s, static_cast<int32_t>(r), static_cast<int32_t>(std::min<int64_t>(p->n, r + R)), 0});
       it.load = p->n_arcs + 3 * p->n;
       if (lds) {
+        const bool c128 = b->dtype == QW_C128;
+        const int64_t block = c128 ? kLdsBlockBytes128 / 16 : kLdsBlockBytes64 / 8;
+        const int64_t slots = static_cast<int64_t>(lds_rows_per_thread(c128, w.ell_d)) * w.ell_d;
+        it.load = 40 + (p->n + block - 1) / block * (40 + slots);
         litems.push_back(std::move(it));
         continue;
       }
@@ -218,7 +269,12 @@ int build_table(qw_batch *b) {
   for (int s = 0; s < b->capacity; ++s)
     has_struct |= b->slots[s].kind == QW_COINED && b->slots[s].structure != kGeneral;
   std::vector<TileEntry> table = lay_out(items, b->xcd_aware);
-  std::vector<TileEntry> ltable = lay_out(litems, b->xcd_aware);
+  int grid_lds = 8;
+  std::vector<TileEntry> ltable = lay_out_lds(litems, b->xcd_aware, &grid_lds);
+  if (static_cast<int64_t>(ltable.size()) > b->max_tiles) {  // its padding does not fit: tiles in turn
+    ltable = lay_out(litems, b->xcd_aware);
+    grid_lds = std::max(8, std::min(kLdsMaxGrid, (static_cast<int>(ltable.size()) + 7) / 8 * 8));
+  }
   if (static_cast<int64_t>(table.size()) > b->max_tiles || static_cast<int64_t>(ltable.size()) > b->max_tiles)
     return set_error(QW_ENOMEM, "batch needs %zu + %zu tiles, capacity is %d per table", table.size(),
                      ltable.size(), b->max_tiles);
@@ -228,7 +284,6 @@ int build_table(qw_batch *b) {
   const bool run_gather = !table.empty() || !has_lds;
   // grids: multiples of 8 (keeps the XCD placement), no larger than the work
   const int grid = std::max(8, std::min(kMaxGrid, (static_cast<int>(table.size()) + 7) / 8 * 8));
-  const int grid_lds = std::max(8, std::min(kLdsMaxGrid, (static_cast<int>(ltable.size()) + 7) / 8 * 8));
   if (has_struct != b->has_struct || has_lds != b->has_lds || run_gather != b->run_gather || grid != b->grid ||
       grid_lds != b->grid_lds) {
     if (b->exec) {
