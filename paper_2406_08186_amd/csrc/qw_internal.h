@@ -99,6 +99,21 @@ constexpr int kSweepMinRowsPerStage = 4;
 constexpr int kCoinedSteps64 = 5, kCoinedSteps128 = 6, kCoinedMatrixSteps128 = 4;
 constexpr int kCoinedAhead = 3;
 
+// Square-lattice sweep: steps per launch by type, and row pairs read ahead.
+// Measured, one wavefront per SIMD (us for 60 steps of 768 x 1100 complex128 and
+// of 760 x 1000 complex64, 24 of 2048^2; two steps per launch through LDS tiles
+// 405, 308, 493 and 377):
+//   steps, pairs ahead       3, 1   4, 1   6, 1   3, 2   4, 2   6, 2   4, 4
+//   768 x 1100 complex128    179    169    160    186    174    179    195
+//   2048^2 complex128        237    193    168    238    198    178    209
+//   760 x 1000 complex64     181    180    178    167    168    182    184
+//   2048^2 complex64         212    192    187    179    177    188    194
+// Reading further ahead unrolls the loop further, and the longer code costs more
+// in instruction fetches than the loads it hides; two wavefronts per SIMD are
+// 5-40% slower (more halo).
+constexpr int kStagSteps64 = 4, kStagSteps128 = 6;
+constexpr int kStagAhead64 = 2, kStagAhead128 = 1;
+
 // Coefficients of one launch of the grid's Chebyshev series (stage st at [st-1]).
 struct SweepSeries {
   double a[5], alpha[5], beta[5];
@@ -303,8 +318,10 @@ hipError_t stag_small(bool c128, const GraphView &g, void *psi, int64_t steps, c
 hipError_t stag_tess(bool c128, const GraphView &g, const StagTess &t, void *psi, bool mark, double *partials,
                      hipStream_t s);
 // Staggered walk on the square lattice (structure kStagLattice, dims {l1, l2}):
-// `steps` (1 or 2) steps, both tessellations each, in one launch, from `in`
-// to `out` (distinct buffers); `ta`, `tb` give the tessellations' (c0, c1).
+// `steps` steps (at most what stag_lattice_steps gives), both tessellations
+// each, in one launch, from `in` to `out` (distinct buffers); `ta`, `tb` give
+// the tessellations' (c0, c1).
+int stag_lattice_steps(bool c128, int64_t left);
 hipError_t stag_lattice_step(bool c128, const GraphView &g, const StagTess &ta, const StagTess &tb, int steps,
                              const void *in, void *out, hipStream_t s);
 

@@ -2002,166 +2002,138 @@ __global__ __launch_bounds__(1024) void k_stag_small(GraphView g, T *psi, int64_
 
 // Staggered walk on the periodic l1 x l2 square lattice (l1, l2 even):
 // tessellation a holds the 2 x 2 squares with top-left corner at even
-// coordinates, tessellation b those at odd coordinates, amplitudes 1/2.  A
-// workgroup owns a tile of kLatRows x kLatCols vertices (top-left corner at
-// even coordinates) and stages it with a halo of two cells on every side
-// (periodic) in LDS in the storage type (each tessellation computes in FP64
-// and rounds once, as the per-tessellation kernels do): the marked flip as
-// it loads, tessellation a on
-// every whole a-square of the staged region, then tessellation b on the
-// b-squares that cover the tile (their corners lie at most one cell outside
-// it, where the halo's a-squares have been applied).  Each vertex of the tile
-// is a corner of exactly one b-square, whose update is stored once.
-constexpr int kLatRows = 16, kLatCols = 64;
-constexpr int kLatR = kLatRows + 4, kLatC = kLatCols + 4;  // staged region
+// coordinates, tessellation b those at odd coordinates, amplitudes 1/2.
+//
+// S steps per launch (streaming temporal blocking).  A wavefront takes 128
+// columns, two per lane (an even one and the next), and sweeps a strip of R
+// core rows plus 2S halo rows above and below from top to bottom, two rows (a
+// pair, the first even) at a time.  Step s takes a pair from the step before
+// it: the marked flip and the a-squares are within the lane; the b-squares lie
+// between the lower row of the pair before and the upper row of this one, and
+// between a lane and the next (the upper lane's column comes down by one-lane
+// wavefront shifts, the square's sum goes back up).  That completes the pair
+// before, which the next step takes in the same iteration; between iterations
+// a step keeps two rows, whatever R is.  The outermost lane and pair become
+// inexact with every step; the core is exact after S.  Every tessellation
+// computes in FP64 and rounds once to the storage type, as the per-tessellation
+// kernels do, with the products fused explicitly so that all depths round
+// alike.  Windows wrap; on lattices smaller than one a vertex is held more than
+// once, and every copy goes through the same updates.
+// Bound by the chain of FP64 operations of one wavefront per SIMD and, on small
+// lattices, by the launches: 2.6 us per step at 768 x 1100 complex128 (LDS tiles
+// of 16 x 64 with two steps per launch: 6.7).
+template <typename T> struct alignas(sizeof(T)) Two {
+  T a, b;
+};
 
-// One square: inner = <alpha|x> with alpha = (1, 1, 1, 1)/2, and
-// x_v <- c0 x_v + c1 (2 (1/2) inner - x_v), which for the reflection form
-// (c0, c1) = (0, 1) is inner - x_v.
-template <bool REFL>
-__device__ __forceinline__ void lat_square(double2 &x0, double2 &x1, double2 &x2, double2 &x3, double2 c0,
-                                           double2 c1) {
-  const double2 inner = scale(add(add(x0, x1), add(x2, x3)), 0.5);
-  if (REFL) {
-    x0 = sub(inner, x0);
-    x1 = sub(inner, x1);
-    x2 = sub(inner, x2);
-    x3 = sub(inner, x3);
-  } else {
-    x0 = add(cmul(c0, x0), cmul(c1, sub(inner, x0)));
-    x1 = add(cmul(c0, x1), cmul(c1, sub(inner, x1)));
-    x2 = add(cmul(c0, x2), cmul(c1, sub(inner, x2)));
-    x3 = add(cmul(c0, x3), cmul(c1, sub(inner, x3)));
-  }
-}
-
+// One vertex of a square with the sum of its four amplitudes, alpha = (1, 1,
+// 1, 1)/2, inner = <alpha|x>: x <- c0 x + c1 (2 (1/2) inner - x), which for the
+// reflection form (c0, c1) = (0, 1) is sum / 2 - x.
 template <typename T, bool REFL>
-__global__ __launch_bounds__(256) void k_stag_lattice(GraphView g, const T *__restrict__ in, T *__restrict__ out,
-                                                      double2 c0a, double2 c1a, double2 c0b, double2 c1b) {
-  __shared__ T sv[kLatR][kLatC];
-  const int l1 = g.dims[0], l2 = g.dims[1];
-  const int tiles_c = (l2 + kLatCols - 1) / kLatCols;
-  // consecutive tiles (a row of tiles, then the next) on one XCD, so the halo
-  // rows a tile shares with the tile row above come from that XCD's L2
-  const int tile = xcd_remap(blockIdx.x, gridDim.x);
-  const int tr = tile / tiles_c, tc = tile - tr * tiles_c;
-  const int r0 = tr * kLatRows, c0 = tc * kLatCols;  // even: kLatRows, kLatCols are even
-  const bool mark = g.n_marked > 0;
-  for (int e = threadIdx.x; e < kLatR * kLatC; e += blockDim.x) {
-    const int i = e / kLatC, j = e - i * kLatC;
-    // periodic: on lattices smaller than the staged region a vertex is staged
-    // more than once, and every copy goes through the same updates
-    int gr = r0 - 2 + i, gc = c0 - 2 + j;
-    gr += gr < 0 ? l1 : 0;
-    gc += gc < 0 ? l2 : 0;
-    while (gr >= l1) gr -= l1;
-    while (gc >= l2) gc -= l2;
-    const int v = gr * l2 + gc;
-    T x = in[v];
-    if (mark && marked(g.markbits, v)) x = pack<T>(scale(cvt(x), -1.0));
-    sv[i][j] = x;
-  }
-  __syncthreads();
-  // tessellation a: squares at region rows/cols (2p, 2q), p < kLatR/2, q < kLatC/2
-  for (int e = threadIdx.x; e < (kLatR / 2) * (kLatC / 2); e += blockDim.x) {
-    const int p = e / (kLatC / 2), q = e - p * (kLatC / 2);
-    const int i = 2 * p, j = 2 * q;
-    double2 x0 = cvt(sv[i][j]), x1 = cvt(sv[i][j + 1]), x2 = cvt(sv[i + 1][j]), x3 = cvt(sv[i + 1][j + 1]);
-    lat_square<REFL>(x0, x1, x2, x3, c0a, c1a);
-    sv[i][j] = pack<T>(x0);
-    sv[i][j + 1] = pack<T>(x1);
-    sv[i + 1][j] = pack<T>(x2);
-    sv[i + 1][j + 1] = pack<T>(x3);
-  }
-  __syncthreads();
-  // tessellation b: squares at region rows/cols (2p+1, 2q+1) covering the tile
-  for (int e = threadIdx.x; e < (kLatRows / 2 + 1) * (kLatCols / 2 + 1); e += blockDim.x) {
-    const int p = e / (kLatCols / 2 + 1), q = e - p * (kLatCols / 2 + 1);
-    const int i = 2 * p + 1, j = 2 * q + 1;
-    double2 x[4] = {cvt(sv[i][j]), cvt(sv[i][j + 1]), cvt(sv[i + 1][j]), cvt(sv[i + 1][j + 1])};
-    lat_square<REFL>(x[0], x[1], x[2], x[3], c0b, c1b);
+__device__ __forceinline__ T lat_update(double2 x, double2 sum, double2 c0, double2 c1) {
+  const double2 t = make_double2(__fma_rn(sum.x, 0.5, -x.x), __fma_rn(sum.y, 0.5, -x.y));
+  if (REFL) return pack<T>(t);
+  return pack<T>(make_double2(__fma_rn(c0.x, x.x, -(c0.y * x.y)) + __fma_rn(c1.x, t.x, -(c1.y * t.y)),
+                              __fma_rn(c0.y, x.x, c0.x * x.y) + __fma_rn(c1.y, t.x, c1.x * t.y)));
+}
+
+template <typename T, bool REFL, int S, bool MARK>
+__device__ __forceinline__ void stag_strip(const GraphView &g, const T *__restrict__ in, T *__restrict__ out,
+                                           int r0, int rows, int row, int gcol, int lane, bool keep, double2 c0a,
+                                           double2 c1a, double2 c0b, double2 c1b) {
+  constexpr int AHEAD = sizeof(T) == 16 ? kStagAhead128 : kStagAhead64;
+  const int l1 = g.dims[0], l2 = g.dims[1], np = rows / 2 + 2 * S;
+  Two<T> nx[AHEAD][2];
+  uint32_t nm[AHEAD];
+  auto fetch = [&](int i, int t) {
+    const int o = row * l2 + gcol;
+    nx[i][0] = *reinterpret_cast<const Two<T> *>(in + o);
+    nx[i][1] = *reinterpret_cast<const Two<T> *>(in + o + l2);
+    if (MARK)
+      nm[i] = ((g.markbits[o >> 5] >> (o & 31)) & 3u) | (((g.markbits[(o + l2) >> 5] >> ((o + l2) & 31)) & 3u) << 2);
+    if (t + 1 < np) row = row + 2 == l1 ? 0 : row + 2;  // the last pair again past the end
+  };
+  // step s: lower row of the last pair after its a-squares, its upper row completed
+  Two<T> low[S], up[S];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int li = i + (k >> 1), lj = j + (k & 1);  // region cell of corner k
-      const int gr = r0 - 2 + li, gc = c0 - 2 + lj;
-      if (li >= 2 && li < 2 + kLatRows && lj >= 2 && lj < 2 + kLatCols && gr < l1 && gc < l2)
-        st(out, gr * l2 + gc, x[k]);
+  for (int s = 0; s < S; ++s) low[s] = up[s] = Two<T>{};
+  uint32_t mh = 0;  // bits 4s ..: marks of the pair step s takes
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) fetch(i, i);
+  T *dst = out + static_cast<int64_t>(r0) * l2 + gcol;
+  for (int t0 = 0; t0 < np; t0 += AHEAD) {
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) {
+      const int t = t0 + i;
+      if (t >= np) break;
+      Two<T> x0 = nx[i][0], x1 = nx[i][1];
+      if (MARK) mh = (mh << 4) | nm[i];
+      const bool flips = MARK && __ballot(mh != 0) != 0;
+      fetch(i, t + AHEAD);
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        if (t < 2 * s) break;  // pairs above what step s needs
+        if (flips) {
+          const uint32_t m = mh >> (4 * s);
+          if (m & 1u) x0.a = pack<T>(scale(cvt(x0.a), -1.0));
+          if (m & 2u) x0.b = pack<T>(scale(cvt(x0.b), -1.0));
+          if (m & 4u) x1.a = pack<T>(scale(cvt(x1.a), -1.0));
+          if (m & 8u) x1.b = pack<T>(scale(cvt(x1.b), -1.0));
+        }
+        {
+          const double2 p = cvt(x0.a), q = cvt(x0.b), r = cvt(x1.a), u = cvt(x1.b);
+          const double2 sum = add(add(p, q), add(r, u));
+          x0.a = lat_update<T, REFL>(p, sum, c0a, c1a);
+          x0.b = lat_update<T, REFL>(q, sum, c0a, c1a);
+          x1.a = lat_update<T, REFL>(r, sum, c0a, c1a);
+          x1.b = lat_update<T, REFL>(u, sum, c0a, c1a);
+        }
+        // the square this lane's odd column and the next lane's even one form
+        const double2 sum_r = add(add(cvt(low[s].b), cvt(lane_shift<kFromUpper>(low[s].a))),
+                                  add(cvt(x0.b), cvt(lane_shift<kFromUpper>(x0.a))));
+        const double2 sum_l = lane_shift<kFromLower>(sum_r);
+        const Two<T> lower{lat_update<T, REFL>(cvt(low[s].a), sum_l, c0b, c1b),
+                           lat_update<T, REFL>(cvt(low[s].b), sum_r, c0b, c1b)};
+        const Two<T> upper{lat_update<T, REFL>(cvt(x0.a), sum_l, c0b, c1b),
+                           lat_update<T, REFL>(cvt(x0.b), sum_r, c0b, c1b)};
+        low[s] = x1;
+        x0 = up[s];
+        x1 = lower;
+        up[s] = upper;
+      }
+      if (t >= 2 * S) {
+        if (keep) {
+          *reinterpret_cast<Two<T> *>(dst) = x0;
+          *reinterpret_cast<Two<T> *>(dst + l2) = x1;
+        }
+        dst += 2 * static_cast<int64_t>(l2);
+      }
     }
   }
 }
 
-// P steps per launch (temporal blocking): the tile is staged with a halo of
-// 2P cells; every step applies the marked flip, tessellation a on every
-// a-square of the staged region and tessellation b on every b-square inside
-// it, writing back to LDS.  The cells whose values are still exact shrink by
-// two per side and step (one for the b-squares at the border, one for the
-// a-squares' alignment), so after P steps the tile is exact and is stored row
-// by row.  Two steps per launch measured fastest on 4096^2 (c64 50.0, c128
-// 77.1 us per step; three: 46.6 / 84.6; four: 49.4 / 96.1).
-template <typename T, bool REFL, int P>
-__global__ __launch_bounds__(256) void k_stag_lattice_p(GraphView g, const T *__restrict__ in, T *__restrict__ out,
-                                                        double2 c0a, double2 c1a, double2 c0b, double2 c1b) {
-  constexpr int H = 2 * P, R = kLatRows + 2 * H, C = kLatCols + 2 * H;
-  __shared__ T sv[R][C];
-  __shared__ uint8_t mk[R][C];  // marked cells, flipped again at every later step
+template <typename T, bool REFL, int S>
+__global__ __launch_bounds__(64 * kStripWaves) void k_stag_sweep(GraphView g, const T *__restrict__ in,
+                                                                 T *__restrict__ out, int R, double2 c0a, double2 c1a,
+                                                                 double2 c0b, double2 c1b) {
+  constexpr int CORE = 128 - 4 * S;
   const int l1 = g.dims[0], l2 = g.dims[1];
-  const int tiles_c = (l2 + kLatCols - 1) / kLatCols;
-  const int tile = xcd_remap(blockIdx.x, gridDim.x);
+  const int tiles_c = (l2 + CORE - 1) / CORE, tiles_r = (l1 + R - 1) / R;
+  const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  const int tile = xcd_remap(blockIdx.x, gridDim.x) * kStripWaves + wv;
+  if (tile >= tiles_r * tiles_c) return;  // whole wavefront
+  const int lane = threadIdx.x & 63;
   const int tr = tile / tiles_c, tc = tile - tr * tiles_c;
-  const int r0 = tr * kLatRows, c0 = tc * kLatCols;
-  const bool mark = g.n_marked > 0;
-  for (int e = threadIdx.x; e < R * C; e += blockDim.x) {
-    const int i = e / C, j = e - i * C;
-    int gr = r0 - H + i, gc = c0 - H + j;  // periodic, also on lattices smaller than the region
-    while (gr < 0) gr += l1;
-    while (gc < 0) gc += l2;
-    while (gr >= l1) gr -= l1;
-    while (gc >= l2) gc -= l2;
-    const int v = gr * l2 + gc;
-    T x = in[v];
-    const bool m = mark && marked(g.markbits, v);
-    if (m) x = pack<T>(scale(cvt(x), -1.0));
-    sv[i][j] = x;
-    mk[i][j] = m ? 1 : 0;
-  }
-  __syncthreads();
-#pragma unroll 1
-  for (int s = 0; s < P; ++s) {
-    if (s > 0 && mark) {
-      for (int e = threadIdx.x; e < R * C; e += blockDim.x) {
-        const int i = e / C, j = e - i * C;
-        if (mk[i][j]) sv[i][j] = pack<T>(scale(cvt(sv[i][j]), -1.0));
-      }
-      __syncthreads();
-    }
-    for (int e = threadIdx.x; e < (R / 2) * (C / 2); e += blockDim.x) {
-      const int p = e / (C / 2), q = e - p * (C / 2);
-      const int i = 2 * p, j = 2 * q;
-      double2 x0 = cvt(sv[i][j]), x1 = cvt(sv[i][j + 1]), x2 = cvt(sv[i + 1][j]), x3 = cvt(sv[i + 1][j + 1]);
-      lat_square<REFL>(x0, x1, x2, x3, c0a, c1a);
-      sv[i][j] = pack<T>(x0);
-      sv[i][j + 1] = pack<T>(x1);
-      sv[i + 1][j] = pack<T>(x2);
-      sv[i + 1][j + 1] = pack<T>(x3);
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < ((R - 2) / 2) * ((C - 2) / 2); e += blockDim.x) {
-      const int p = e / ((C - 2) / 2), q = e - p * ((C - 2) / 2);
-      const int i = 2 * p + 1, j = 2 * q + 1;
-      double2 x0 = cvt(sv[i][j]), x1 = cvt(sv[i][j + 1]), x2 = cvt(sv[i + 1][j]), x3 = cvt(sv[i + 1][j + 1]);
-      lat_square<REFL>(x0, x1, x2, x3, c0b, c1b);
-      sv[i][j] = pack<T>(x0);
-      sv[i][j + 1] = pack<T>(x1);
-      sv[i + 1][j] = pack<T>(x2);
-      sv[i + 1][j + 1] = pack<T>(x3);
-    }
-    __syncthreads();
-  }
-  for (int e = threadIdx.x; e < kLatRows * kLatCols; e += blockDim.x) {
-    const int i = e / kLatCols, j = e - i * kLatCols;
-    const int gr = r0 + i, gc = c0 + j;
-    if (gr < l1 && gc < l2) out[gr * l2 + gc] = sv[H + i][H + j];
-  }
+  const int r0 = tr * R, col = tc * CORE + 2 * (lane - S);  // even: R and CORE are even
+  int row = (r0 - 2 * S) % l1, gcol = col % l2;
+  row += row < 0 ? l1 : 0;
+  gcol += gcol < 0 ? l2 : 0;
+  const bool keep = lane >= S && lane < 64 - S && col < l2;
+  const int rows = min(R, l1 - r0);
+  if (g.n_marked > 0)
+    stag_strip<T, REFL, S, true>(g, in, out, r0, rows, row, gcol, lane, keep, c0a, c1a, c0b, c1b);
+  else
+    stag_strip<T, REFL, S, false>(g, in, out, r0, rows, row, gcol, lane, keep, c0a, c1a, c0b, c1b);
 }
 
 // Many independent small walks in one launch: workgroup b runs walk b whole,
@@ -3236,31 +3208,62 @@ size_t ctqw_small_lds(bool c128, int n, int n_arcs) {
          4 * ((static_cast<size_t>(n) + 31) / 32);
 }
 
+// Core rows of a strip of the square-lattice sweep: one wavefront per SIMD.
+template <int S> int stag_strip_rows(int l1, int l2) {
+  constexpr int core = 128 - 4 * S;
+  const int want = std::max(1, kSimds / ((l2 + core - 1) / core));
+  return 2 * ((l1 / 2 + want - 1) / want);
+}
+
+template <typename T, bool REFL, int S>
+void launch_stag_sweep(const GraphView &g, const void *in, void *out, const StagTess &ta, const StagTess &tb,
+                       hipStream_t s) {
+  constexpr int core = 128 - 4 * S;
+  const int R = stag_strip_rows<S>(g.dims[0], g.dims[1]);
+  const int64_t strips = static_cast<int64_t>((g.dims[0] + R - 1) / R) * ((g.dims[1] + core - 1) / core);
+  hipLaunchKernelGGL((k_stag_sweep<T, REFL, S>), dim3(static_cast<unsigned>((strips + kStripWaves - 1) / kStripWaves)),
+                     dim3(64 * kStripWaves), 0, s, g, static_cast<const T *>(in), static_cast<T *>(out), R,
+                     make_double2(ta.c0[0], ta.c0[1]), make_double2(ta.c1[0], ta.c1[1]),
+                     make_double2(tb.c0[0], tb.c0[1]), make_double2(tb.c1[0], tb.c1[1]));
+}
+
 template <typename T, bool REFL>
-void launch_stag_lattice(const GraphView &g, int steps, dim3 grid, const void *in, void *out, double2 c0a,
-                         double2 c1a, double2 c0b, double2 c1b, hipStream_t s) {
-  const T *x = static_cast<const T *>(in);
-  T *y = static_cast<T *>(out);
-  if (steps == 2)
-    hipLaunchKernelGGL((k_stag_lattice_p<T, REFL, 2>), grid, dim3(256), 0, s, g, x, y, c0a, c1a, c0b, c1b);
-  else
-    hipLaunchKernelGGL((k_stag_lattice<T, REFL>), grid, dim3(256), 0, s, g, x, y, c0a, c1a, c0b, c1b);
+hipError_t launch_stag_lattice(const GraphView &g, int steps, const void *in, void *out, const StagTess &ta,
+                               const StagTess &tb, hipStream_t s) {
+  switch (steps) {
+    case 1: launch_stag_sweep<T, REFL, 1>(g, in, out, ta, tb, s); break;
+    case 2: launch_stag_sweep<T, REFL, 2>(g, in, out, ta, tb, s); break;
+    case 3: launch_stag_sweep<T, REFL, 3>(g, in, out, ta, tb, s); break;
+    case 4: launch_stag_sweep<T, REFL, 4>(g, in, out, ta, tb, s); break;
+    case 5:
+    case 6:
+      if constexpr (sizeof(T) == 16) {
+        if (steps == 5) launch_stag_sweep<T, REFL, 5>(g, in, out, ta, tb, s);
+        else launch_stag_sweep<T, REFL, 6>(g, in, out, ta, tb, s);
+        break;
+      }
+      return hipErrorInvalidValue;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+int stag_lattice_steps(bool c128, int64_t left) {
+  // launches of nearly equal depth: a single step costs twice its share of a deep launch
+  const int most = c128 ? kStagSteps128 : kStagSteps64;
+  const int64_t launches = (left + most - 1) / most;
+  return static_cast<int>((left + launches - 1) / launches);
 }
 
 hipError_t stag_lattice_step(bool c128, const GraphView &g, const StagTess &ta, const StagTess &tb, int steps,
                              const void *in, void *out, hipStream_t s) {
-  if (steps != 1 && steps != 2) return hipErrorInvalidValue;
-  const int l1 = g.dims[0], l2 = g.dims[1];
-  const dim3 grid(static_cast<unsigned>(((l1 + kLatRows - 1) / kLatRows) * ((l2 + kLatCols - 1) / kLatCols)));
-  const double2 c0a = make_double2(ta.c0[0], ta.c0[1]), c1a = make_double2(ta.c1[0], ta.c1[1]);
-  const double2 c0b = make_double2(tb.c0[0], tb.c0[1]), c1b = make_double2(tb.c1[0], tb.c1[1]);
   const bool refl = ta.c0[0] == 0.0 && ta.c0[1] == 0.0 && ta.c1[0] == 1.0 && ta.c1[1] == 0.0 && tb.c0[0] == 0.0 &&
                     tb.c0[1] == 0.0 && tb.c1[0] == 1.0 && tb.c1[1] == 0.0;
-  if (c128 && refl) launch_stag_lattice<double2, true>(g, steps, grid, in, out, c0a, c1a, c0b, c1b, s);
-  else if (c128) launch_stag_lattice<double2, false>(g, steps, grid, in, out, c0a, c1a, c0b, c1b, s);
-  else if (refl) launch_stag_lattice<float2, true>(g, steps, grid, in, out, c0a, c1a, c0b, c1b, s);
-  else launch_stag_lattice<float2, false>(g, steps, grid, in, out, c0a, c1a, c0b, c1b, s);
-  return hipGetLastError();
+  if (c128)
+    return refl ? launch_stag_lattice<double2, true>(g, steps, in, out, ta, tb, s)
+                : launch_stag_lattice<double2, false>(g, steps, in, out, ta, tb, s);
+  return refl ? launch_stag_lattice<float2, true>(g, steps, in, out, ta, tb, s)
+              : launch_stag_lattice<float2, false>(g, steps, in, out, ta, tb, s);
 }
 
 size_t stag_small_lds(bool c128, int n) { return (c128 ? 16 : 8) * static_cast<size_t>(n); }
