@@ -809,6 +809,23 @@ int build_plan(const qw_csr *g, const qw_walk_desc *w, qw_plan *p) {
   return ok();
 }
 
+// How a one-workgroup staggered walk keeps its polygons in registers: 1, one
+// per thread, of at most kStagRegSize vertices each; 2 or 4, several of that
+// size per thread, uniform amplitudes; 0, not at all.  Measured, 48 steps of a
+// 120 x 140 square lattice complex64: 4 263 us, 0 819 us; 12000-cycle of edges: 2 201 us, 0 674.
+int small_stag_regs(const qw_plan *p) {
+  if (p->structure != kSmall || p->stag.size() > 2) return 0;
+  bool single = true;
+  int size = p->stag[0].small_size;
+  if (size != 2 && size != 4) size = 0;
+  for (const StagTess &t : p->stag) {
+    if (t.n_big > 0) return 0;
+    single = single && t.max_small <= kStagRegSize && t.n_small <= 1024;
+    if (t.small_size != size || t.off_amp >= 0 || t.n_small == 0) size = 0;
+  }
+  return single ? 1 : size;
+}
+
 int check_bound(const qw_plan *p) {
   if (!p) return fail(QW_EINVAL, "null plan");
   if (!p->d_graph) return fail(QW_ESTATE, "plan not uploaded (call qw_plan_upload first)");
@@ -1212,9 +1229,7 @@ int qw_plan_upload(qw_plan *p, void *d_graph, size_t graph_bytes, void *stream) 
   if (!p->stag.empty()) {
     g.stag = reinterpret_cast<const StagTess *>(base + p->off_stag);
     g.n_tess = static_cast<int32_t>(p->stag.size());
-    g.stag_regs = p->structure == kSmall && g.n_tess <= 2;
-    for (const StagTess &t : p->stag)
-      g.stag_regs = g.stag_regs && t.n_big == 0 && t.max_small <= kStagRegSize && t.n_small <= 1024;
+    g.stag_regs = small_stag_regs(p);
   }
   if (p->structure == kDense) {
     g.ld = p->ld;

@@ -205,7 +205,7 @@ struct GraphView {
   const unsigned char *base = nullptr; // start of the plan's device buffer
   const StagTess *stag = nullptr;      // staggered: device array of n_tess descriptors
   int32_t n_tess = 0;
-  int32_t stag_regs = 0;               // staggered, one workgroup: polygons kept in registers
+  int32_t stag_regs = 0;               // staggered, one workgroup: polygons kept in registers (small_stag_regs)
 };
 
 // A Chebyshev series of a one-workgroup CTQW walk (terms == 0: none).

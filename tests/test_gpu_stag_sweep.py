@@ -41,3 +41,32 @@ def test_sweep_equals_single_steps(l1, l2, form, dtype):
     assert (np.abs(err).max() < 1e-12) if dtype == "c128" else (np.linalg.norm(err) < 1e-5)
     assert np.abs(p.cpu().numpy() - np.abs(ref) ** 2).max() < (1e-12 if dtype == "c128" else 1e-6)
     assert abs(float(pm) - float((np.abs(ref) ** 2)[marked].sum())) < (1e-12 if dtype == "c128" else 1e-6)
+
+
+def _edges(n):
+    ptr, v = np.arange(0, n + 1, 2), np.arange(n)
+    return I.cycle(n), [I.Tessellation(ptr, v, None, None), I.Tessellation(ptr, np.roll(v, -1), None, None)]
+
+
+@pytest.mark.parametrize("name,dtype", [("64x66", "c64"), ("138x144", "c64"), ("64x66", "c128"), ("96x104", "c128"),
+                                        (2050, "c64"), (19968, "c64"), (2050, "c128"), (9984, "c128")])
+@pytest.mark.parametrize("form", ["reflection", "hamiltonian"])
+def test_one_workgroup_more_polygons_than_threads(name, dtype, form):
+    """Several polygons of two or four vertices per thread, up to the largest
+    graphs the LDS holds, one and two tessellations."""
+    from paper_2406_08186_amd.walk import Plan
+    print(f"[case] one-workgroup staggered {name} {form} {dtype}", flush=True)
+    g, tess = I.stag_lattice(*map(int, name.split("x"))) if isinstance(name, str) else _edges(name)
+    if form == "hamiltonian":
+        tess = [I.Tessellation(t.poly_ptr, t.poly_vert, None, a) for t, a in zip(tess, (0.83, -0.41))]
+    marked = [0, 1025, g.n - 1]
+    pl = Plan(g, "staggered", dtype=dtype, marked=marked, tessellations=tess)
+    assert pl.structure == "small"
+    psi0 = I.random_state(g.n, 3)
+    x = pl.state(psi0)
+    p, norm, pm = pl.evolve(x, 9, readout=True)
+    torch.cuda.synchronize()
+    ref = oracle.staggered_evolve(g.n, tess, psi0, 9, marked=marked)
+    err = x.cpu().numpy().astype(np.complex128) - ref
+    assert (np.abs(err).max() < 1e-12) if dtype == "c128" else (np.linalg.norm(err) < 1e-5)
+    assert abs(float(pm) - float((np.abs(ref) ** 2)[marked].sum())) < (1e-12 if dtype == "c128" else 1e-6)
