@@ -241,7 +241,9 @@ typedef struct qw_plan_info {
   size_t work_bytes;       /* device workspace qw_evolve/qw_probabilities need*/
   int32_t columns;         /* walks per state (dense layout), else 1          */
   int32_t block_depth;     /* CTQW on a torus: Horner stages per launch (> 1
-                              when temporal blocking applies), else 1         */
+                              when temporal blocking applies), else 1; the
+                              complex64 sweep of small and large grids may
+                              run them in deeper launches                     */
 } qw_plan_info;
 
 /* The walk constructors of the paper's user interface: ContinuousTime(graph,

@@ -326,8 +326,9 @@ std::vector<uint8_t> strip_marks(const StripGrid &sg, int l1, int l2, const std:
       if ((gr - lo + l1) % l1 < sg.rows + 2 * S) rows_hit.push_back(t);
     }
     for (int t = 0; t < sg.tiles_c; ++t) {
-      const int lo = ((std::min(t * sg.core, l2 - sg.core) - S) % l2 + l2) % l2;
-      if ((gc - lo + l2) % l2 < sg.width) cols_hit.push_back(t);
+      // a column more: two-column windows on odd grids may start one early
+      const int lo = ((std::min(t * sg.core, l2 - sg.core) - S - 1) % l2 + l2) % l2;
+      if ((gc - lo + l2) % l2 < sg.width + 1) cols_hit.push_back(t);
     }
     for (int a : rows_hit)
       for (int b : cols_hit) mark[static_cast<size_t>(a) * sg.tiles_c + b] = 1;
@@ -650,8 +651,14 @@ int build_plan(const qw_csr *g, const qw_walk_desc *w, qw_plan *p) {
     tv.dims[1] = p->dims[1];
     p->block_depth = torus_block_depth(c128, tv, p->K);
     if (p->block_depth > 1) {
-      p->strip_rows = torus_strips(c128, p->dims[0], p->dims[1], p->block_depth).rows;
-      tmark = strip_marks(torus_strips(c128, p->dims[0], p->dims[1], p->block_depth), p->dims[0], p->dims[1], mlist);
+      StripGrid sg = torus_strips(c128, p->dims[0], p->dims[1], p->block_depth);
+      const StripGrid dg = c128 ? StripGrid{} : deep_strips(p->dims[0], p->dims[1], p->K, p->block_depth, &p->deep_depth);
+      if (dg.count() > 0) {
+        sg = dg;
+        p->strip_core = dg.core;
+      }
+      p->strip_rows = sg.rows;
+      tmark = strip_marks(sg, p->dims[0], p->dims[1], mlist);
       p->has_tmark = true;
     }
     for (int S : {5, 4, 3, 2}) {
@@ -1039,15 +1046,21 @@ int evolve_ctqw(const qw_plan *p, void *psi, unsigned char *work, int64_t steps,
       a64[k] = alpha[k];
       b64[k] = beta[k];
     }
-    const int S = p->block_depth, per = K / S;
+    const int S = p->block_depth;
+    const int depth = p->strip_core ? p->deep_depth : 0;
     void *pc = psi, *pa = work + p->off_w2;
     void *ybuf[2] = {w0, w1};
     for (int64_t i = 0; i < steps; ++i) {
-      for (int j = 0; j < per; ++j) {
-        const void *yin = (j == 0) ? pc : ybuf[(j - 1) & 1];
-        void *out = (j == per - 1) ? pa : ybuf[j & 1];
-        QW_TRY(torus_block_stages(c128, g, S, pc, yin, out, K - j * S, a64.data(), b64.data(), s),
-               "grid CTQW blocked stages kernel");
+      const void *yin = pc;
+      for (int k = K, j = 0; k > 0; ++j) {
+        const int left = depth ? (k + depth - 1) / depth : 1;  // launches of nearly equal depth
+        const int m = depth ? (k + left - 1) / left : S;
+        void *out = k == m ? pa : ybuf[j & 1];
+        if (depth) QW_TRY(torus_deep(g, p->strip_core, m, pc, yin, out, k, a64.data(), b64.data(), s), "grid CTQW sweep kernel");
+        else QW_TRY(torus_block_stages(c128, g, m, pc, yin, out, k, a64.data(), b64.data(), s),
+                    "grid CTQW blocked stages kernel");
+        yin = out;
+        k -= m;
       }
       std::swap(pc, pa);
     }

@@ -114,6 +114,27 @@ constexpr int kCoinedAhead = 3;
 constexpr int kStagSteps64 = 4, kStagSteps128 = 6;
 constexpr int kStagAhead64 = 2, kStagAhead128 = 1;
 
+// Two-column complex64 grid sweep: stages per launch, K split into launches of
+// nearly equal depth.  Measured against the one-column sweep (S = 5, or the
+// largest of 5, 4, 3, 2 that divides K; us per step; waves per SIMD in brackets):
+//                           one col.  6 (1)  6 (2)  7 (1)  10 (1)  10 (2)
+//   128^2        K 20          31.6    16.8   16.8   19.2   22.4   22.4
+//   300 x 301    K 12 marked   24.1    17.3   17.2   17.3   17.2   17.4
+//   700 x 300    K 20          31.8    21.6   24.4   21.6   25.8   28.8
+//   601 x 777    K 15          24.1    19.7   20.9   19.2   20.3   22.0
+//   601 x 777    K 20 marked   41.4    35.5   35.1   36.9   37.7   37.5
+//   601 x 777    K 14 marked   33.0    24.9   24.4   26.3   26.4   25.2
+//   1024^2       K 20          33.7    35.1   33.9   34.7   38.4   37.9
+//   1024^2       K 20 marked   38.2    50.3   41.8   49.4   49.5   44.7
+//   2048^2       K 20          78.8    82.1   81.1   76.2   76.5   66.8
+//   2048^2       K 20 marked   89.4     116   97.3    108   98.1   78.9
+//   3000^2       K 20           153     173    154    145    136    104
+// Small grids are bound by launches and by the chain of one wavefront's stages,
+// large ones by memory, which deep launches pass less often; between them
+// neither leads and one column stays, unless K only divides by 2 or 3.
+constexpr int kDeepStages = 10, kDeepStagesSmall = 6, kDeepUnroll = 3;
+constexpr int64_t kDeepSmall = 700000, kDeepLarge = int64_t{1} << 21;
+
 // Coefficients of one launch of the grid's Chebyshev series (stage st at [st-1]).
 struct SweepSeries {
   double a[5], alpha[5], beta[5];
@@ -299,6 +320,12 @@ hipError_t dense_stage(bool c128, const GraphView &g, const void *y, const void 
 // from (P, Yin) to Out (Yin may equal P at the first stage of a step).
 // alpha/beta hold 64 entries (stage k at [k-1]).
 int torus_block_depth(bool c128, const GraphView &g, int K);
+// The two-column complex64 sweep for order K: its strips (count 0: the grid is
+// not for it) and the stages of its deepest launch; and a launch of S stages,
+// kfirst down, on the strips of g, `core` columns each.
+StripGrid deep_strips(int l1, int l2, int K, int block_depth, int *depth);
+hipError_t torus_deep(const GraphView &g, int core, int S, const void *P, const void *Yin, void *Out, int kfirst,
+                      const double *alpha, const double *beta, hipStream_t s);
 StripGrid torus_strips(bool c128, int l1, int l2, int S);
 hipError_t torus_block_stages(bool c128, const GraphView &g, int S, const void *P, const void *Yin, void *Out,
                               int kfirst, const double *alpha, const double *beta, hipStream_t s);

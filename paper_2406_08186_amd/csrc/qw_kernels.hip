@@ -1224,13 +1224,19 @@ struct Coefs {
   double alpha[64];
   double beta[64];
 };
-// The same coefficients for FP32 arithmetic, each split into a float head and
-// the float rounding of its remainder (alpha = hi + lo to about 2^-48
-// relative), so that no coefficient of the propagator carries an FP32 rounding
-// error from step to step: only the arithmetic rounds.
-struct CoefsF32 {
-  float ahi[64], alo[64];
-  float bhi[64], blo[64];
+// The coefficients of one launch of N stages (stage st at [st-1]), and the same
+// for FP32 arithmetic, each split into a float head and the float rounding of
+// its remainder (alpha = hi + lo to about 2^-48 relative), so that no
+// coefficient of the propagator carries an FP32 rounding error from step to
+// step: only the arithmetic rounds.  Only the launch's own: read at the start of
+// every launch, a whole order's 64 per array cost 0.2 us of 8.3 on 1024^2, 0.8 of
+// 9.3 with marks.
+template <int N> struct StageCoefs {
+  double alpha[N], beta[N];
+};
+template <int N> struct StageCoefsF32 {
+  float ahi[N], alo[N];
+  float bhi[N], blo[N];
 };
 
 // ---- grid CTQW, streaming temporal blocking ----------------------------------------
@@ -1246,7 +1252,7 @@ struct CoefsF32 {
 // the core 64 - 2S lanes are exact after S stages.  Stage s starts at t = 2s,
 // where its rows become exact, and the last stage stores each core row as soon
 // as it is computed.  The sweep computes in its storage type: complex128 in
-// FP64, complex64 in FP32 with split coefficients (CoefsF32), which halves the
+// FP64, complex64 in FP32 with split coefficients, which halves the
 // lane shifts (one DPP move per float instead of two per double) and needs no
 // conversions; the neighbours are summed in the one-stage kernel's order.
 // Strips at the grid's right and bottom edges are clamped and overlap their
@@ -1255,9 +1261,9 @@ constexpr int kSweepRing = 6;  // rows per unrolled body; holds psi for S <= 5 s
 
 __device__ __forceinline__ constexpr int pmod(int a, int m) { return ((a % m) + m) % m; }
 
-template <typename T> struct SweepCoefs;
-template <> struct SweepCoefs<double2> { using type = Coefs; };
-template <> struct SweepCoefs<float2> { using type = CoefsF32; };
+template <typename T, int N> struct SweepCoefs;
+template <int N> struct SweepCoefs<double2, N> { using type = StageCoefs<N>; };
+template <int N> struct SweepCoefs<float2, N> { using type = StageCoefsF32<N>; };
 
 __device__ __forceinline__ float2 sweep_add(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ double2 sweep_add(double2 a, double2 b) { return add(a, b); }
@@ -1265,11 +1271,21 @@ __device__ __forceinline__ float2 sweep_zero(float2) { return make_float2(0.0f, 
 __device__ __forceinline__ double2 sweep_zero(double2) { return make_double2(0.0, 0.0); }
 
 // psi + i (alpha nsum + beta [marked] y) at stage k (index k - 1)
-__device__ __forceinline__ double2 sweep_out(double2 psi, double2 nsum, double2 yv, bool mk, const Coefs &c,
+template <int N>
+__device__ __forceinline__ double2 sweep_out(double2 psi, double2 nsum, double2 yv, bool mk, const StageCoefs<N> &c,
                                              int ki) {
   return horner_out(psi, nsum, yv, mk, c.alpha[ki], c.beta[ki]);
 }
-__device__ __forceinline__ float2 sweep_out(float2 psi, float2 nsum, float2 yv, bool mk, const CoefsF32 &c,
+template <int N>
+__device__ __forceinline__ float2 sweep_mark(float2 out, float2 yv, const StageCoefsF32<N> &c, int ki) {
+  float re = __fmaf_rn(-c.bhi[ki], yv.y, out.x);
+  float im = __fmaf_rn(c.bhi[ki], yv.x, out.y);
+  re = __fmaf_rn(-c.blo[ki], yv.y, re);
+  im = __fmaf_rn(c.blo[ki], yv.x, im);
+  return make_float2(re, im);
+}
+template <int N>
+__device__ __forceinline__ float2 sweep_out(float2 psi, float2 nsum, float2 yv, bool mk, const StageCoefsF32<N> &c,
                                             int ki) {
   float re = __fmaf_rn(-c.ahi[ki], nsum.y, psi.x);
   float im = __fmaf_rn(c.ahi[ki], nsum.x, psi.y);
@@ -1284,9 +1300,13 @@ __device__ __forceinline__ float2 sweep_out(float2 psi, float2 nsum, float2 yv, 
   return make_float2(re, im);
 }
 
+template <typename T> struct alignas(sizeof(T)) Two {
+  T a, b;
+};
+
 template <typename T, int S, bool YP, bool MARK>
 __device__ __forceinline__ void sweep_strip(const GraphView &g, const T *__restrict__ P, const T *__restrict__ Yin,
-                                            T *__restrict__ Out, int kfirst, const typename SweepCoefs<T>::type &c,
+                                            T *__restrict__ Out, const typename SweepCoefs<T, S>::type &c,
                                             int R, int rb, int lane, int gcol, unsigned boff) {
   constexpr int RING = kSweepRing, W = 64;
   static_assert(S >= 2 && S < RING, "psi ring holds rows t-S .. t");
@@ -1361,7 +1381,7 @@ __device__ __forceinline__ void sweep_strip(const GraphView &g, const T *__restr
         sum = sweep_add(sum, dn);
         sum = sweep_add(sum, up);
         const bool m = MARK && ((mr >> st) & 1u);
-        const T val = sweep_out(pr[pmod(i - st, RING)], sum, self, m, c, kfirst - st);
+        const T val = sweep_out(pr[pmod(i - st, RING)], sum, self, m, c, st - 1);
         if (st < S) {
           yv[st][pmod(i - st, 3)] = val;
         } else if (lane >= S && lane < W - S) {
@@ -1380,8 +1400,8 @@ __device__ __forceinline__ void sweep_strip(const GraphView &g, const T *__restr
 template <typename T, int S, bool YP>
 __global__ __launch_bounds__(64 * kStripWaves) void k_ctqw_torus_sweep(GraphView g, const T *__restrict__ P,
                                                                        const T *__restrict__ Yin,
-                                                                       T *__restrict__ Out, int kfirst,
-                                                                       typename SweepCoefs<T>::type c) {
+                                                                       T *__restrict__ Out,
+                                                                       typename SweepCoefs<T, S>::type c) {
   constexpr int CORE = 64 - 2 * S;
   const int l1 = g.dims[0], l2 = g.dims[1], R = g.strip_rows;
   const int tiles_c = (l2 + CORE - 1) / CORE, tiles_r = (l1 + R - 1) / R;
@@ -1397,9 +1417,129 @@ __global__ __launch_bounds__(64 * kStripWaves) void k_ctqw_torus_sweep(GraphView
   gcol -= gcol >= l2 ? l2 : 0;
   const unsigned boff = static_cast<unsigned>(gcol) * static_cast<unsigned>(sizeof(T));
   if (g.tmark[tile])
-    sweep_strip<T, S, YP, true>(g, P, Yin, Out, kfirst, c, R, rb, lane, gcol, boff);
+    sweep_strip<T, S, YP, true>(g, P, Yin, Out, c, R, rb, lane, gcol, boff);
   else
-    sweep_strip<T, S, YP, false>(g, P, Yin, Out, kfirst, c, R, rb, lane, gcol, boff);
+    sweep_strip<T, S, YP, false>(g, P, Yin, Out, c, R, rb, lane, gcol, boff);
+}
+
+// The complex64 sweep on small and large grids of at least 128 columns (rule and
+// measurements at kDeepStages): up to ten stages per launch, two neighbouring columns per lane.  A cell's neighbour in the same
+// lane costs no shift, a window of 128 columns loses fewer of them to the halo,
+// and fewer launches of a time step are left.  Same arithmetic, same bits.
+// psi moves down its queue by U rows per body of U rows.  The loop is one body
+// with its warm-up tests inside: a strip is only a few bodies long, and the
+// unrolled code of special first, middle and last ones costs more in instruction
+// fetches than the tests do.
+template <int S, bool YP, bool MARK>
+__device__ __forceinline__ void deep_strip(const GraphView &g, const float2 *__restrict__ P,
+                                           const float2 *__restrict__ Yin, float2 *__restrict__ Out,
+                                           const StageCoefsF32<S> &c, int R, int rb, int lane, int gcol) {
+  using T2 = Two<float2>;
+  constexpr int U = kDeepUnroll, H = S + (S & 1);
+  static_assert(U % 3 == 0, "stages keep their rows by window row mod 3");
+  const int l1 = g.dims[0], l2 = g.dims[1], n_in = R + 2 * S, mlast = (g.n + 31) / 32 * 4 - 2;
+  auto off = [&](int t) -> int {
+    const int gr = rb + t;  // < 2 l1 since n_in <= l1
+    return (gr >= l1 ? gr - l1 : gr) * l2 + gcol;
+  };
+  T2 ny[U], np[U];
+  uint32_t nm[U];
+  auto fetch = [&](int t0) {
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      const int o = off(min(t0 + i, n_in - 1));
+      np[i] = *reinterpret_cast<const T2 *>(P + o);
+      ny[i] = YP ? np[i] : *reinterpret_cast<const T2 *>(Yin + o);
+      if (MARK) {  // two bytes from the first cell's on, within the bitmap's words
+        const int b = min(o >> 3, mlast);
+        uint16_t w;
+        __builtin_memcpy(&w, reinterpret_cast<const unsigned char *>(g.markbits) + b, 2);
+        nm[i] = (static_cast<uint32_t>(w) >> (o - 8 * b)) & 3u;
+      }
+    }
+  };
+  T2 yv[S][3];    // stage s-1 (s = 1 .. S) rows, slot = window row mod 3
+  T2 pr[S + U];   // psi of window rows t0 - S .. t0 + U - 1
+  uint32_t mr = 0;  // bits 2k ..: marks of window row t - k
+#pragma unroll
+  for (int s = 0; s < S; ++s)
+#pragma unroll
+    for (int j = 0; j < 3; ++j) yv[s][j] = T2{};
+#pragma unroll
+  for (int j = 0; j < S + U; ++j) pr[j] = T2{};
+  fetch(0);
+  for (int t0 = 0; t0 < n_in; t0 += U) {
+    T2 cy[U];
+    uint32_t cm[U];
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      cy[i] = ny[i];
+      pr[S + i] = np[i];
+      if (MARK) cm[i] = nm[i];
+    }
+    if (t0 + U < n_in) fetch(t0 + U);
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      const int t = t0 + i;
+      if (t >= n_in) break;
+      yv[0][i % 3] = cy[i];
+      if (MARK) mr = (mr << 2) | cm[i];
+      const bool any = MARK && __ballot(mr >> 2 & ((1u << (2 * S)) - 1)) != 0;
+#pragma unroll
+      for (int st = 1; st <= S; ++st) {
+        if (t < 2 * st) continue;  // window rows above stage st's exact region
+        const T2 up = yv[st - 1][pmod(i - st - 1, 3)];
+        const T2 self = yv[st - 1][pmod(i - st, 3)];
+        const T2 dn = yv[st - 1][pmod(i - st + 1, 3)];
+        // the one-stage kernel's order: right, left, below, above
+        const float2 na = sweep_add(sweep_add(sweep_add(self.b, lane_shift<kFromLower>(self.b)), dn.a), up.a);
+        const float2 nb = sweep_add(sweep_add(sweep_add(lane_shift<kFromUpper>(self.a), self.a), dn.b), up.b);
+        T2 val{sweep_out(pr[S + i - st].a, na, self.a, false, c, st - 1),
+               sweep_out(pr[S + i - st].b, nb, self.b, false, c, st - 1)};
+        if (MARK && any) {
+          const uint32_t m = mr >> (2 * st) & 3u;
+          if (__ballot(m != 0)) {
+            if (m & 1u) val.a = sweep_mark(val.a, self.a, c, st - 1);
+            if (m & 2u) val.b = sweep_mark(val.b, self.b, c, st - 1);
+          }
+        }
+        if (st < S) {
+          yv[st][pmod(i - st, 3)] = val;
+        } else if (lane >= H / 2 && lane < 64 - H / 2) {
+          *reinterpret_cast<T2 *>(Out + off(t - S)) = val;
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < S; ++j) pr[j] = pr[j + U];
+  }
+}
+
+template <int S, bool YP>
+__global__ __launch_bounds__(64 * kStripWaves) void k_ctqw_torus_deep(GraphView g, const float2 *__restrict__ P,
+                                                                      const float2 *__restrict__ Yin,
+                                                                      float2 *__restrict__ Out,
+                                                                      StageCoefsF32<S> c, int core) {
+  constexpr int H = S + (S & 1);
+  const int l1 = g.dims[0], l2 = g.dims[1], R = g.strip_rows;
+  const int tiles_c = (l2 + core - 1) / core, tiles_r = (l1 + R - 1) / R;
+  const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  const int tile = xcd_remap(blockIdx.x, gridDim.x) * kStripWaves + wv;
+  if (tile >= tiles_r * tiles_c) return;  // whole wavefront
+  const int lane = threadIdx.x & 63;
+  const int tr = tile / tiles_c, tc = tile - tr * tiles_c;
+  int rb = min(tr * R, l1 - R) - S, cb = min(tc * core, l2 - core) - H;
+  rb += rb < 0 ? l1 : 0;
+  // no pair of columns across the grid's edge: on odd widths a window that wraps
+  // starts a column earlier, which its core allows for
+  if (cb > 0 && cb + 128 > l2) cb -= (l2 - cb) & 1;
+  int gcol = cb + 2 * lane;  // in (-l2, 2 l2) since 128 <= l2
+  gcol += gcol < 0 ? l2 : 0;
+  gcol -= gcol >= l2 ? l2 : 0;
+  if (g.tmark[tile])
+    deep_strip<S, YP, true>(g, P, Yin, Out, c, R, rb, lane, gcol);
+  else
+    deep_strip<S, YP, false>(g, P, Yin, Out, c, R, rb, lane, gcol);
 }
 
 // S stages of a Chebyshev series on a strip, complex128: the sweep above with
@@ -2084,10 +2224,6 @@ __global__ __launch_bounds__(1024) void k_stag_small(GraphView g, T *psi, int64_
 // Bound by the chain of FP64 operations of one wavefront per SIMD and, on small
 // lattices, by the launches: 2.6 us per step at 768 x 1100 complex128 (LDS tiles
 // of 16 x 64 with two steps per launch: 6.7).
-template <typename T> struct alignas(sizeof(T)) Two {
-  T a, b;
-};
-
 // One vertex of a square with the sum of its four amplitudes, alpha = (1, 1,
 // 1, 1)/2, inner = <alpha|x>: x <- c0 x + c1 (2 (1/2) inner - x), which for the
 // reflection form (c0, c1) = (0, 1) is sum / 2 - x.
@@ -3640,18 +3776,44 @@ int torus_block_depth(bool c128, const GraphView &g, int K) {
   return 1;
 }
 
+// Stage coefficients of a launch; alpha and beta point at its first stage's, the
+// later stages' lie before them.
+template <int N> void fill_coefs(StageCoefs<N> &c, const double *alpha, const double *beta) {
+  for (int i = 0; i < N; ++i) {
+    c.alpha[i] = alpha[-i];
+    c.beta[i] = beta[-i];
+  }
+}
+template <int N> void fill_coefs(StageCoefsF32<N> &c, const double *alpha, const double *beta) {
+  for (int i = 0; i < N; ++i) {
+    c.ahi[i] = static_cast<float>(alpha[-i]);
+    c.alo[i] = static_cast<float>(alpha[-i] - static_cast<double>(c.ahi[i]));
+    c.bhi[i] = static_cast<float>(beta[-i]);
+    c.blo[i] = static_cast<float>(beta[-i] - static_cast<double>(c.bhi[i]));
+  }
+}
+
 template <typename T, int S>
-hipError_t launch_sweep(const GraphView &g, const void *P, const void *Yin, void *Out, int kfirst,
-                        const typename SweepCoefs<T>::type &c, hipStream_t s) {
+hipError_t launch_sweep(const GraphView &g, const void *P, const void *Yin, void *Out, const double *alpha,
+                        const double *beta, hipStream_t s) {
+  typename SweepCoefs<T, S>::type c;
+  fill_coefs(c, alpha, beta);
   const StripGrid sg = torus_strips(sizeof(T) == 16, g.dims[0], g.dims[1], S);
   if (sg.count() == 0 || sg.rows != g.strip_rows || !g.tmark) return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>((sg.count() + kStripWaves - 1) / kStripWaves)), block(64 * kStripWaves);
   const T *p = static_cast<const T *>(P), *y = static_cast<const T *>(Yin);
   if (Yin == P)
-    hipLaunchKernelGGL((k_ctqw_torus_sweep<T, S, true>), grid, block, 0, s, g, p, y, static_cast<T *>(Out), kfirst, c);
+    hipLaunchKernelGGL((k_ctqw_torus_sweep<T, S, true>), grid, block, 0, s, g, p, y, static_cast<T *>(Out), c);
   else
-    hipLaunchKernelGGL((k_ctqw_torus_sweep<T, S, false>), grid, block, 0, s, g, p, y, static_cast<T *>(Out), kfirst, c);
+    hipLaunchKernelGGL((k_ctqw_torus_sweep<T, S, false>), grid, block, 0, s, g, p, y, static_cast<T *>(Out), c);
   return hipGetLastError();
+}
+
+template <int S>
+hipError_t launch_sweep(bool c128, const GraphView &g, const void *P, const void *Yin, void *Out, const double *alpha,
+                        const double *beta, hipStream_t s) {
+  return c128 ? launch_sweep<double2, S>(g, P, Yin, Out, alpha, beta, s)
+              : launch_sweep<float2, S>(g, P, Yin, Out, alpha, beta, s);
 }
 
 template <int S>
@@ -3681,34 +3843,70 @@ hipError_t torus_series_stages(const GraphView &g, int S, const void *P, const v
   }
 }
 
+StripGrid deep_strips(int l1, int l2, int K, int block_depth, int *depth) {
+  StripGrid sg;
+  const int64_t cells = static_cast<int64_t>(l1) * l2;
+  const bool large = cells >= kDeepLarge, small = cells <= kDeepSmall;
+  if (!large && !small && block_depth > 3) return sg;
+  const int most = large ? kDeepStages : kDeepStagesSmall;
+  const int launches = (K + most - 1) / most, S = (K + launches - 1) / launches;
+  if (l2 < 128 || S < 2) return sg;
+  sg.width = 128;
+  sg.halo = S + (S & 1);
+  sg.core = 128 - 2 * sg.halo - 2 * (l2 & 1);
+  sg.tiles_c = (l2 + sg.core - 1) / sg.core;
+  const int want = std::max(1, (small ? 1 : 2) * kSimds / sg.tiles_c);
+  sg.rows = std::min((l1 + want - 1) / want, l1 - 2 * sg.halo);
+  if (sg.rows < 1) return StripGrid{};
+  sg.tiles_r = (l1 + sg.rows - 1) / sg.rows;
+  *depth = S;
+  return sg;
+}
+
+template <int S>
+hipError_t launch_deep(const GraphView &g, int core, const void *P, const void *Yin, void *Out, const double *alpha,
+                       const double *beta, hipStream_t s) {
+  StageCoefsF32<S> c;
+  fill_coefs(c, alpha, beta);
+  const int R = g.strip_rows;
+  if (R < 1 || R + 2 * S > g.dims[0] || core < 2 || core > 128 - 2 * (S + (S & 1)) - 2 * (g.dims[1] & 1) || !g.tmark)
+    return hipErrorInvalidValue;
+  const int64_t strips = static_cast<int64_t>((g.dims[0] + R - 1) / R) * ((g.dims[1] + core - 1) / core);
+  const dim3 grid(static_cast<unsigned>((strips + kStripWaves - 1) / kStripWaves)), block(64 * kStripWaves);
+  const float2 *p = static_cast<const float2 *>(P), *y = static_cast<const float2 *>(Yin);
+  if (Yin == P)
+    hipLaunchKernelGGL((k_ctqw_torus_deep<S, true>), grid, block, 0, s, g, p, y, static_cast<float2 *>(Out), c, core);
+  else
+    hipLaunchKernelGGL((k_ctqw_torus_deep<S, false>), grid, block, 0, s, g, p, y, static_cast<float2 *>(Out), c,
+                       core);
+  return hipGetLastError();
+}
+
+hipError_t torus_deep(const GraphView &g, int core, int S, const void *P, const void *Yin, void *Out, int kfirst,
+                      const double *alpha, const double *beta, hipStream_t s) {
+  const double *ca = alpha + kfirst - 1, *cb = beta + kfirst - 1;
+  switch (S) {
+    case 2: return launch_deep<2>(g, core, P, Yin, Out, ca, cb, s);
+    case 3: return launch_deep<3>(g, core, P, Yin, Out, ca, cb, s);
+    case 4: return launch_deep<4>(g, core, P, Yin, Out, ca, cb, s);
+    case 5: return launch_deep<5>(g, core, P, Yin, Out, ca, cb, s);
+    case 6: return launch_deep<6>(g, core, P, Yin, Out, ca, cb, s);
+    case 7: return launch_deep<7>(g, core, P, Yin, Out, ca, cb, s);
+    case 8: return launch_deep<8>(g, core, P, Yin, Out, ca, cb, s);
+    case 9: return launch_deep<9>(g, core, P, Yin, Out, ca, cb, s);
+    case 10: return launch_deep<10>(g, core, P, Yin, Out, ca, cb, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 hipError_t torus_block_stages(bool c128, const GraphView &g, int S, const void *P, const void *Yin, void *Out,
                               int kfirst, const double *alpha, const double *beta, hipStream_t s) {
-  if (c128) {
-    Coefs c;
-    for (int k = 0; k < 64; ++k) {
-      c.alpha[k] = alpha[k];
-      c.beta[k] = beta[k];
-    }
-    switch (S) {
-      case 5: return launch_sweep<double2, 5>(g, P, Yin, Out, kfirst, c, s);
-      case 4: return launch_sweep<double2, 4>(g, P, Yin, Out, kfirst, c, s);
-      case 3: return launch_sweep<double2, 3>(g, P, Yin, Out, kfirst, c, s);
-      case 2: return launch_sweep<double2, 2>(g, P, Yin, Out, kfirst, c, s);
-      default: return hipErrorInvalidValue;
-    }
-  }
-  CoefsF32 c;
-  for (int k = 0; k < 64; ++k) {
-    c.ahi[k] = static_cast<float>(alpha[k]);
-    c.alo[k] = static_cast<float>(alpha[k] - static_cast<double>(c.ahi[k]));
-    c.bhi[k] = static_cast<float>(beta[k]);
-    c.blo[k] = static_cast<float>(beta[k] - static_cast<double>(c.bhi[k]));
-  }
+  const double *ca = alpha + kfirst - 1, *cb = beta + kfirst - 1;
   switch (S) {
-    case 5: return launch_sweep<float2, 5>(g, P, Yin, Out, kfirst, c, s);
-    case 4: return launch_sweep<float2, 4>(g, P, Yin, Out, kfirst, c, s);
-    case 3: return launch_sweep<float2, 3>(g, P, Yin, Out, kfirst, c, s);
-    case 2: return launch_sweep<float2, 2>(g, P, Yin, Out, kfirst, c, s);
+    case 5: return launch_sweep<5>(c128, g, P, Yin, Out, ca, cb, s);
+    case 4: return launch_sweep<4>(c128, g, P, Yin, Out, ca, cb, s);
+    case 3: return launch_sweep<3>(c128, g, P, Yin, Out, ca, cb, s);
+    case 2: return launch_sweep<2>(c128, g, P, Yin, Out, ca, cb, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -67,6 +67,8 @@ struct qw_plan {
   // where their array sits, and the workspace of big-polygon partial sums
   std::vector<qwk::StagTess> stag;
   size_t off_stag = 0, off_stagpart = 0;
+  int32_t strip_core = 0;   // two-column complex64 sweep: core columns per strip (0: not used)
+  int deep_depth = 0;       // two-column complex64 sweep: stages of its deepest launch
   int32_t strip_rows = 0;   // grid CTQW blocked kernel: core rows per strip
   int32_t two_reg = 0;      // one-workgroup coined walk in one wavefront's registers: 0 no, 1 permutes, 2 cycle shifts
   qwk::Series series;       // CTQW: whole groups of series.steps time steps (terms == 0: one step at a time)

@@ -1,0 +1,43 @@
+"""The two-column complex64 sweep of the grid CTQW: the oracle's states for
+orders that split into launches of every depth, at the narrowest grids, even
+and odd widths, windows that wrap, the fewest rows, and marks at strip edges;
+and the same bits whichever way the steps are called."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2406_08186_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("l1,l2", [(13, 128), (17, 129), (40, 229), (61, 232), (300, 131)])
+@pytest.mark.parametrize("K", [2, 3, 4, 5, 9, 14, 22])
+def test_small_grids(l1, l2, K):
+    _check(l1, l2, K, 5)
+
+
+@pytest.mark.parametrize("l1,l2,K", [(1449, 1449, 20), (1024, 2050, 18), (11000, 193, 8), (1024, 1030, 14)])
+def test_large_grids(l1, l2, K):
+    _check(l1, l2, K, 2)
+
+
+def _check(l1, l2, K, steps):
+    from paper_2406_08186_amd.walk import Plan
+    print(f"[case] grid sweep {l1}x{l2} K {K}", flush=True)
+    g = I.torus(l1, l2)
+    marked = sorted({0, 1, l2 - 1, min(115, l2 - 1) + 3 * l2, min(116, l2 - 1) + 4 * l2, g.n // 2, g.n - 1})
+    psi0 = I.random_state(g.n, K)
+    dt = 0.07
+    pl = Plan(g, "ctqw", dtype="c64", gamma=0.25, dt=dt, taylor_order=K, marked=marked, layout="structured")
+    assert pl.structure == "torus" and pl.info.block_depth > 1
+    x, y = pl.state(psi0), pl.state(psi0)
+    p, norm, pm = pl.evolve(x, steps, readout=True)
+    for _ in range(steps):
+        pl.evolve(y, 1)
+    torch.cuda.synchronize()
+    assert torch.equal(x, y)
+    ref = oracle.ctqw_evolve(g.row_ptr, g.col, psi0, steps, gamma=0.25, dt=dt, K=K, marked=marked)
+    assert np.linalg.norm(x.cpu().numpy().astype(np.complex128) - ref) < 1e-5
+    assert abs(float(pm) - float((np.abs(ref) ** 2)[marked].sum())) < 1e-6
