@@ -880,12 +880,19 @@ int evolve_coined(const qw_plan *p, void *psi, unsigned char *work, int64_t step
   }
   if (steps == 0) return readout_only(p, psi, ro, s);
   if (p->structure == kGeneral) {
+    // complex64: phi stays in arc order between steps and the next step gathers
+    // it; the last shift is a scatter into psi (even counts) or a pass of its own
+    const bool hold = !c128;
     void *cur = psi, *oth = w0;
     for (int64_t i = 0; i < steps; ++i) {
-      QW_TRY(coined_tile_step(c128, g, cur, oth, had, s), "coined step kernel");
+      const bool scatter = !hold || (i + 1 == steps && oth == psi);
+      QW_TRY(coined_tile_step(c128, g, cur, oth, had, hold && i > 0, scatter, s), "coined step kernel");
       std::swap(cur, oth);
     }
-    if (cur != psi) QW_TRY(copy_state(c128, p->n_arcs, cur, psi, s), "state copy kernel");
+    if (cur != psi) {
+      if (hold) QW_TRY(coined_shift(c128, g, cur, psi, s), "coined shift kernel");
+      else QW_TRY(copy_state(c128, p->n_arcs, cur, psi, s), "state copy kernel");
+    }
     return readout_only(p, psi, ro, s);
   }
   QW_TRY(coined_perm_in(c128, g, psi, w0, s), "layout permutation kernel");

@@ -13,6 +13,7 @@ namespace qwk {
 // one workgroup's LDS tile are processed together.
 constexpr int kTileArcs = 2048;
 constexpr int kTileThreads = 256;
+constexpr int kCoinedTileThreads = 512;  // single coined walks: four gathers in flight per thread
 // The LDS-staged batch stage, per state type: workgroup size, the LDS block of
 // the input vector it stages (whole rounds of 1 KiB direct loads by every
 // wavefront) and rows per thread for walks of degree d (1..8).  A row takes d
@@ -280,8 +281,12 @@ hipError_t coined_small(bool c128, const GraphView &g, void *psi, int hadamard, 
                         const Readout &ro, hipStream_t s);
 size_t coined_small_lds(bool c128, int n, int n_arcs);
 
-hipError_t coined_tile_step(bool c128, const GraphView &g, const void *in, void *out,
-                            int hadamard, hipStream_t s);
+// One step in CSR arc order.  gather: `in` holds the previous step's coin output,
+// still to be shifted; scatter: shift on the way out (else `out` needs the next
+// step's gather, or coined_shift).
+hipError_t coined_tile_step(bool c128, const GraphView &g, const void *in, void *out, int hadamard, bool gather,
+                            bool scatter, hipStream_t s);
+hipError_t coined_shift(bool c128, const GraphView &g, const void *phi, void *out, hipStream_t s);
 hipError_t coined_struct_step(bool c128, const GraphView &g, const void *in, void *out,
                               int hadamard, hipStream_t s);
 // Grid walks: how many of `left` steps the next launch takes (1: one step by

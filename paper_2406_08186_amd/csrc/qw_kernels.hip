@@ -425,11 +425,20 @@ __global__ __launch_bounds__(1024) void k_coined_small(GraphView g, T *psi, int 
 
 // ---- coined: general CSR, one LDS tile of whole vertex blocks per workgroup --
 // Tile t covers vertices [tiles[t], tiles[t+1]); its arcs fit kTileArcs unless
-// the tile is a single vertex of larger degree.  Loads are coalesced in arc
-// order; the flip-flop shift scatters phi_a to out[rev[a]].
-template <typename T>
-__global__ __launch_bounds__(kTileThreads) void k_coined_tile(GraphView g, const T *__restrict__ in,
-                                                              T *__restrict__ out, int hadamard) {
+// the tile is a single vertex of larger degree.  The flip-flop shift moves phi_a
+// to rev[a], and rev is its own inverse.  complex64: a step leaves phi in arc
+// order and the next one reads phi[rev[a]] (GATHER), cheaper than scattered
+// 8-byte stores; only an even last step scatters (SCATTER), into the caller's
+// buffer.  complex128 scatters at every step: its 16-byte gathers cost more.
+// Bound by these accesses (9 us) and the latency of a tile's chain of loads, coin
+// and stores (11 us at two tiles per compute unit).  60 steps on 120000 vertices
+// of mean degree 9 complex64: 1282 us with 256 threads and scatters, 1200 so (1388
+// with 1024 threads; degree-wide register copies of the rows 1354); 110000
+// vertices complex128: 1173, 1115 so, 1290 gathering.
+template <typename T, bool GATHER, bool SCATTER>
+__global__ __launch_bounds__(kCoinedTileThreads) void k_coined_tile(GraphView g, const T *__restrict__ in,
+                                                                    T *__restrict__ out, int hadamard) {
+  constexpr int PER = kTileArcs / kCoinedTileThreads;
   __shared__ T s[kTileArcs];
   __shared__ double red[16];
   const int t = blockIdx.x;
@@ -437,12 +446,30 @@ __global__ __launch_bounds__(kTileThreads) void k_coined_tile(GraphView g, const
   const int ab = g.rp[vb], ae = g.rp[ve];
   const int na = ae - ab;
   if (na <= kTileArcs) {
-    for (int i = threadIdx.x; i < na; i += blockDim.x) s[i] = in[ab + i];
+    // the thread's first vertex, read while the amplitudes arrive
+    const int v1 = min(vb + static_cast<int>(threadIdx.x), ve - 1);
+    const int lo1 = g.rp[v1] - ab, hi1 = g.rp[v1 + 1] - ab;
+    const bool mk1 = marked(g.markbits, v1);
+    T x[PER];
+    int src[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const int i = ab + min(static_cast<int>(threadIdx.x) + q * kCoinedTileThreads, na - 1);
+      src[q] = GATHER ? g.rev[i] : i;
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) x[q] = in[src[q]];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const int i = threadIdx.x + q * kCoinedTileThreads;
+      if (i < na) s[i] = x[q];
+    }
     __syncthreads();
     for (int v = vb + threadIdx.x; v < ve; v += blockDim.x) {
-      const int lo = g.rp[v] - ab, hi = g.rp[v + 1] - ab, d = hi - lo;
+      const bool first = v == v1;
+      const int lo = first ? lo1 : g.rp[v] - ab, hi = first ? hi1 : g.rp[v + 1] - ab, d = hi - lo;
       if (d == 0) continue;
-      if (marked(g.markbits, v)) {
+      if (first ? mk1 : marked(g.markbits, v)) {
         for (int i = lo; i < hi; ++i) s[i] = pack<T>(scale(cvt(s[i]), -1.0));
       } else if (hadamard) {
         double2 x0 = cvt(s[lo]), x1 = cvt(s[lo + 1]);
@@ -461,7 +488,7 @@ __global__ __launch_bounds__(kTileThreads) void k_coined_tile(GraphView g, const
       }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < na; i += blockDim.x) out[g.rev[ab + i]] = s[i];
+    for (int i = threadIdx.x; i < na; i += blockDim.x) out[SCATTER ? g.rev[ab + i] : ab + i] = s[i];
   } else {
     // one vertex of degree > kTileArcs (Hadamard is never here: d = 2)
     const int v = vb;
@@ -469,8 +496,9 @@ __global__ __launch_bounds__(kTileThreads) void k_coined_tile(GraphView g, const
     double2 m = make_double2(0.0, 0.0);
     if (!mk) {
       double sx = 0.0, sy = 0.0;
-      for (int i = ab + threadIdx.x; i < ae; i += blockDim.x) {
-        double2 x = ld(in, i);
+      // summed by the first kTileThreads threads, whatever the block
+      for (int i = ab + threadIdx.x; i < ae && threadIdx.x < kTileThreads; i += kTileThreads) {
+        double2 x = ld(in, GATHER ? g.rev[i] : i);
         const double wt = g.sqrtp ? g.sqrtp[i] : 1.0;
         sx += wt * x.x;
         sy += wt * x.y;
@@ -480,12 +508,20 @@ __global__ __launch_bounds__(kTileThreads) void k_coined_tile(GraphView g, const
       m = g.sqrtp ? make_double2(sx, sy) : grover_mean(make_double2(sx, sy), na);
     }
     for (int i = ab + threadIdx.x; i < ae; i += blockDim.x) {
-      double2 x = ld(in, i);
+      double2 x = ld(in, GATHER ? g.rev[i] : i);
       double2 phi = mk ? scale(x, -1.0)
                        : (g.sqrtp ? sub(scale(m, 2.0 * g.sqrtp[i]), x) : sub(add(m, m), x));
-      st(out, g.rev[i], phi);
+      st(out, SCATTER ? g.rev[i] : i, phi);
     }
   }
+}
+
+// out[a] = phi[rev[a]]: the shift that the last of an odd number of steps left out.
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_coined_shift(const T *__restrict__ phi, T *__restrict__ out,
+                                                         const int32_t *__restrict__ rev, int na) {
+  const int i = blockIdx.x * kBlock + threadIdx.x;
+  if (i < na) out[i] = phi[rev[i]];
 }
 
 // ---- coined: index-free structured layouts ------------------------------------
@@ -3511,15 +3547,39 @@ hipError_t coined_small(bool c128, const GraphView &g, void *psi, int hadamard, 
               : launch_coined_small<float2>(g, psi, hadamard, steps, ro, s);
 }
 
-hipError_t coined_tile_step(bool c128, const GraphView &g, const void *in, void *out, int hadamard,
-                            hipStream_t s) {
-  if (g.n_tiles == 0) return hipSuccess;
-  if (c128)
-    hipLaunchKernelGGL(k_coined_tile<double2>, dim3(g.n_tiles), dim3(kTileThreads), 0, s, g,
-                       static_cast<const double2 *>(in), static_cast<double2 *>(out), hadamard);
+template <typename T>
+hipError_t launch_coined_tile(const GraphView &g, const void *in, void *out, int hadamard, bool gather, bool scatter,
+                              hipStream_t s) {
+  const T *x = static_cast<const T *>(in);
+  T *y = static_cast<T *>(out);
+  const dim3 grid(g.n_tiles), block(kCoinedTileThreads);
+  if (scatter && !gather)
+    hipLaunchKernelGGL((k_coined_tile<T, false, true>), grid, block, 0, s, g, x, y, hadamard);
+  else if (!gather)
+    hipLaunchKernelGGL((k_coined_tile<T, false, false>), grid, block, 0, s, g, x, y, hadamard);
+  else if (scatter)
+    hipLaunchKernelGGL((k_coined_tile<T, true, true>), grid, block, 0, s, g, x, y, hadamard);
   else
-    hipLaunchKernelGGL(k_coined_tile<float2>, dim3(g.n_tiles), dim3(kTileThreads), 0, s, g,
-                       static_cast<const float2 *>(in), static_cast<float2 *>(out), hadamard);
+    hipLaunchKernelGGL((k_coined_tile<T, true, false>), grid, block, 0, s, g, x, y, hadamard);
+  return hipGetLastError();
+}
+
+hipError_t coined_tile_step(bool c128, const GraphView &g, const void *in, void *out, int hadamard, bool gather,
+                            bool scatter, hipStream_t s) {
+  if (g.n_tiles == 0) return hipSuccess;
+  return c128 ? launch_coined_tile<double2>(g, in, out, hadamard, gather, scatter, s)
+              : launch_coined_tile<float2>(g, in, out, hadamard, gather, scatter, s);
+}
+
+hipError_t coined_shift(bool c128, const GraphView &g, const void *phi, void *out, hipStream_t s) {
+  if (g.n_arcs == 0) return hipSuccess;
+  const dim3 grid(blocks_for(g.n_arcs, kBlock));
+  if (c128)
+    hipLaunchKernelGGL(k_coined_shift<double2>, grid, dim3(kBlock), 0, s, static_cast<const double2 *>(phi),
+                       static_cast<double2 *>(out), g.rev, g.n_arcs);
+  else
+    hipLaunchKernelGGL(k_coined_shift<float2>, grid, dim3(kBlock), 0, s, static_cast<const float2 *>(phi),
+                       static_cast<float2 *>(out), g.rev, g.n_arcs);
   return hipGetLastError();
 }
 
