@@ -43,10 +43,6 @@ METRIC = "arc-steps/s (c64 batched vs c128 plain, L2 err<=1e-4); p50/p99 latency
 # 256 MiB copy (x2.00 / x1.00).  Each entry holds only for the kernel version
 # and launch configuration named in its key and source; any other reports None.
 MEASURED_TRAFFIC = {
-    # profiles/batch4096_ctqw_search_lds.md: mean over the 5120 timed launches of the
-    # default command, FETCH_SIZE 3,088,620.9 KiB x 2.00 + WRITE_SIZE 1,164,456.9 KiB x 1.00
-    # (768 threads x 9 rows, 19968-entry blocks staged by LDS-direct loads)
-    "k_batch_ell_lds<float2,768,9,19968> batch4096 seed1 launches1280-6400": (3088620.9 * 2 + 1164456.9) * 1024,
     # profiles/ctqw_torus1024_sweep.md: the FP32 complex64 sweep, averaged over the four
     # launches of a step, FETCH_SIZE (4543.1 + 3 x 8942.0) / 4 KiB x 2.00 + WRITE_SIZE 8193.3 KiB
     "k_ctqw_torus_sweep<float2,5> 1024x1024": ((4543.1 + 3 * 8942.0) / 4 * 2 + 8193.3) * 1024,
@@ -159,14 +155,22 @@ def timed_passes(plan, psi, steps, warmup, spp):
     return wall, per, out
 
 
-def stage_launch_ms(plan, per_pass_ms, steps_per_pass):
+def grid_launches(plan, cells):
+    """Launches of one complex64 time step on the grid: K / block_depth, or, on
+    grids of at least 2^21 cells, those of the two-column sweep's ten stages
+    (its launches on grids of up to 700000 cells are of K / 4 stages, as many).
+    """
+    depth = max(1, int(plan.info.block_depth))
+    return -(-K_ORDER // 10) if depth > 1 and cells >= 1 << 21 else K_ORDER // depth
+
+
+def stage_launch_ms(per_pass_ms, steps_per_pass, launches_per_step):
     """Average duration of one launch of the stage kernel over the timed
     region: the HIP-event time of the timed passes (recorded on the stream
-    the kernels run on) over the number of stage launches they made
-    (K / block_depth per time step).  The FP64 readout at the end of each
-    pass, one small launch per thousands, is counted in."""
-    launches = len(per_pass_ms) * steps_per_pass * (K_ORDER // max(1, plan.info.block_depth))
-    return sum(per_pass_ms) / launches
+    the kernels run on) over the number of stage launches they made.  The FP64
+    readout at the end of each pass, one small launch per thousands, is counted
+    in."""
+    return sum(per_pass_ms) / (len(per_pass_ms) * steps_per_pass * launches_per_step)
 
 
 def pct(sorted_vals, q):
@@ -268,16 +272,17 @@ def run_grid(args):
         wall, per, (p, norm, _) = timed_passes(pl, psi, args.steps, args.warmup, spp)
         total_steps = (args.steps + args.warmup) * spp
         state = psi.cpu().numpy().astype(np.complex128)
-        launch_ms = stage_launch_ms(pl, per, spp)
+        # complex128 runs groups of steps as one series: no launches of a step to time
+        lps = grid_launches(pl, g.n) if dtype == "c64" else None
+        launch_ms = stage_launch_ms(per, spp, lps) if lps else None
         es = 8 if dtype == "c64" else 16
         # algorithmic bytes of one row-stage of the matrix-free grid stencil: read y,
-        # read psi, write y' (3 S); one launch runs block_depth stages of every row
-        depth = int(pl.info.block_depth)
+        # read psi, write y' (3 S); one launch runs `depth` stages of every row
+        depth = K_ORDER // lps if lps else int(pl.info.block_depth)
         # bytes a launch must move: read y_in and psi, write y_out (3 S per row);
         # the first launch of a time step reads psi as y_in (2 S).  Averaged over
         # the K / depth launches of a step.
-        lps = max(1, K_ORDER // depth)
-        bytes_per_launch = (3 * lps - 1) / lps * es * g.n
+        bytes_per_launch = (3 * lps - 1) / lps * es * g.n if lps else None
         stage_model_bytes = depth * 3 * es * g.n
         res[dtype] = dict(plan=pl, wall=wall, per=per, norm=float(norm), state=state,
                           total_steps=total_steps, launch_ms=launch_ms,
@@ -328,9 +333,6 @@ def run_grid(args):
         "p50_ms": pct(r64["per"], 50), "p99_ms": pct(r64["per"], 99),
         "c128": {"value": rate(r128), "ms_per_step": r128["wall"] / args.steps * 1e3,
                  "p50_ms": pct(r128["per"], 50), "p99_ms": pct(r128["per"], 99),
-                 "stage_launch_ms": r128["launch_ms"],
-                 "launch_gbs": r128["bytes_per_launch"] / (r128["launch_ms"] * 1e-3) / 1e9,
-                 "launch_frac": r128["bytes_per_launch"] / (r128["launch_ms"] * 1e-3) / 1e9 / HBM_PEAK_GBS,
                  "l2_vs_closed_form": l2_128},
         "speedup_c64_vs_c128": rate(r64) / rate(r128),
         "l2_c64_vs_closed_form": l2_64,
@@ -584,7 +586,7 @@ def run_batch(args):
 
     value = arc_steps / wall
     l2_max = max(l2s) if l2s else None
-    kname = "k_batch_ell_lds<float2,768,9,19968>" if stage_kernel == "lds" else "k_batch_stage<float2>"
+    kname = "k_batch_ell_lds<float2,768,19968>" if stage_kernel == "lds" else "k_batch_stage<float2>"
     traffic_key = f"{kname} batch{len(plans)} seed{args.batch_seed} launches{La}-{Lb}"
     traffic = MEASURED_TRAFFIC.get(traffic_key)
     line = {
@@ -1124,11 +1126,12 @@ def run_sparse(args):
             ms = a.elapsed_time(b)
             es = 8 if dtype == "c64" else 16
             per_launch = (4 * g.n if pl.structure == "general" else 0) + 4 * g.n_arcs + 3 * es * g.n
-            launch_ms = ms / (steps * K)
-            gbs = per_launch / (launch_ms * 1e-3) / 1e9
-            res[dtype] = {"path": pl.structure, "K": K, "arc_steps_per_s": g.n_arcs * steps / (ms * 1e-3),
-                          "arc_spmv_per_s": g.n_arcs * steps * K / (ms * 1e-3), "stage_us": launch_ms * 1e3,
-                          "bytes_per_stage": per_launch, "achieved_gbs": gbs, "frac": gbs / HBM_PEAK_GBS}
+            res[dtype] = {"path": pl.structure, "K": K, "arc_steps_per_s": g.n_arcs * steps / (ms * 1e-3)}
+            if dtype == "c64":  # K stages per step; complex128 runs groups of steps as one series
+                launch_ms = ms / (steps * K)
+                gbs = per_launch / (launch_ms * 1e-3) / 1e9
+                res[dtype].update({"arc_spmv_per_s": g.n_arcs * steps * K / (ms * 1e-3), "stage_us": launch_ms * 1e3,
+                                   "bytes_per_stage": per_launch, "achieved_gbs": gbs, "frac": gbs / HBM_PEAK_GBS})
             del psi
             pl.close()
         out[name] = res
