@@ -445,6 +445,7 @@ __global__ __launch_bounds__(kCoinedTileThreads) void k_coined_tile(GraphView g,
   const int vb = g.tiles[t], ve = g.tiles[t + 1];
   const int ab = g.rp[vb], ae = g.rp[ve];
   const int na = ae - ab;
+  if (na == 0) return;  // isolated vertices alone: the clamped loads below need an arc
   if (na <= kTileArcs) {
     // the thread's first vertex, read while the amplitudes arrive
     const int v1 = min(vb + static_cast<int>(threadIdx.x), ve - 1);

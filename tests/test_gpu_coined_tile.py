@@ -45,3 +45,43 @@ def test_steps_equal_single_steps(n, hub, marked, dtype):
     ref = oracle.coined_evolve(rp, col, psi0, 5, marked=marked)
     err = got.cpu().numpy().astype(np.complex128) - ref
     assert (np.abs(err).max() < 1e-12) if dtype == "c128" else (np.linalg.norm(err) < 1e-5)
+
+
+def _without_arcs_first(lead, hub, n):
+    """`lead` isolated vertices, a vertex joined to `hub` others, a ring over the rest;
+    n 0: the isolated vertices alone."""
+    if n == 0:
+        return np.zeros(lead + 1, np.int64), np.zeros(0, np.int32)
+    v = np.arange(n)
+    a, b = np.concatenate([v, np.zeros(hub, int)]), np.concatenate([(v + 1) % n, 2 + np.arange(hub)])
+    e = np.unique(np.sort(np.stack([a, b], 1), axis=1), axis=0) + lead
+    src, dst = np.concatenate([e[:, 0], e[:, 1]]), np.concatenate([e[:, 1], e[:, 0]])
+    o = np.lexsort((dst, src))
+    rp = np.concatenate([[0], np.cumsum(np.bincount(src, minlength=lead + n))])
+    return rp.astype(np.int64), dst[o].astype(np.int32)
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("lead,hub,n", [(1024, 4, 900), (1025, 0, 1200), (2500, 30, 2600), (1, 2100, 2200), (1500, 0, 0)])
+def test_tiles_without_arcs(lead, hub, n, dtype):
+    """Isolated vertices that fill the first tiles, or stand alone before a vertex of more than
+    a tile's arcs, have nothing to read; a graph without arcs has no state at all."""
+    from paper_2406_08186_amd.walk import Plan
+    print(f"[case] coined CSR, {lead} isolated first, hub {hub} of {n}, {dtype}", flush=True)
+    rp, col = _without_arcs_first(lead, hub, n)
+    marked = [0, lead + 1] if n else [0]
+    pl = Plan(I.Graph(lead + n, rp, col), "coined", dtype=dtype, layout="csr", marked=marked)
+    assert pl.structure == "general" and rp[lead] == 0
+    psi0 = I.random_state(len(col), 3) if n else np.zeros(0, np.complex128)
+    pref = np.zeros(lead + n)
+    for steps in (1, 2, 3):
+        psi = pl.state(psi0)
+        p, norm, pm = pl.evolve(psi, steps, readout=True)
+        torch.cuda.synchronize()
+        if n:
+            ref = oracle.coined_evolve(rp, col, psi0, steps, marked=marked)
+            pref = oracle.coined_prob(rp, col, ref)
+            err = psi.cpu().numpy().astype(np.complex128) - ref
+            assert (np.abs(err).max() < 1e-12) if dtype == "c128" else (np.linalg.norm(err) < 1e-5)
+        assert np.abs(p.cpu().numpy() - pref).max() < (1e-12 if dtype == "c128" else 1e-6)
+        assert abs(float(norm) - pref.sum()) < 1e-5 and abs(float(pm) - pref[marked].sum()) < 1e-5
