@@ -1489,9 +1489,9 @@ __global__ __launch_bounds__(64 * kStripWaves) void k_ctqw_torus_sweep(GraphView
 template <int S, bool YP, bool MARK>
 __device__ __forceinline__ void deep_strip(const GraphView &g, const float2 *__restrict__ P,
                                            const float2 *__restrict__ Yin, float2 *__restrict__ Out,
-                                           const StageCoefsF32<S> &c, int R, int rb, int lane, int gcol) {
+                                           const StageCoefsF32<S> &c, int R, int rb, int lane, int gcol, bool keep) {
   using T2 = Two<float2>;
-  constexpr int U = kDeepUnroll, H = S + (S & 1);
+  constexpr int U = kDeepUnroll;
   static_assert(U % 3 == 0, "stages keep their rows by window row mod 3");
   const int l1 = g.dims[0], l2 = g.dims[1], n_in = R + 2 * S, mlast = (g.n + 31) / 32 * 4 - 2;
   auto off = [&](int t) -> int {
@@ -1561,7 +1561,7 @@ __device__ __forceinline__ void deep_strip(const GraphView &g, const float2 *__r
         }
         if (st < S) {
           yv[st][pmod(i - st, 3)] = val;
-        } else if (lane >= H / 2 && lane < 64 - H / 2) {
+        } else if (keep) {
           *reinterpret_cast<T2 *>(Out + off(t - S)) = val;
         }
       }
@@ -1588,14 +1588,19 @@ __global__ __launch_bounds__(64 * kStripWaves) void k_ctqw_torus_deep(GraphView 
   rb += rb < 0 ? l1 : 0;
   // no pair of columns across the grid's edge: on odd widths a window that wraps
   // starts a column earlier, which its core allows for
-  if (cb > 0 && cb + 128 > l2) cb -= (l2 - cb) & 1;
+  const int early = cb > 0 && cb + 128 > l2 ? (l2 - cb) & 1 : 0;
+  cb -= early;
   int gcol = cb + 2 * lane;  // in (-l2, 2 l2) since 128 <= l2
   gcol += gcol < 0 ? l2 : 0;
   gcol -= gcol >= l2 ? l2 : 0;
+  // The pairs with columns of the strip's core, whatever columns beyond it this
+  // depth still has exact: a shallower launch of the time step (K = 9: 5, 4) would
+  // store more, and the strip's mark flag covers the halo of the core alone.
+  const bool keep = lane >= H / 2 && lane < H / 2 + core / 2 + early;
   if (g.tmark[tile])
-    deep_strip<S, YP, true>(g, P, Yin, Out, c, R, rb, lane, gcol);
+    deep_strip<S, YP, true>(g, P, Yin, Out, c, R, rb, lane, gcol, keep);
   else
-    deep_strip<S, YP, false>(g, P, Yin, Out, c, R, rb, lane, gcol);
+    deep_strip<S, YP, false>(g, P, Yin, Out, c, R, rb, lane, gcol, keep);
 }
 
 // S stages of a Chebyshev series on a strip, complex128: the sweep above with

@@ -41,3 +41,26 @@ def _check(l1, l2, K, steps):
     ref = oracle.ctqw_evolve(g.row_ptr, g.col, psi0, steps, gamma=0.25, dt=dt, K=K, marked=marked)
     assert np.linalg.norm(x.cpu().numpy().astype(np.complex128) - ref) < 1e-5
     assert abs(float(pm) - float((np.abs(ref) ** 2)[marked].sum())) < 1e-6
+
+
+@pytest.mark.parametrize("l1,l2,K,columns", [
+    (300, 300, 9, [*range(14), *range(112, 131)]), (300, 300, 14, [*range(14), *range(112, 131)]),
+    (40, 229, 9, [*range(14), *range(110, 131)]), (61, 232, 14, [*range(4, 12), *range(116, 128)]),
+    (300, 131, 14, [*range(4, 12), *range(116, 128)]), (1449, 1449, 25, [12, 13, 118, 119])])
+def test_marks_around_strip_edges(l1, l2, K, columns):
+    """A time step of launches of unequal depth (5, 4; 5, 5, 4; 9, 8, 8): one mark at a time at
+    every column around the ends of a strip and of its halo.  A mark term of the last launch
+    lost in one strip is 2.7e-4 of an amplitude or more at this step length; FP32 rounds each of
+    the last stages' values once, 6e-8 each."""
+    from paper_2406_08186_amd.walk import Plan
+    g = I.torus(l1, l2)
+    psi0 = np.exp(2j * np.pi * np.random.default_rng(K).random(g.n)) / np.sqrt(g.n)
+    for c in columns:
+        print(f"[case] grid sweep {l1}x{l2} K {K} mark at column {c}", flush=True)
+        mark = [(l1 // 3) * l2 + c]
+        pl = Plan(g, "ctqw", dtype="c64", gamma=0.25, dt=0.8, taylor_order=K, marked=mark, layout="structured")
+        x = pl.state(psi0)
+        pl.evolve(x, 1)
+        torch.cuda.synchronize()
+        ref = oracle.ctqw_evolve(g.row_ptr, g.col, psi0, 1, gamma=0.25, dt=0.8, K=K, marked=mark)
+        assert np.abs(x.cpu().numpy().astype(np.complex128) - ref).max() * np.sqrt(g.n) < 1e-5, c
