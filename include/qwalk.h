@@ -285,11 +285,7 @@ int qw_plan_upload(qw_plan *plan, void *d_graph, size_t graph_bytes, void *strea
  * d_p (double[n]), d_norm (double[1]), d_pmarked (double[1]) is non-NULL the
  * readout of qw_probabilities is produced from the final state as part of
  * the same call (fused into the last kernel where the layout permits).
- * steps = 0 leaves psi unchanged.  Rounding: splitting `steps` over several
- * calls gives the same bits for complex64 walks; for a complex128 CTQW it does
- * where every call but the last runs a multiple of 64 steps (groups of 8 to 64
- * steps are rounded together), and to FP64 rounding otherwise.
- * Errors: QW_EINVAL, QW_ENOMEM (workspace
+ * steps = 0 leaves psi unchanged.  Errors: QW_EINVAL, QW_ENOMEM (workspace
  * too small), QW_ESTATE (not uploaded), QW_EDEVICE. */
 int qw_evolve(const qw_plan *plan, void *d_psi, void *d_work, size_t work_bytes, int64_t steps,
               double *d_p, double *d_norm, double *d_pmarked, void *stream);

@@ -615,11 +615,6 @@ int build_plan(const qw_csr *g, const qw_walk_desc *w, qw_plan *p) {
         }
   }
 
-  // CTQW time steps in groups (complex128).  A complex64 walk rounds its state
-  // to FP32 at every stage, so another sequence of stages gives other FP32
-  // values and with them FP64 readouts that differ at 1e-7: it keeps the
-  // stages of single steps.  So does a regular graph's walk (ELL) below a
-  // whole group: its bits there are those of the same walk in a batch.
   // One-workgroup walk with its tables in registers.  Its three vectors have a
   // pad entry each, in the LDS room of the tables that it does without.
   std::vector<int32_t> by_degree;
@@ -635,15 +630,10 @@ int build_plan(const qw_csr *g, const qw_walk_desc *w, qw_plan *p) {
       p->small_regs = p->small_regs && rp[v + 1] - rp[v] <= small_row(c128, per, i);
     }
   }
-  if (ctqw && c128 && (structure != kSmall || p->small_regs)) {
-    for (int m = structure == kTorus ? kSeriesMaxSteps : kSeriesGroup; m >= kSeriesMinSteps; m /= 2)
-      if (chebyshev_series(p->dt * p->h_bound, p->K, m, &p->series)) break;
-    if (p->series.terms >= p->K * p->series.steps) p->series = Series();
-    p->series_rest = structure != kEll && structure != kSmall;
-  }
 
-  // grid CTQW: stages per launch, of single steps and of the series
-  std::vector<uint8_t> tmark, smark;
+  // grid CTQW: stages per launch and, per strip of the blocked kernel, whether
+  // a marked vertex lies in its window (halo included)
+  std::vector<uint8_t> tmark;
   if (ctqw && structure == kTorus) {
     GraphView tv;
     tv.structure = structure;
@@ -661,21 +651,6 @@ int build_plan(const qw_csr *g, const qw_walk_desc *w, qw_plan *p) {
       tmark = strip_marks(sg, p->dims[0], p->dims[1], mlist);
       p->has_tmark = true;
     }
-    for (int S : {5, 4, 3, 2}) {
-      const StripGrid sg = torus_strips(c128, p->dims[0], p->dims[1], S);
-      if (p->series.terms == 0 || sg.count() == 0) continue;
-      // The blocked series takes four buffers of the workspace (their last one
-      // also holds the readout's scratch, which is used after it).  Where this
-      // alone would take a plan out of the allocation-free entry point's
-      // array, the series' stages run unblocked in the two buffers there are.
-      const size_t es = 16 * static_cast<size_t>(n);
-      const size_t single = (p->block_depth > 1 ? 3 : 2) * align256(es) + align256(8 * static_cast<size_t>(n));
-      if (4 * align256(es) > QW_STATIC_SCRATCH_BYTES && single + (size_t{1} << 20) <= QW_STATIC_SCRATCH_BYTES) break;
-      p->series_depth = S;
-      p->series_rows = sg.rows;
-      smark = strip_marks(sg, p->dims[0], p->dims[1], mlist);
-      break;
-    }
   }
 
   size_t off = 0;
@@ -692,7 +667,6 @@ int build_plan(const qw_csr *g, const qw_walk_desc *w, qw_plan *p) {
   p->off_bits = section(sizeof(uint32_t) * bits.size());
   p->off_mlist = section(sizeof(int32_t) * std::max<size_t>(mlist.size(), 1));
   if (p->has_tmark) p->off_tmark = section(tmark.size());
-  if (p->series_depth > 1) p->off_smark = section(smark.size());
   p->has_coin = !p->coin_mat.empty();
   if (p->has_coin) p->off_coin = section(sizeof(double) * p->coin_mat.size());
   p->has_sqrtp = p->kind == QW_COINED && p->coin == QW_SZEGEDY;
@@ -753,7 +727,6 @@ int build_plan(const qw_csr *g, const qw_walk_desc *w, qw_plan *p) {
   put(p->image, p->off_bits, bits.data(), bits.size());
   put(p->image, p->off_mlist, mlist.data(), mlist.size());
   if (p->has_tmark) put(p->image, p->off_tmark, tmark.data(), tmark.size());
-  if (p->series_depth > 1) put(p->image, p->off_smark, smark.data(), smark.size());
   if (p->has_coin) put(p->image, p->off_coin, p->coin_mat.data(), p->coin_mat.size());
   if (p->has_sqrtp) put(p->image, p->off_sqrtp, p->sqrt_p.data(), p->sqrt_p.size());
   int64_t max_chunks = 0;
@@ -797,14 +770,9 @@ int build_plan(const qw_csr *g, const qw_walk_desc *w, qw_plan *p) {
     wsec(p->state_bytes);                  // buffer 0 at offset 0
     p->off_w1 = wsec(p->state_bytes);      // buffer 1
   }
-  if (p->block_depth > 1 || p->series_depth > 1) p->off_w2 = wsec(p->state_bytes);  // buffer 2: the other psi
-  const size_t w3 = w_off;  // blocked series: buffer 3, over the readout's scratch
+  if (p->block_depth > 1) p->off_w2 = wsec(p->state_bytes);  // buffer 2: the other psi
   p->off_pscratch = wsec(sizeof(double) * static_cast<size_t>(n) * p->columns);
   p->off_partials = wsec(sizeof(double) * partials);
-  if (p->series_depth > 1) {
-    p->off_w3 = w3;
-    w_off = std::max(w_off, align256(w3 + p->state_bytes));
-  }
   if (structure == kDense) {
     GraphView dv;
     dv.n = static_cast<int32_t>(n);
@@ -936,52 +904,6 @@ int evolve_staggered(const qw_plan *p, void *psi, unsigned char *work, int64_t s
   return readout_only(p, psi, ro, s);
 }
 
-// Steps [i, i + m) of the walk as one series: Clenshaw's recurrence with d_k
-// in the two work buffers, the newer written over the one two stages older,
-// and the result over psi, which every stage reads element by element only.
-// `stage(y, out, StageCoef, last)` enqueues one stage.
-template <typename F>
-int run_series(const qw_plan *p, const Series &se, void *psi, void *w0, void *w1, F stage) {
-  const double beta = 2.0 / p->h_bound, alpha = p->gamma * beta;
-  void *buf[2] = {w0, w1};
-  const int M = se.terms;
-  for (int k = M - 1; k >= 0; --k) {
-    const int j = M - 1 - k;  // stage number
-    const double h = k ? 1.0 : 0.5;
-    StageCoef c{h * alpha, h * beta, se.a[k], nullptr};
-    const void *y = buf[(j + 1) & 1];
-    if (j == 0) {  // d_M = a_M psi is not stored
-      y = psi;
-      c.alpha *= se.a[M];
-      c.beta *= se.a[M];
-    } else if (j == 1) {
-      c.a += se.a[M];
-    } else {
-      c.prev = buf[j & 1];
-    }
-    const int st = stage(y, k ? buf[j & 1] : psi, c, k == 0);
-    if (st != QW_OK) return st;
-  }
-  return QW_OK;
-}
-
-// Calls `run(series)` for the leading steps that go through series: whole
-// groups, then, where the plan takes it, the rest.  *done counts the steps run.
-template <typename F> int for_each_series(const qw_plan *p, int64_t steps, int64_t *done, F run) {
-  *done = 0;
-  if (p->series.terms == 0) return QW_OK;
-  for (; steps - *done >= p->series.steps; *done += p->series.steps)
-    if (const int st = run(p->series); st != QW_OK) return st;
-  const int64_t rest = steps - *done;
-  Series se;
-  if (p->series_rest && rest >= kSeriesMinSteps && chebyshev_series(p->dt * p->h_bound, p->K, rest, &se) &&
-      se.terms < p->K * rest) {
-    if (const int st = run(se); st != QW_OK) return st;
-    *done = steps;
-  }
-  return QW_OK;
-}
-
 int evolve_ctqw(const qw_plan *p, void *psi, unsigned char *work, int64_t steps, const Readout &ro,
                 hipStream_t s) {
   const bool c128 = p->dtype == QW_C128;
@@ -993,59 +915,12 @@ int evolve_ctqw(const qw_plan *p, void *psi, unsigned char *work, int64_t steps,
     alpha[k - 1] = p->gamma * p->dt / k;
   }
   if (p->structure == kSmall) {
-    QW_TRY(ctqw_small(c128, g, psi, alpha.data(), beta.data(), K, p->small_series(), steps, ro, s), "CTQW small-graph kernel");
+    QW_TRY(ctqw_small(c128, g, psi, alpha.data(), beta.data(), K, steps, ro, s), "CTQW small-graph kernel");
     return QW_OK;
   }
   if (steps == 0) return readout_only(p, psi, ro, s);
   void *w0 = work, *w1 = work + p->off_w1;
-  GraphView gd = g;
-  gd.dense_partial = p->off_dpartial ? reinterpret_cast<double *>(work + p->off_dpartial) : nullptr;
-  int64_t first = 0;  // steps taken in groups
-  bool fused_done = false;
-  int st = QW_OK;
-  if (p->series_depth > 1) {
-    // blocked series: each launch reads psi and two vectors and writes two
-    // others, the last one the new psi, so the five buffers trade places
-    void *cur = psi, *spare[4] = {w0, w1, work + p->off_w2, work + p->off_w3};
-    st = for_each_series(p, steps, &first, [&](const Series &se) {
-      const int S = p->series_depth, launches = (se.terms + S - 1) / S, M = launches * S;
-      const double b2 = 2.0 / p->h_bound, a2 = p->gamma * b2;
-      for (int j = 0; j < launches; ++j) {
-        SweepSeries c{};
-        for (int t = 0; t < S; ++t) {
-          const int k = M - 1 - j * S - t;
-          const double h = (k ? 1.0 : 0.5) * (j || t ? 1.0 : se.a[M]);
-          c.alpha[t] = h * a2;
-          c.beta[t] = h * b2;
-          c.a[t] = se.a[k] + (j == 0 && t == 1 ? se.a[M] : 0.0);
-        }
-        void **in = spare + 2 * (j & 1), **out = spare + 2 * ((j + 1) & 1);
-        const bool last = j == launches - 1;
-        QW_TRY(torus_series_stages(g, S, cur, j ? in[0] : nullptr, j ? in[1] : nullptr, out[0],
-                                   last ? nullptr : out[1], c, s),
-               "grid CTQW series kernel");
-        if (last) std::swap(cur, out[0]);
-      }
-      return QW_OK;
-    });
-    if (st == QW_OK && cur != psi) QW_TRY(copy_state(c128, p->n, cur, psi, s), "state copy kernel");
-  } else {
-    st = for_each_series(p, steps, &first, [&](const Series &se) {
-      return run_series(p, se, psi, w0, w1, [&](const void *y, void *out, const StageCoef &c, bool last) {
-        if (p->structure == kDense) {
-          QW_TRY(dense_stage(c128, gd, y, psi, out, c, s), "dense series stage kernel");
-          return QW_OK;
-        }
-        const bool fuse = ro.any() && last && first + se.steps == steps;
-        QW_TRY(ctqw_stage(c128, g, y, psi, out, c, fuse ? &ro : nullptr, s), "CTQW series stage kernel");
-        fused_done |= fuse;
-        return QW_OK;
-      });
-    });
-  }
-  if (st != QW_OK) return st;
-  steps -= first;  // the others one at a time
-  if (p->block_depth > 1 && steps > 0) {
+  if (p->block_depth > 1) {
     // temporal blocking: K/S launches per step, each S stages in registers;
     // psi alternates between the caller's buffer and buffer 2, y between 0 and 1
     std::vector<double> a64(64, 0.0), b64(64, 0.0);
@@ -1075,17 +950,20 @@ int evolve_ctqw(const qw_plan *p, void *psi, unsigned char *work, int64_t steps,
     return readout_only(p, psi, ro, s);
   }
   if (p->structure == kDense) {
+    GraphView gd = g;
+    gd.dense_partial = p->off_dpartial ? reinterpret_cast<double *>(work + p->off_dpartial) : nullptr;
     for (int64_t i = 0; i < steps; ++i) {
       const void *yin = psi;
       for (int k = K; k >= 1; --k) {
         void *yout = (k == 1) ? (K == 1 ? w0 : psi) : (((K - k) & 1) ? w1 : w0);
-        QW_TRY(dense_stage(c128, gd, yin, psi, yout, {0.0, beta[k - 1]}, s), "dense Horner stage kernel");
+        QW_TRY(dense_stage(c128, gd, yin, psi, yout, beta[k - 1], s), "dense Horner stage kernel");
         yin = yout;
       }
       if (K == 1) QW_TRY(copy_state(c128, p->n * p->columns, w0, psi, s), "state copy kernel");
     }
     return readout_only(p, psi, ro, s);
   }
+  bool fused_done = false;
   for (int64_t i = 0; i < steps; ++i) {
     const void *yin = psi;
     for (int k = K; k >= 1; --k) {
@@ -1105,17 +983,6 @@ int evolve_ctqw(const qw_plan *p, void *psi, unsigned char *work, int64_t steps,
 }
 
 }  // namespace
-
-qwk::SmallSeries qw_plan::small_series() const {
-  qwk::SmallSeries s;
-  if (series.terms == 0) return s;
-  s.terms = series.terms;
-  s.steps = static_cast<int32_t>(series.steps);
-  s.beta = 2.0 / h_bound;
-  s.alpha = gamma * s.beta;
-  for (int k = 0; k <= series.terms; ++k) s.a[k] = series.a[k];
-  return s;
-}
 
 namespace qwk {
 
@@ -1237,8 +1104,6 @@ int qw_plan_upload(qw_plan *p, void *d_graph, size_t graph_bytes, void *stream) 
   g.marklist = reinterpret_cast<const int32_t *>(base + p->off_mlist);
   if (p->has_tmark) g.tmark = reinterpret_cast<const uint8_t *>(base + p->off_tmark);
   g.strip_rows = p->strip_rows;
-  if (p->series_depth > 1) g.series_mark = reinterpret_cast<const uint8_t *>(base + p->off_smark);
-  g.series_rows = p->series_rows;
   g.two_reg = p->two_reg;
   if (p->small_regs) g.order = reinterpret_cast<const int32_t *>(base + p->off_order);
   g.persistent = p->shift == QW_PERSISTENT;
@@ -1370,7 +1235,6 @@ int qw_small_many(const qw_plan *const *plans, void *const *d_psi, const int64_t
       w.beta[k - 1] = p->dt / k;
       w.alpha[k - 1] = p->gamma * p->dt / k;
     }
-    if (p->kind == QW_CTQW) w.series = p->small_series();
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
   const size_t bytes = qw_small_many_desc_bytes(count);

@@ -136,11 +136,6 @@ constexpr int kStagAhead64 = 2, kStagAhead128 = 1;
 constexpr int kDeepStages = 10, kDeepStagesSmall = 6, kDeepUnroll = 3;
 constexpr int64_t kDeepSmall = 700000, kDeepLarge = int64_t{1} << 21;
 
-// Coefficients of one launch of the grid's Chebyshev series (stage st at [st-1]).
-struct SweepSeries {
-  double a[5], alpha[5], beta[5];
-};
-
 // Strip decomposition of an l1 x l2 grid for S stages per launch.
 struct StripGrid {
   int rows = 0;     // core rows per strip
@@ -215,8 +210,6 @@ struct GraphView {
   const int32_t *marklist = nullptr;   // n_marked
   const uint8_t *tmark = nullptr;      // grid CTQW strips: 1 if a marked vertex lies in the strip's window
   int32_t strip_rows = 0;              // grid CTQW strips: core rows per strip
-  const uint8_t *series_mark = nullptr;  // the same two for the strips of the grid's series
-  int32_t series_rows = 0;
   int32_t two_reg = 0;                 // coined, one workgroup: 1 if every vertex has degree 2 and n <= 64
                                        // (amplitudes in one wavefront's registers), 2 if moreover a cycle in
                                        // direction order (rev[2v] = 2(v+1)+1, rev[2v+1] = 2(v-1), mod n)
@@ -230,13 +223,7 @@ struct GraphView {
   int32_t stag_regs = 0;               // staggered, one workgroup: polygons kept in registers (small_stag_regs)
 };
 
-// A Chebyshev series of a one-workgroup CTQW walk (terms == 0: none).
-struct SmallSeries {
-  int32_t terms = 0;
-  int32_t steps = 0;
-  double alpha = 0.0, beta = 0.0;
-  double a[66] = {};
-};
+;
 
 // One walk of a many-small-walks launch (the whole walk in one workgroup's LDS).
 struct SmallWalk {
@@ -249,7 +236,6 @@ struct SmallWalk {
   int64_t steps = 0;
   double alpha[64] = {};  // CTQW stage coefficients gamma dt / k, dt / k
   double beta[64] = {};
-  SmallSeries series;
 };
 
 // Readout request: any pointer may be null.  `pscratch` (n doubles) and
@@ -264,15 +250,11 @@ struct Readout {
   double *p_out() const { return p ? p : pscratch; }
 };
 
-// Coefficients of one stage y_out = base + i*(alpha*sum_nbr y + beta*[marked] y_v).
-// Horner stage: base = psi, alpha = gamma*dt/k, beta = dt/k.  Stage of a
-// Chebyshev series: base = a psi + prev, prev the stage before the last one
-// (null: none), element v of which may be where element v of y_out goes.
+// Coefficients of one Horner stage y_out = psi + i*(alpha*sum_nbr y + beta*[marked] y_v),
+// alpha = gamma*dt/k, beta = dt/k (FP64; rounded once for complex64).
 struct StageCoef {
   double alpha;
   double beta;
-  double a = 1.0;
-  const void *prev = nullptr;
 };
 
 // ---- launchers (qw_kernels.hip) -------------------------------------------
@@ -303,8 +285,7 @@ hipError_t coined_prob_csr(bool c128, const GraphView &g, const void *psi, const
 
 hipError_t small_many(bool c128, const SmallWalk *d_walks, int count, size_t lds, int threads, hipStream_t s);
 hipError_t ctqw_small(bool c128, const GraphView &g, void *psi, const double *alpha,
-                      const double *beta, int K, const SmallSeries &se, int64_t steps, const Readout &ro,
-                      hipStream_t s);
+                      const double *beta, int K, int64_t steps, const Readout &ro, hipStream_t s);
 size_t ctqw_small_lds(bool c128, int n, int n_arcs);
 hipError_t ctqw_stage(bool c128, const GraphView &g, const void *y, const void *psi, void *out,
                       StageCoef c, const Readout *fused, hipStream_t s);
@@ -316,8 +297,7 @@ hipError_t vertex_prob(bool c128, const GraphView &g, const void *psi, const Rea
 hipError_t dense_fill(bool c128, const GraphView &g, double gamma, size_t rows_pad, hipStream_t s);
 // Number of k ranges the dense stage splits into (1 = no split; partials then unused).
 int dense_splits(bool c128, const GraphView &g);
-// (c.beta is the stage's dt / k; a series only in complex128)
-hipError_t dense_stage(bool c128, const GraphView &g, const void *y, const void *psi, void *out, const StageCoef &c,
+hipError_t dense_stage(bool c128, const GraphView &g, const void *y, const void *psi, void *out, double c,
                        hipStream_t s);
 
 // Grid CTQW with temporal blocking: depth S (stages per launch, dividing K;
@@ -334,12 +314,6 @@ hipError_t torus_deep(const GraphView &g, int core, int S, const void *P, const 
 StripGrid torus_strips(bool c128, int l1, int l2, int S);
 hipError_t torus_block_stages(bool c128, const GraphView &g, int S, const void *P, const void *Yin, void *Out,
                               int kfirst, const double *alpha, const double *beta, hipStream_t s);
-
-// S stages of a grid's Chebyshev series (complex128) from (P, D1, D2) to (E1,
-// E2), all distinct buffers; D1 null: the series' first launch (D2 unused);
-// E2 null: its last.
-hipError_t torus_series_stages(const GraphView &g, int S, const void *P, const void *D1, const void *D2, void *E1,
-                               void *E2, const SweepSeries &c, hipStream_t s);
 
 // Staggered walk.  stag_small: every step in one workgroup's LDS (descriptors
 // read from g.stag).  stag_tess: one tessellation in place on psi; `mark`

@@ -931,25 +931,12 @@ __device__ __forceinline__ double2 horner_out(double2 psi, double2 nsum, double2
   return make_double2(re, im);
 }
 
-// What a stage adds H y to (StageCoef): a psi + prev, or a psi where there is
-// no prev.  A Horner stage has a = 1 and no prev: 1 * psi is psi bit for bit
-// (complex64 walks have no other stages).
-template <typename T>
-__device__ __forceinline__ double2 stage_base(const T *psi, const T *prev, double a, int64_t v) {
-  const double2 x = ld(psi, v);
-  if constexpr (sizeof(T) == 8) return x;
-  if (!prev) return scale(x, a);
-  const double2 q = ld(prev, v);
-  return make_double2(__fma_rn(a, x.x, q.x), __fma_rn(a, x.y, q.y));
-}
-
 // General CSR, G lanes per row (G in 1..64, power of two), lane sums strided
 // by G then a butterfly across the G lanes.  PROB fuses the readout.
 template <typename T, int G, bool PROB>
 __global__ __launch_bounds__(kBlock) void k_ctqw_csr(GraphView g, const T *__restrict__ y,
                                                      const T *psi, T *out, double alpha, double beta,
-                                                     double base_a, const T *prev, double *p,
-                                                     double *partials) {
+                                                     double *p, double *partials) {
   __shared__ double red[16];
   const int gid = blockIdx.x * blockDim.x + threadIdx.x;
   const int row = gid / G, lane = gid % G;
@@ -991,7 +978,7 @@ __global__ __launch_bounds__(kBlock) void k_ctqw_csr(GraphView g, const T *__res
   if (row < g.n && lane == 0) {
     const bool mk = marked(g.markbits, row);
     double2 yv = mk ? ld(y, row) : make_double2(0.0, 0.0);
-    double2 r = horner_out(stage_base(psi, prev, base_a, row), make_double2(sx, sy), yv, mk, alpha, beta);
+    double2 r = horner_out(ld(psi, row), make_double2(sx, sy), yv, mk, alpha, beta);
     st(out, row, r);
     if (PROB) {
       T stored = pack<T>(r);
@@ -1092,8 +1079,8 @@ __global__ __launch_bounds__(kDirRows) void k_ctqw_csr_direct(const int32_t *__r
 // Regular graphs: ELL stage, one thread per row, column-major neighbour table.
 template <typename T, bool PROB>
 __global__ __launch_bounds__(kBlock) void k_ctqw_ell(GraphView g, const T *__restrict__ y, const T *psi,
-                                                     T *out, double alpha, double beta, double base_a,
-                                                     const T *prev, double *p, double *partials) {
+                                                     T *out, double alpha, double beta, double *p,
+                                                     double *partials) {
   __shared__ double red[16];
   const int n = g.n;
   const int v = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1102,7 +1089,7 @@ __global__ __launch_bounds__(kBlock) void k_ctqw_ell(GraphView g, const T *__res
     const double2 s = ell_gather_sum(y, g.col, n, g.ell_d, v);
     const bool mk = marked(g.markbits, v);
     const double2 yv = mk ? ld(y, v) : make_double2(0.0, 0.0);
-    const double2 r = horner_out(stage_base(psi, prev, base_a, v), s, yv, mk, alpha, beta);
+    const double2 r = horner_out(ld(psi, v), s, yv, mk, alpha, beta);
     st(out, v, r);
     if (PROB) {
       pv = abs2(cvt(pack<T>(r)));
@@ -1127,8 +1114,7 @@ __global__ __launch_bounds__(kBlock) void k_ctqw_ell(GraphView g, const T *__res
 // k_ctqw_ell.
 template <typename T, int RPT>
 __global__ __launch_bounds__(kBlock) void k_ctqw_ell_sliced(GraphView g, const T *__restrict__ y, const T *psi,
-                                                            T *out, double alpha, double beta, double base_a,
-                                                            const T *prev, int slice) {
+                                                            T *out, double alpha, double beta, int slice) {
   const int n = g.n, d = g.ell_d;
   const int n_groups = (n + kBlock * RPT - 1) / (kBlock * RPT);
   for (int grp = blockIdx.x; grp < n_groups; grp += gridDim.x) {
@@ -1163,7 +1149,7 @@ __global__ __launch_bounds__(kBlock) void k_ctqw_ell_sliced(GraphView g, const T
       if (r >= n) continue;
       const bool mk = marked(g.markbits, r);
       const double2 yv = mk ? ld(y, r) : make_double2(0.0, 0.0);
-      st(out, r, horner_out(stage_base(psi, prev, base_a, r), acc[i], yv, mk, alpha, beta));
+      st(out, r, horner_out(ld(psi, r), acc[i], yv, mk, alpha, beta));
     }
   }
 }
@@ -1176,8 +1162,7 @@ __global__ __launch_bounds__(kBlock) void k_ctqw_ell_sliced(GraphView g, const T
 // across the row's lanes, are those of k_ctqw_csr<G>: the same bits.
 template <typename T, int G>
 __global__ __launch_bounds__(kBlock) void k_ctqw_csr_sliced(GraphView g, const T *__restrict__ y, const T *psi,
-                                                            T *out, double alpha, double beta, double base_a,
-                                                            const T *prev, int slice) {
+                                                            T *out, double alpha, double beta, int slice) {
   constexpr int RPW = kBlock / G;  // rows per workgroup
   const int n = g.n;
   const int n_groups = (n + RPW - 1) / RPW;
@@ -1218,7 +1203,7 @@ __global__ __launch_bounds__(kBlock) void k_ctqw_csr_sliced(GraphView g, const T
     if (row < n && lane == 0) {
       const bool mk = marked(g.markbits, row);
       const double2 yv = mk ? ld(y, row) : make_double2(0.0, 0.0);
-      st(out, row, horner_out(stage_base(psi, prev, base_a, row), make_double2(sx, sy), yv, mk, alpha, beta));
+      st(out, row, horner_out(ld(psi, row), make_double2(sx, sy), yv, mk, alpha, beta));
     }
   }
 }
@@ -1242,9 +1227,8 @@ template <typename K> int resident_groups(K kernel) {
 // Structured stencils (no index arrays): neighbours computed from v.
 template <typename T, int KIND, bool PROB>
 __global__ __launch_bounds__(kBlock) void k_ctqw_struct(GraphView g, const T *__restrict__ y,
-                                                        const T *psi, T *out, double alpha, double beta,
-                                                        double base_a, const T *prev, double *p,
-                                                        double *partials) {
+                                                        const T *psi, T *out, double alpha,
+                                                        double beta, double *p, double *partials) {
   __shared__ double red[16];
   const int n = g.n;
   const int v = xcd_remap(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
@@ -1263,7 +1247,7 @@ __global__ __launch_bounds__(kBlock) void k_ctqw_struct(GraphView g, const T *__
     }
     const bool mk = marked(g.markbits, v);
     double2 yv = mk ? ld(y, v) : make_double2(0.0, 0.0);
-    double2 r = horner_out(stage_base(psi, prev, base_a, v), s, yv, mk, alpha, beta);
+    double2 r = horner_out(ld(psi, v), s, yv, mk, alpha, beta);
     st(out, v, r);
     if (PROB) {
       pv = abs2(cvt(pack<T>(r)));
@@ -1603,153 +1587,6 @@ __global__ __launch_bounds__(64 * kStripWaves) void k_ctqw_torus_deep(GraphView 
     deep_strip<S, YP, false>(g, P, Yin, Out, c, R, rb, lane, gcol, keep);
 }
 
-// S stages of a Chebyshev series on a strip, complex128: the sweep above with
-// d_k = a psi + d_{k+2} + i (alpha nsum + beta [marked] d_{k+1}) in place of
-// the Horner stage.  d_{k+2} of a stage is the row that the stage before the
-// last one still holds among its three; the first stage's comes from memory
-// (D2, loaded with D1 and psi), and the last two stages' rows leave together,
-// as the next launch's D1 and D2.  FIRST: the series' first launch, whose
-// d_{k+1} is psi itself (its factor is in the coefficients) and whose d_{k+2}
-// are folded into a.  E2 null: the last launch, of which only E1 is wanted.
-// 1024 x 1024: a launch moves 5 vectors of 16.8 MB for its 5 stages, 3 when
-// Horner stages do; the series needs 17 stages where those need 320.
-template <int S, bool FIRST, bool MARK>
-__device__ __forceinline__ void series_strip(const GraphView &g, const double2 *__restrict__ P,
-                                             const double2 *__restrict__ D1, const double2 *__restrict__ D2,
-                                             double2 *__restrict__ E1, double2 *__restrict__ E2,
-                                             const SweepSeries &c, int R, int rb, int lane, int gcol, unsigned boff) {
-  constexpr int RING = kSweepRing, W = 64;
-  static_assert(S >= 2 && S < RING, "psi ring holds rows t-S .. t");
-  const int l1 = g.dims[0], l2 = g.dims[1];
-  const int n_in = R + 2 * S;
-  auto row_off = [&](int t) -> size_t {
-    const int gr = rb + t;  // < 2 l1 since n_in <= l1
-    return static_cast<size_t>(gr >= l1 ? gr - l1 : gr) * l2;
-  };
-  auto at = [](const double2 *row, unsigned off) -> double2 {
-    return *reinterpret_cast<const double2 *>(reinterpret_cast<const char *>(row) + off);
-  };
-  double2 np[RING], n1[RING], n2[RING];  // rows of the next body
-  uint32_t nmw[RING], nms[RING];
-  auto fetch = [&](int t0) {
-#pragma unroll
-    for (int i = 0; i < RING; ++i) {
-      const size_t o = row_off(min(t0 + i, n_in - 1));
-      np[i] = at(P + o, boff);
-      if (!FIRST) {
-        n1[i] = at(D1 + o, boff);
-        n2[i] = at(D2 + o, boff);
-      }
-      if (MARK) {
-        const int v = static_cast<int>(o) + gcol;
-        nmw[i] = g.markbits[v >> 5];
-        nms[i] = static_cast<uint32_t>(v & 31);
-      }
-    }
-  };
-  double2 yv[S][3];  // stage s-1 (s = 1 .. S) rows, slot = window row mod 3
-  double2 dr[3];     // D2 rows, slot = window row mod 3
-  double2 pr[RING];  // psi, slot = window row mod RING
-  uint32_t mr = 0;   // bit k: window row t - k is marked
-  const double2 zero = make_double2(0.0, 0.0);
-#pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    dr[j] = zero;
-#pragma unroll
-    for (int s = 0; s < S; ++s) yv[s][j] = zero;
-  }
-#pragma unroll
-  for (int j = 0; j < RING; ++j) pr[j] = zero;
-
-  auto body = [&](int t0, auto full_tag) {
-    constexpr bool FULL = decltype(full_tag)::value;
-    double2 cp[RING], c1[RING], c2[RING];
-    uint32_t cmw[RING], cms[RING];
-#pragma unroll
-    for (int i = 0; i < RING; ++i) {
-      cp[i] = np[i];
-      if (!FIRST) {
-        c1[i] = n1[i];
-        c2[i] = n2[i];
-      }
-      if (MARK) {
-        cmw[i] = nmw[i];
-        cms[i] = nms[i];
-      }
-    }
-    if (t0 + RING < n_in) fetch(t0 + RING);
-#pragma unroll
-    for (int i = 0; i < RING; ++i) {
-      const int t = t0 + i;
-      if (!FULL && t >= n_in) break;
-      yv[0][i % 3] = FIRST ? cp[i] : c1[i];
-      if (!FIRST) dr[i % 3] = c2[i];
-      pr[i] = cp[i];
-      if (MARK) mr = (mr << 1) | ((cmw[i] >> cms[i]) & 1u);
-#pragma unroll
-      for (int st = 1; st <= S; ++st) {
-        if (!FULL && t < 2 * st) break;
-        const double2 up = yv[st - 1][pmod(i - st - 1, 3)];
-        const double2 self = yv[st - 1][pmod(i - st, 3)];
-        const double2 dn = yv[st - 1][pmod(i - st + 1, 3)];
-        const double2 left = lane_shift<kFromLower>(self), right = lane_shift<kFromUpper>(self);
-        double2 sum = add(right, left);
-        sum = add(sum, dn);
-        sum = add(sum, up);
-        const double a = c.a[st - 1];
-        const double2 ps = pr[pmod(i - st, RING)];
-        double2 base;
-        if (FIRST && st <= 2) {
-          base = scale(ps, a);
-        } else {
-          const double2 q = st == 1 ? dr[pmod(i - 1, 3)] : yv[st >= 2 ? st - 2 : 0][pmod(i - st, 3)];
-          base = make_double2(__fma_rn(a, ps.x, q.x), __fma_rn(a, ps.y, q.y));
-        }
-        const bool m = MARK && ((mr >> st) & 1u);
-        const double2 val = horner_out(base, sum, self, m, c.alpha[st - 1], c.beta[st - 1]);
-        if (st < S) {
-          yv[st][pmod(i - st, 3)] = val;
-        } else if (lane >= S && lane < W - S) {
-          const size_t o = row_off(t - S);
-          *reinterpret_cast<double2 *>(reinterpret_cast<char *>(E1 + o) + boff) = val;
-          if (E2) *reinterpret_cast<double2 *>(reinterpret_cast<char *>(E2 + o) + boff) = self;
-        }
-      }
-    }
-  };
-  fetch(0);
-  int t0 = 0;
-  for (; t0 < 2 * S; t0 += RING) body(t0, std::false_type{});
-  for (; t0 + RING <= n_in; t0 += RING) body(t0, std::true_type{});
-  if (t0 < n_in) body(t0, std::false_type{});
-}
-
-template <int S, bool FIRST>
-__global__ __launch_bounds__(64 * kStripWaves) void k_ctqw_torus_series(GraphView g, const double2 *__restrict__ P,
-                                                                        const double2 *__restrict__ D1,
-                                                                        const double2 *__restrict__ D2,
-                                                                        double2 *__restrict__ E1,
-                                                                        double2 *__restrict__ E2, SweepSeries c) {
-  constexpr int CORE = 64 - 2 * S;
-  const int l1 = g.dims[0], l2 = g.dims[1], R = g.series_rows;
-  const int tiles_c = (l2 + CORE - 1) / CORE, tiles_r = (l1 + R - 1) / R;
-  const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
-  const int tile = xcd_remap(blockIdx.x, gridDim.x) * kStripWaves + wv;
-  if (tile >= tiles_r * tiles_c) return;  // whole wavefront
-  const int lane = threadIdx.x & 63;
-  const int tr = tile / tiles_c, tc = tile - tr * tiles_c;
-  int rb = min(tr * R, l1 - R) - S, cb = min(tc * CORE, l2 - CORE) - S;
-  rb += rb < 0 ? l1 : 0;
-  cb += cb < 0 ? l2 : 0;
-  int gcol = cb + lane;  // < 2 l2 since 64 <= l2
-  gcol -= gcol >= l2 ? l2 : 0;
-  const unsigned boff = static_cast<unsigned>(gcol) * static_cast<unsigned>(sizeof(double2));
-  if (g.series_mark[tile])
-    series_strip<S, FIRST, true>(g, P, D1, D2, E1, E2, c, R, rb, lane, gcol, boff);
-  else
-    series_strip<S, FIRST, false>(g, P, D1, D2, E1, E2, c, R, rb, lane, gcol, boff);
-}
-
 // FP64 readout of a one-workgroup vertex walk whose final state is ps (LDS).
 template <typename T>
 __device__ void small_vertex_readout(const GraphView &g, const T *ps, const Readout &ro, double *red) {
@@ -1807,7 +1644,7 @@ __device__ __forceinline__ double lane_value(double x, int k) {
 // copies of the stage (0.60 to 0.72).
 template <typename T, int VPT>
 __device__ void ctqw_small_regs(const GraphView &g, T *psi, const double *alpha, const double *beta, int K,
-                                const SmallSeries &se, int64_t steps, const Readout &ro, unsigned char *smem,
+                                int64_t steps, const Readout &ro, unsigned char *smem,
                                 double *red) {
   const int n = g.n, lane = threadIdx.x & 63;
   T *ps = reinterpret_cast<T *>(smem), *ya = ps + n + 1, *yb = ya + n + 1;
@@ -1815,7 +1652,7 @@ __device__ void ctqw_small_regs(const GraphView &g, T *psi, const double *alpha,
   constexpr int D0 = small_row(C128, VPT, 0);
   int c[VPT][D0], vert[VPT], quads[VPT];  // quads: the wavefront's longest row, in fours
   bool mk[VPT];
-  T own[VPT], d1[VPT], d2[VPT];  // psi and the last two stages' values of the own vertices
+  T own[VPT], last[VPT];  // psi and the last stage's values of the own vertices
 #pragma unroll
   for (int i = 0; i < VPT; ++i) {
     const int r = threadIdx.x + i * blockDim.x;
@@ -1837,10 +1674,9 @@ __device__ void ctqw_small_regs(const GraphView &g, T *psi, const double *alpha,
     ps[n] = ya[n] = yb[n] = pad;
   }
   const double la = lane < K ? alpha[lane] : 0.0, lb = lane < K ? beta[lane] : 0.0;  // K <= 64
-  const double ls = se.terms > 0 && lane < se.terms ? se.a[lane] : 0.0, top = se.terms > 0 ? se.a[se.terms] : 0.0;
   __syncthreads();
-  // d1 = base + i (a2 nsum + b2 [marked] d1) on every own vertex, also to yout
-  auto stage = [&](const T *yin, T *yout, double a2, double b2, auto base) {
+  // last = psi + i (a2 nsum + b2 [marked] last) on every own vertex, also to yout
+  auto stage = [&](const T *yin, T *yout, double a2, double b2) {
 #pragma unroll
     for (int i = 0; i < VPT; ++i) {
       if (vert[i] >= n) continue;  // idle wavefronts leave the others their issue slots
@@ -1855,47 +1691,25 @@ __device__ void ctqw_small_regs(const GraphView &g, T *psi, const double *alpha,
           else if (4 * quads[i] > j) sum = lds_gather_sum<T, 4>(sum, yin, c[i] + j);
         }
       }
-      const double2 yv = mk[i] ? cvt(d1[i]) : make_double2(0.0, 0.0);
-      const T r = pack<T>(horner_out(base(i), sum, yv, mk[i], a2, b2));
+      const double2 yv = mk[i] ? cvt(last[i]) : make_double2(0.0, 0.0);
+      const T r = pack<T>(horner_out(cvt(own[i]), sum, yv, mk[i], a2, b2));
       yout[vert[i]] = r;
-      d2[i] = d1[i];
-      d1[i] = r;
+      last[i] = r;
     }
     __syncthreads();
   };
-  // (only complex128 plans have a series)
-  for (; C128 && se.terms > 0 && steps >= se.steps; steps -= se.steps) {
-#pragma unroll
-    for (int i = 0; i < VPT; ++i) d1[i] = own[i];
-    T *in = ps, *out = ya;
-    for (int k = se.terms - 1; k >= 0; --k) {
-      const bool first = k == se.terms - 1, second = k == se.terms - 2;
-      const double h = (k ? 1.0 : 0.5) * (first ? top : 1.0);
-      const double ak = lane_value(ls, k);
-      const double a = second ? ak + top : ak;  // d_M = a_M psi is folded into the first two stages
-      if (k == 0) out = ps;
-      stage(in, out, h * se.alpha, h * se.beta, [&](int i) {
-        const double2 x = cvt(own[i]), q = first || second ? make_double2(0.0, 0.0) : cvt(d2[i]);
-        return make_double2(__fma_rn(a, x.x, q.x), __fma_rn(a, x.y, q.y));
-      });
-      in = out;
-      out = in == ya ? yb : ya;
-    }
-#pragma unroll
-    for (int i = 0; i < VPT; ++i) own[i] = d1[i];
-  }
   for (int64_t s = 0; s < steps; ++s) {
 #pragma unroll
-    for (int i = 0; i < VPT; ++i) d1[i] = own[i];
+    for (int i = 0; i < VPT; ++i) last[i] = own[i];
     T *in = ps, *out = ya;
     for (int k = K; k >= 1; --k) {
       if (k == 1) out = ps;  // K >= 2: this stage reads another vector
-      stage(in, out, lane_value(la, k - 1), lane_value(lb, k - 1), [&](int i) { return cvt(own[i]); });
+      stage(in, out, lane_value(la, k - 1), lane_value(lb, k - 1));
       in = out;
       out = in == ya ? yb : ya;
     }
 #pragma unroll
-    for (int i = 0; i < VPT; ++i) own[i] = d1[i];
+    for (int i = 0; i < VPT; ++i) own[i] = last[i];
   }
 #pragma unroll
   for (int i = 0; i < VPT; ++i)
@@ -1906,15 +1720,15 @@ __device__ void ctqw_small_regs(const GraphView &g, T *psi, const double *alpha,
 // CTQW small graphs: every stage of every step in one workgroup, vectors in LDS.
 template <typename T>
 __device__ void ctqw_small_walk(const GraphView &g, T *psi, const double *alpha, const double *beta, int K,
-                                const SmallSeries &se, int64_t steps, const Readout &ro, unsigned char *smem,
+                                int64_t steps, const Readout &ro, unsigned char *smem,
                                 double *red) {
   const int n = g.n, na = g.n_arcs;
   if (g.order) {
     // the plan has checked degree, size and K; a workgroup has min(n, 1024) threads at least
     const int bd = static_cast<int>(blockDim.x);
-    if (n <= bd) ctqw_small_regs<T, 1>(g, psi, alpha, beta, K, se, steps, ro, smem, red);
-    else if (n <= 2 * bd) ctqw_small_regs<T, 2>(g, psi, alpha, beta, K, se, steps, ro, smem, red);
-    else ctqw_small_regs<T, 4>(g, psi, alpha, beta, K, se, steps, ro, smem, red);
+    if (n <= bd) ctqw_small_regs<T, 1>(g, psi, alpha, beta, K, steps, ro, smem, red);
+    else if (n <= 2 * bd) ctqw_small_regs<T, 2>(g, psi, alpha, beta, K, steps, ro, smem, red);
+    else ctqw_small_regs<T, 4>(g, psi, alpha, beta, K, steps, ro, smem, red);
     return;
   }
   T *ps = reinterpret_cast<T *>(smem);
@@ -1956,10 +1770,10 @@ __device__ void ctqw_small_walk(const GraphView &g, T *psi, const double *alpha,
 
 template <typename T>
 __global__ __launch_bounds__(1024) void k_ctqw_small(GraphView g, T *psi, Coefs c, int K,
-                                                     SmallSeries se, int64_t steps, Readout ro) {
+                                                     int64_t steps, Readout ro) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ double red[16];
-  ctqw_small_walk<T>(g, psi, c.alpha, c.beta, K, se, steps, ro, smem, red);
+  ctqw_small_walk<T>(g, psi, c.alpha, c.beta, K, steps, ro, smem, red);
 }
 
 // ---- staggered walk -----------------------------------------------------------
@@ -2410,7 +2224,7 @@ __global__ __launch_bounds__(1024) void k_small_many(const SmallWalk *__restrict
   else if (w.coined)
     coined_small_walk<T>(w.g, static_cast<T *>(w.psi), w.hadamard, w.steps, none, smem, red);
   else
-    ctqw_small_walk<T>(w.g, static_cast<T *>(w.psi), w.alpha, w.beta, w.K, w.series, w.steps, none, smem, red);
+    ctqw_small_walk<T>(w.g, static_cast<T *>(w.psi), w.alpha, w.beta, w.K, w.steps, none, smem, red);
 }
 
 // ---- batched launch over many walks -------------------------------------------
@@ -2852,18 +2666,11 @@ template <> struct Mfma<float> {
   }
 };
 
-// What a dense stage adds to (StageCoef): a psi + prev, or a psi.
-template <typename R>
-__device__ __forceinline__ double dense_base(const R *psi, const R *prev, double a, int64_t i) {
-  const double x = static_cast<double>(psi[i]);
-  return prev ? __fma_rn(a, x, static_cast<double>(prev[i])) : a * x;
-}
-
-// A wavefront's 16 x 16 NT results z(t, r): y_out = base + c (b - i a), or the
+// A wavefront's 16 x 16 NT results z(t, r): y_out = psi + c (b - i a), or the
 // raw products where k is split over workgroups.
 template <typename R, int NT, typename Z>
 __device__ __forceinline__ void dense_store(Z z_of, int row0, int col0, int l, int n, int c2, int split, const R *psi,
-                                            R *out, double c, double base_a, const R *prev, double *partial) {
+                                            R *out, double c, double *partial) {
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
 #pragma unroll
@@ -2878,7 +2685,7 @@ __device__ __forceinline__ void dense_store(Z z_of, int row0, int col0, int l, i
       }
       if (row < n && col < c2) {
         const int64_t idx = static_cast<int64_t>(row) * c2 + col;
-        const double ps = dense_base(psi, prev, base_a, idx);
+        const double ps = static_cast<double>(psi[idx]);
         out[idx] = static_cast<R>((col & 1) ? ps - c * zp : ps + c * zp);
       }
     }
@@ -2888,8 +2695,7 @@ __device__ __forceinline__ void dense_store(Z z_of, int row0, int col0, int l, i
 template <typename R, int NT, int KC>
 __global__ __launch_bounds__(256) void k_dense_stage(const R *__restrict__ H, int ld, int n, int c2,
                                                      const R *__restrict__ yin, const R *psi, R *out,
-                                                     double c, double base_a, const R *prev, int ksplit,
-                                                     double *partial) {
+                                                     double c, int ksplit, double *partial) {
   using M = Mfma<R>;
   constexpr int NC = NT * 16;
   static_assert(kDenseK % KC == 0 && 256 % KC == 0, "chunks tile the split ranges and the FP32 fold");
@@ -2966,7 +2772,7 @@ __global__ __launch_bounds__(256) void k_dense_stage(const R *__restrict__ H, in
     }
   }
   dense_store<R, NT>([&](int t, int r) { return wide[t][r] + static_cast<double>(acc[t][r]); }, row0 + wave * 16, 0, l,
-                     n, c2, split, psi, out, c, base_a, prev, partial);
+                     n, c2, split, psi, out, c, partial);
 }
 
 // FP64 H times 33 or more real columns: bound by the FP64 matrix rate (78.6
@@ -2985,8 +2791,7 @@ __global__ __launch_bounds__(256) void k_dense_stage(const R *__restrict__ H, in
 template <int NT, int KC>
 __global__ __launch_bounds__(512) void k_dense_stage_f64(const double *__restrict__ H, int ld, int n, int c2,
                                                          const double *__restrict__ yin, const double *psi,
-                                                         double *out, double c, double base_a, const double *prev,
-                                                         int ksplit, double *partial) {
+                                                         double *out, double c, int ksplit, double *partial) {
   using M = Mfma<double>;
   constexpr int NC = NT * 16, STR = NC + 4, SUB = KC / 16;
   constexpr int NW = NT / 2;              // tiles of 16 real columns per wavefront
@@ -3070,8 +2875,8 @@ __global__ __launch_bounds__(512) void k_dense_stage_f64(const double *__restric
     chunk(std::integral_constant<int, 0>{}, k0);
     if (k0 + KC < kend) chunk(std::integral_constant<int, 1>{}, k0 + KC);
   }
-  dense_store<double, NW>([&](int t, int r) { return acc[t][r]; }, row0, half * NW * 16, l, n, c2, split, psi, out, c, base_a, prev,
-                          partial);
+  dense_store<double, NW>([&](int t, int r) { return acc[t][r]; }, row0, half * NW * 16, l, n, c2, split, psi, out,
+                          c, partial);
 }
 
 // One walk with FP32 H: H y is bound by streaming H once, so it runs on the
@@ -3164,8 +2969,7 @@ __global__ __launch_bounds__(256) void k_dense_gemv(const R *__restrict__ H, int
 // then y_out = psi + c (b - i a) for z = a + i b.  One thread per complex entry.
 template <typename R>
 __global__ __launch_bounds__(kBlock) void k_dense_reduce(const double *__restrict__ partial, int splits, int n,
-                                                         int c2, const R *psi, R *out, double c, double base_a,
-                                                         const R *prev) {
+                                                         int c2, const R *psi, R *out, double c) {
   const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;  // complex index
   const int64_t total = static_cast<int64_t>(n) * (c2 / 2);
   if (e >= total) return;
@@ -3175,7 +2979,7 @@ __global__ __launch_bounds__(kBlock) void k_dense_reduce(const double *__restric
     a += ps[0];
     b += ps[1];
   }
-  const double pr = dense_base(psi, prev, base_a, 2 * e), pi = dense_base(psi, prev, base_a, 2 * e + 1);
+  const double pr = static_cast<double>(psi[2 * e]), pi = static_cast<double>(psi[2 * e + 1]);
   out[2 * e] = static_cast<R>(pr + c * b);
   out[2 * e + 1] = static_cast<R>(pi - c * a);
 }
@@ -3197,8 +3001,7 @@ __global__ __launch_bounds__(kBlock) void k_dense_scatter(GraphView g, R *H, dou
 }
 
 template <typename R, int NT>
-void launch_dense(const GraphView &g, const void *y, const void *psi, void *out, double c, double a,
-                  const void *prev, hipStream_t s) {
+void launch_dense(const GraphView &g, const void *y, const void *psi, void *out, double c, hipStream_t s) {
   const int rblocks = (g.n + kDenseRows - 1) / kDenseRows;
   const int splits = dense_splits(sizeof(R) == 8, g);
   const int ksplit = ((g.n + splits - 1) / splits + kDenseK - 1) / kDenseK * kDenseK;
@@ -3212,17 +3015,15 @@ void launch_dense(const GraphView &g, const void *y, const void *psi, void *out,
   if constexpr (sizeof(R) == 8 && NT >= 4)
     hipLaunchKernelGGL((k_dense_stage_f64<NT, NT <= 8 ? 32 : 16>), grid, dim3(512), 0, s,
                        static_cast<const double *>(g.dense), g.ld, g.n, 2 * g.columns, static_cast<const double *>(y),
-                       static_cast<const double *>(psi), static_cast<double *>(out), c, a,
-                       static_cast<const double *>(prev), ksplit, partial);
+                       static_cast<const double *>(psi), static_cast<double *>(out), c, ksplit, partial);
   else
     hipLaunchKernelGGL((k_dense_stage<R, NT, KC>), grid, dim3(256), 0, s, static_cast<const R *>(g.dense), g.ld, g.n,
                        2 * g.columns, static_cast<const R *>(y), static_cast<const R *>(psi), static_cast<R *>(out),
-                       c, a, static_cast<const R *>(prev), ksplit, partial);
+                       c, ksplit, partial);
   if (partial) {
     const int64_t total = static_cast<int64_t>(g.n) * g.columns;
     hipLaunchKernelGGL(k_dense_reduce<R>, dim3(blocks_for(total, kBlock)), dim3(kBlock), 0, s, partial, used,
-                       g.n, 2 * g.columns, static_cast<const R *>(psi), static_cast<R *>(out), c, a,
-                       static_cast<const R *>(prev));
+                       g.n, 2 * g.columns, static_cast<const R *>(psi), static_cast<R *>(out), c);
   }
 }
 
@@ -3234,18 +3035,17 @@ void launch_gemv(const GraphView &g, const void *y, const void *psi, void *out, 
 }
 
 template <typename R>
-void launch_dense_nt(const GraphView &g, const void *y, const void *psi, void *out, double c, double a,
-                     const void *prev, hipStream_t s) {
+void launch_dense_nt(const GraphView &g, const void *y, const void *psi, void *out, double c, hipStream_t s) {
   const int c2 = 2 * g.columns;
   // the vector kernel reads 2 B state reals per H element from cache; the
   // LDS-staged matrix-core kernel streams H at a rate that does not depend on
   // B up to 8 walks: for FP64 H it is ahead from B = 1, for FP32 H from B = 2
   if (sizeof(R) == 4 && g.columns == 1) return launch_gemv<R, 1, 4>(g, y, psi, out, c, s);
-  if (c2 <= 16) launch_dense<R, 1>(g, y, psi, out, c, a, prev, s);
-  else if (c2 <= 32) launch_dense<R, 2>(g, y, psi, out, c, a, prev, s);
-  else if (c2 <= 64) launch_dense<R, 4>(g, y, psi, out, c, a, prev, s);
-  else if (c2 <= 128) launch_dense<R, 8>(g, y, psi, out, c, a, prev, s);
-  else launch_dense<R, 16>(g, y, psi, out, c, a, prev, s);
+  if (c2 <= 16) launch_dense<R, 1>(g, y, psi, out, c, s);
+  else if (c2 <= 32) launch_dense<R, 2>(g, y, psi, out, c, s);
+  else if (c2 <= 64) launch_dense<R, 4>(g, y, psi, out, c, s);
+  else if (c2 <= 128) launch_dense<R, 8>(g, y, psi, out, c, s);
+  else launch_dense<R, 16>(g, y, psi, out, c, s);
 }
 
 
@@ -3269,8 +3069,8 @@ template <typename T> hipError_t launch_coined_small(const GraphView &g, void *p
 }
 
 template <typename T> hipError_t launch_ctqw_small(const GraphView &g, void *psi, const double *alpha,
-                                                   const double *beta, int K, const SmallSeries &se,
-                                                   int64_t steps, const Readout &ro, hipStream_t s) {
+                                                   const double *beta, int K, int64_t steps, const Readout &ro,
+                                                   hipStream_t s) {
   Coefs c;
   for (int k = 0; k < 64; ++k) {
     c.alpha[k] = k < K ? alpha[k] : 0.0;
@@ -3280,7 +3080,7 @@ template <typename T> hipError_t launch_ctqw_small(const GraphView &g, void *psi
   if (hipError_t e = allow_lds(&k_ctqw_small<T>, lds); e != hipSuccess) return e;
   int threads = 64;
   while (threads < 1024 && threads < g.n) threads *= 2;
-  hipLaunchKernelGGL(k_ctqw_small<T>, dim3(1), dim3(threads), lds, s, g, static_cast<T *>(psi), c, K, se,
+  hipLaunchKernelGGL(k_ctqw_small<T>, dim3(1), dim3(threads), lds, s, g, static_cast<T *>(psi), c, K,
                      steps, ro);
   return hipGetLastError();
 }
@@ -3353,13 +3153,13 @@ void launch_csr_g(const GraphView &g, const T *y, const T *psi, T *out, StageCoe
     constexpr int GS = G <= 16 ? G : 16;
     const int groups = static_cast<int>(blocks_for(g.n, kBlock / GS));
     const dim3 sgrid(std::min(groups, resident_groups(k_ctqw_csr_sliced<T, GS>)));
-    hipLaunchKernelGGL((k_ctqw_csr_sliced<T, GS>), sgrid, dim3(kBlock), 0, s, g, y, psi, out, c.alpha, c.beta, c.a,
-                       static_cast<const T *>(c.prev), kEllSliceEntries);
+    hipLaunchKernelGGL((k_ctqw_csr_sliced<T, GS>), sgrid, dim3(kBlock), 0, s, g, y, psi, out, c.alpha, c.beta,
+                       kEllSliceEntries);
     return;
   }
   const int64_t threads = static_cast<int64_t>(g.n) * G;
   hipLaunchKernelGGL((k_ctqw_csr<T, G, PROB>), dim3(blocks_for(threads, kBlock)), dim3(kBlock), 0, s, g, y,
-                     psi, out, c.alpha, c.beta, c.a, static_cast<const T *>(c.prev), p, partials);
+                     psi, out, c.alpha, c.beta, p, partials);
 }
 
 template <typename T, bool PROB>
@@ -3377,19 +3177,18 @@ hipError_t launch_ctqw_stage(const GraphView &g, const T *y, const T *psi, T *ou
     }
   } else {
     const dim3 grid(blocks_for(g.n, kBlock));
-    const T *prev = static_cast<const T *>(c.prev);
     switch (g.structure) {
       case kCycle:
         hipLaunchKernelGGL((k_ctqw_struct<T, kCycle, PROB>), grid, dim3(kBlock), 0, s, g, y, psi, out,
-                           c.alpha, c.beta, c.a, prev, p, partials);
+                           c.alpha, c.beta, p, partials);
         break;
       case kTorus:
         hipLaunchKernelGGL((k_ctqw_struct<T, kTorus, PROB>), grid, dim3(kBlock), 0, s, g, y, psi, out,
-                           c.alpha, c.beta, c.a, prev, p, partials);
+                           c.alpha, c.beta, p, partials);
         break;
       case kHypercube:
         hipLaunchKernelGGL((k_ctqw_struct<T, kHypercube, PROB>), grid, dim3(kBlock), 0, s, g, y, psi,
-                           out, c.alpha, c.beta, c.a, prev, p, partials);
+                           out, c.alpha, c.beta, p, partials);
         break;
       case kEll:
         if (!PROB && g.ell_d <= 8 && static_cast<int64_t>(g.n) * static_cast<int64_t>(sizeof(T)) > kEllSliceFrom) {
@@ -3397,10 +3196,10 @@ hipError_t launch_ctqw_stage(const GraphView &g, const T *y, const T *psi, T *ou
           const int groups = static_cast<int>(blocks_for(g.n, kBlock * RPT));
           const dim3 sgrid(std::min(groups, resident_groups(k_ctqw_ell_sliced<T, RPT>)));
           hipLaunchKernelGGL((k_ctqw_ell_sliced<T, RPT>), sgrid, dim3(kBlock), 0, s, g, y, psi, out, c.alpha, c.beta,
-                             c.a, prev, kEllSliceEntries);
+                             kEllSliceEntries);
         } else {
-          hipLaunchKernelGGL((k_ctqw_ell<T, PROB>), grid, dim3(kBlock), 0, s, g, y, psi, out, c.alpha, c.beta, c.a,
-                             prev, p, partials);
+          hipLaunchKernelGGL((k_ctqw_ell<T, PROB>), grid, dim3(kBlock), 0, s, g, y, psi, out, c.alpha, c.beta, p,
+                             partials);
         }
         break;
       default: return hipErrorInvalidValue;
@@ -3684,9 +3483,9 @@ hipError_t coined_prob_csr(bool c128, const GraphView &g, const void *psi, const
 }
 
 hipError_t ctqw_small(bool c128, const GraphView &g, void *psi, const double *alpha, const double *beta,
-                      int K, const SmallSeries &se, int64_t steps, const Readout &ro, hipStream_t s) {
-  return c128 ? launch_ctqw_small<double2>(g, psi, alpha, beta, K, se, steps, ro, s)
-              : launch_ctqw_small<float2>(g, psi, alpha, beta, K, se, steps, ro, s);
+                      int K, int64_t steps, const Readout &ro, hipStream_t s) {
+  return c128 ? launch_ctqw_small<double2>(g, psi, alpha, beta, K, steps, ro, s)
+              : launch_ctqw_small<float2>(g, psi, alpha, beta, K, steps, ro, s);
 }
 
 hipError_t ctqw_stage(bool c128, const GraphView &g, const void *y, const void *psi, void *out, StageCoef c,
@@ -3821,11 +3620,11 @@ hipError_t dense_fill(bool c128, const GraphView &g, double gamma, size_t rows_p
   return hipGetLastError();
 }
 
-hipError_t dense_stage(bool c128, const GraphView &g, const void *y, const void *psi, void *out, const StageCoef &c,
+hipError_t dense_stage(bool c128, const GraphView &g, const void *y, const void *psi, void *out, double c,
                        hipStream_t s) {
   if (g.n == 0) return hipSuccess;
-  if (c128) launch_dense_nt<double>(g, y, psi, out, c.beta, c.a, c.prev, s);
-  else launch_dense_nt<float>(g, y, psi, out, c.beta, c.a, c.prev, s);
+  if (c128) launch_dense_nt<double>(g, y, psi, out, c, s);
+  else launch_dense_nt<float>(g, y, psi, out, c, s);
   return hipGetLastError();
 }
 
@@ -3901,33 +3700,6 @@ hipError_t launch_sweep(bool c128, const GraphView &g, const void *P, const void
                         const double *beta, hipStream_t s) {
   return c128 ? launch_sweep<double2, S>(g, P, Yin, Out, alpha, beta, s)
               : launch_sweep<float2, S>(g, P, Yin, Out, alpha, beta, s);
-}
-
-template <int S>
-hipError_t launch_series(const GraphView &g, const void *P, const void *D1, const void *D2, void *E1, void *E2,
-                         const SweepSeries &c, hipStream_t s) {
-  const StripGrid sg = torus_strips(true, g.dims[0], g.dims[1], S);
-  if (sg.count() == 0 || sg.rows != g.series_rows || !g.series_mark) return hipErrorInvalidValue;
-  const dim3 grid(static_cast<unsigned>((sg.count() + kStripWaves - 1) / kStripWaves)), block(64 * kStripWaves);
-  auto *p = static_cast<const double2 *>(P), *d1 = static_cast<const double2 *>(D1),
-       *d2 = static_cast<const double2 *>(D2);
-  auto *e1 = static_cast<double2 *>(E1), *e2 = static_cast<double2 *>(E2);
-  if (D1)
-    hipLaunchKernelGGL((k_ctqw_torus_series<S, false>), grid, block, 0, s, g, p, d1, d2, e1, e2, c);
-  else
-    hipLaunchKernelGGL((k_ctqw_torus_series<S, true>), grid, block, 0, s, g, p, d1, d2, e1, e2, c);
-  return hipGetLastError();
-}
-
-hipError_t torus_series_stages(const GraphView &g, int S, const void *P, const void *D1, const void *D2, void *E1,
-                               void *E2, const SweepSeries &c, hipStream_t s) {
-  switch (S) {
-    case 5: return launch_series<5>(g, P, D1, D2, E1, E2, c, s);
-    case 4: return launch_series<4>(g, P, D1, D2, E1, E2, c, s);
-    case 3: return launch_series<3>(g, P, D1, D2, E1, E2, c, s);
-    case 2: return launch_series<2>(g, P, D1, D2, E1, E2, c, s);
-    default: return hipErrorInvalidValue;
-  }
 }
 
 StripGrid deep_strips(int l1, int l2, int K, int block_depth, int *depth) {

@@ -9,24 +9,6 @@
 #include "qw_internal.h"
 #include "qwalk.h"
 
-namespace qwk {
-// `steps` time steps of a CTQW as one Chebyshev series of `terms` products
-// with H (qw_series.cpp); terms == 0: none.
-constexpr int kSeriesMaxTerms = 64;
-constexpr int kSeriesMaxSteps = 64;
-constexpr int kSeriesMinSteps = 8;  // below, FP64 rounds more in a series than in Horner stages (1.5-5x)
-constexpr int kSeriesGroup = 16;    // steps per group, halved if they need more terms than that
-struct Series {
-  int64_t steps = 0;
-  int32_t terms = 0;
-  double a[kSeriesMaxTerms + 2] = {};  // a[0 .. terms], zero beyond
-};
-// The series of `steps` steps of the order-K Taylor propagator with
-// rho = dt * ||H||; false if it has no such series of at most
-// kSeriesMaxTerms terms.
-bool chebyshev_series(double rho, int K, int64_t steps, Series *out);
-}  // namespace qwk
-
 struct qw_plan {
   // walk description
   int32_t kind = QW_COINED, coin = QW_GROVER, dtype = QW_C128, layout = QW_LAYOUT_AUTO;
@@ -71,14 +53,8 @@ struct qw_plan {
   int deep_depth = 0;       // two-column complex64 sweep: stages of its deepest launch
   int32_t strip_rows = 0;   // grid CTQW blocked kernel: core rows per strip
   int32_t two_reg = 0;      // one-workgroup coined walk in one wavefront's registers: 0 no, 1 permutes, 2 cycle shifts
-  qwk::Series series;       // CTQW: whole groups of series.steps time steps (terms == 0: one step at a time)
-  bool series_rest = false; // and a rest of at least kSeriesMinSteps steps through a series of its own
-  int32_t series_depth = 1;    // grid CTQW: stages of the series per launch (> 1: blocked)
-  int32_t series_rows = 0;
-  size_t off_smark = 0, off_w3 = 0;
   bool small_regs = false;  // one-workgroup CTQW with its tables in registers (GraphView::order)
   size_t off_order = 0;
-  qwk::SmallSeries small_series() const;
   int32_t block_depth = 1;  // grid CTQW: Horner stages per launch (temporal blocking)
   // out-of-core binding (qw_plan_upload_streamed): the CSR neighbour table stays
   // in caller-pinned host memory.  Ring mode streams it, tile by tile, through
