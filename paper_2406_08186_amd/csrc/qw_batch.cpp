@@ -13,10 +13,10 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <functional>
 #include <map>
 #include <mutex>
 #include <new>
+#include <numeric>
 #include <numeric>
 #include <vector>
 
@@ -191,42 +191,48 @@ std::vector<TileEntry> lay_out(std::vector<Item> &items, bool xcd_aware) {
 // vector (staging, then the sums) and a constant, whatever its rows.  Taken in
 // turn instead, 192 walks kept the fullest workgroup busy 1.25 times as long as
 // the mean one (1.04 so), and a few walks left most units idle.
-std::vector<TileEntry> lay_out_lds(std::vector<Item> &items, bool xcd_aware, int *grid) {
+std::vector<TileEntry> lay_out_lds(const std::vector<Item> &items, bool xcd_aware, int *grid) {
   const int groups = xcd_aware ? 8 : 1, most = kLdsMaxGrid / groups;
-  std::vector<std::vector<const Item *>> of(static_cast<size_t>(groups));
+  std::vector<std::pair<int64_t, const Item *>> walks;  // by what all their tiles cost, then by one's cost
+  for (const Item &it : items) walks.emplace_back(-it.load * static_cast<int64_t>(it.tiles.size()), &it);
+  std::sort(walks.begin(), walks.end());
+  std::vector<std::vector<std::pair<int64_t, const Item *>>> of(static_cast<size_t>(groups));
   std::vector<int64_t> load(static_cast<size_t>(groups), 0);
   std::vector<size_t> count(static_cast<size_t>(groups), 0);
-  std::sort(items.begin(), items.end(), [](const Item &x, const Item &y) {
-    return x.load * static_cast<int64_t>(x.tiles.size()) > y.load * static_cast<int64_t>(y.tiles.size());
-  });
-  for (const Item &it : items) {
+  size_t tiles = 0;
+  for (const auto &[cost, it] : walks) {
     const size_t x = static_cast<size_t>(std::min_element(load.begin(), load.end()) - load.begin());
-    load[x] += it.load * static_cast<int64_t>(it.tiles.size());
-    count[x] += it.tiles.size();
-    of[x].push_back(&it);
+    load[x] -= cost;
+    count[x] += it->tiles.size();
+    tiles += it->tiles.size();
+    of[x].emplace_back(-it->load, it);
   }
   const int per = static_cast<int>(
       std::min<size_t>(static_cast<size_t>(most), std::max<size_t>(1, *std::max_element(count.begin(), count.end()))));
   *grid = std::max(8, groups * per);  // a multiple of 8 with placement
-  std::vector<std::vector<TileEntry>> lists(static_cast<size_t>(*grid));
+  std::vector<std::pair<size_t, const TileEntry *>> placed;  // table entry of each tile
+  placed.reserve(tiles);
+  std::vector<size_t> rounds(static_cast<size_t>(*grid), 0);
+  std::vector<int64_t> heap(static_cast<size_t>(per));  // 256 * load + workgroup of the group, the least first
   for (int x = 0; x < groups; ++x) {
-    std::sort(of[x].begin(), of[x].end(), [](const Item *p, const Item *q) { return p->load > q->load; });
-    std::vector<std::pair<int64_t, int>> heap;  // (load, workgroup), the least first
-    for (int j = 0; j < per; ++j) heap.emplace_back(0, groups * j + x);
-    const auto more = std::greater<std::pair<int64_t, int>>();
-    for (const Item *it : of[x])
+    std::sort(of[x].begin(), of[x].end());
+    std::iota(heap.begin(), heap.end(), int64_t{0});
+    for (const auto &[cost, it] : of[x])
       for (const TileEntry &t : it->tiles) {
-        std::pop_heap(heap.begin(), heap.end(), more);
-        lists[static_cast<size_t>(heap.back().second)].push_back(t);
-        heap.back().first += it->load;
-        std::push_heap(heap.begin(), heap.end(), more);
+        const size_t b = static_cast<size_t>(groups * (heap[0] & 255) + x);
+        placed.emplace_back(rounds[b]++ * rounds.size() + b, &t);
+        const int64_t key = heap[0] - 256 * cost;
+        size_t h = 0;  // the least workgroup's load grew: sift it down
+        for (size_t c; (c = 2 * h + 1) < heap.size(); h = c) {
+          c += c + 1 < heap.size() && heap[c + 1] < heap[c];
+          if (key <= heap[c]) break;
+          heap[h] = heap[c];
+        }
+        heap[h] = key;
       }
   }
-  size_t rounds = 0;
-  for (const auto &l : lists) rounds = std::max(rounds, l.size());
-  std::vector<TileEntry> table(rounds * lists.size(), TileEntry{-1, 0, 0, 0});
-  for (size_t b = 0; b < lists.size(); ++b)
-    for (size_t r = 0; r < lists[b].size(); ++r) table[r * lists.size() + b] = lists[b][r];
+  std::vector<TileEntry> table(*std::max_element(rounds.begin(), rounds.end()) * rounds.size(), TileEntry{-1, 0, 0, 0});
+  for (const auto &[at, t] : placed) table[at] = *t;
   return table;
 }
 
