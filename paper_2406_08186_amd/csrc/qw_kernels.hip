@@ -2551,38 +2551,32 @@ __device__ __forceinline__ void ell_lds_tile(T *xs, const WalkSlot &w, const Til
           if (h + j < D) acc[i] = add(acc[i], cvt(xv[j]));
       }
   }
-  // The rows' own values, in two halves where next to the sums they would not fit
-  // the registers all at once: spilling 24 of them made 190 complex128 walks of up
-  // to 9000 vertices 27 us per launch instead of 20.
-  constexpr int PER = RPL <= (sizeof(T) == 16 ? 7 : 10) ? RPL : (RPL + 1) / 2;
+  // The rows' own values, all in flight at once.  A marked vertex, rare, reads its
+  // input on its own: with that vector's RPL values beside these and the sums the
+  // registers spill (24 of them in complex128: 190 walks of up to 9000 vertices
+  // 27 us per launch instead of 20).
+  T pv[RPL];
+  uint32_t mw[RPL];
 #pragma unroll
-  for (int i0 = 0; i0 < RPL; i0 += PER) {
-    T pv[PER], yv[PER];
-    uint32_t mw[PER];
+  for (int i = 0; i < RPL; ++i) {
+    const int r = te.begin + tid + i * NT;
+    const int rc = r < te.end ? r : te.end - 1;
+    pv[i] = gld(psi, rc);
+    mw[i] = bits[rc >> 5];
+  }
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      if (i0 + i >= RPL) break;
-      const int r = te.begin + tid + (i0 + i) * NT;
-      const int rc = r < te.end ? r : te.end - 1;
-      pv[i] = gld(psi, rc);
-      yv[i] = gld(yin, rc);
-      mw[i] = bits[rc >> 5];
+  for (int i = 0; i < RPL; ++i) {
+    const int r = te.begin + tid + i * NT;
+    const int rc = r < te.end ? r : te.end - 1;
+    const bool mk = (mw[i] >> (rc & 31)) & 1u;
+    double2 y_self = make_double2(0.0, 0.0);
+    if (mk) y_self = cvt(gld(yin, rc));
+    const T o = pack<T>(horner_out(cvt(pv[i]), acc[i], y_self, mk, alpha, beta));
+    if (r < te.end) {
+      gst(yout, r, o);
+      if (k == 1 && mk && w.hist) atomicAdd(&w.hist[step], abs2(cvt(o)));
     }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      if (i0 + i >= RPL) break;
-      const int r = te.begin + tid + (i0 + i) * NT;
-      const int rc = r < te.end ? r : te.end - 1;
-      const bool mk = (mw[i] >> (rc & 31)) & 1u;
-      const double2 y_self = mk ? cvt(yv[i]) : make_double2(0.0, 0.0);
-      const T o = pack<T>(horner_out(cvt(pv[i]), acc[i0 + i], y_self, mk, alpha, beta));
-      if (r < te.end) {
-        gst(yout, r, o);
-        if (k == 1 && mk && w.hist) atomicAdd(&w.hist[step], abs2(cvt(o)));
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
   }
 }
 
