@@ -99,6 +99,18 @@ constexpr int kSweepMinRowsPerStage = 4;
 // best throughout, and one wavefront per SIMD (two: 5-30% slower).
 constexpr int kCoinedSteps64 = 5, kCoinedSteps128 = 6, kCoinedMatrixSteps128 = 4;
 constexpr int kCoinedAhead = 3;
+// Grids below these cells take the matrix coin one step per launch: a strip has
+// twice its halo's rows at least, and on a small grid the chain of that many rows
+// of FP64 products in each of few wavefronts takes longer than the launches it
+// saves.  us for 50 steps one by one and swept:
+//   cells              22500  65536  90000  122500  160000  202500  250000  302500
+//   Fourier c64, one     157    165    178     188     211     235     245     271
+//                swept   217    220    223     225     229     233     237     240
+//   Fourier c128, one    170    191    208     231     256
+//                 swept  198    204    211     216     219
+// and on narrow ones, 64 x 4000 complex64 245 and 254, 64 x 2000 complex128 234
+// and 239, 64 x 2400 220 and 208.
+constexpr int64_t kCoinedMatrixFrom64 = 300000, kCoinedMatrixFrom128 = 150000;
 
 // Square-lattice sweep: steps per launch by type, and row pairs read ahead.
 // Measured, one wavefront per SIMD (us for 60 steps of 768 x 1100 complex128 and

@@ -3403,6 +3403,7 @@ int coined_sweep_steps(bool c128, const GraphView &g, int64_t left) {
   if (g.structure != kTorus) return 1;
   const int most = !c128 ? kCoinedSteps64 : g.coin ? kCoinedMatrixSteps128 : kCoinedSteps128;
   const int S = static_cast<int>(std::min<int64_t>(left, most));
+  if (g.coin && static_cast<int64_t>(g.dims[0]) * g.dims[1] < (c128 ? kCoinedMatrixFrom128 : kCoinedMatrixFrom64)) return 1;
   return S >= 2 && coined_strip_rows(g.dims[0], g.dims[1], S) > 0 ? S : 1;
 }
 
