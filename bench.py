@@ -157,11 +157,11 @@ def timed_passes(plan, psi, steps, warmup, spp):
 
 def grid_launches(plan, cells):
     """Launches of one complex64 time step on the grid: K / block_depth, or, on
-    grids of at least 2^21 cells, those of the two-column sweep's ten stages
-    (its launches on grids of up to 700000 cells are of K / 4 stages, as many).
+    grids of at least 3000000 cells, those of the two-column sweep's ten stages
+    (its launches on small grids are of K / 4 stages, as many).
     """
     depth = max(1, int(plan.info.block_depth))
-    return -(-K_ORDER // 10) if depth > 1 and cells >= 1 << 21 else K_ORDER // depth
+    return -(-K_ORDER // 10) if depth > 1 and cells >= 3_000_000 else K_ORDER // depth
 
 
 def stage_launch_ms(per_pass_ms, steps_per_pass, launches_per_step):

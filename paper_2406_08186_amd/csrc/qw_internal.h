@@ -142,11 +142,27 @@ constexpr int kStagAhead64 = 2, kStagAhead128 = 1;
 //   2048^2       K 20          78.8    82.1   81.1   76.2   76.5   66.8
 //   2048^2       K 20 marked   89.4     116   97.3    108   98.1   78.9
 //   3000^2       K 20           153     173    154    145    136    104
+// and on either side of the lines below, the marks again costing most:
+//                                   one col.  6 (1)  10 (2)
+//   700^2         K 9 marked          18.1    16.7   15.7
+//   800^2         K 9 marked          15.8    17.1   16.5
+//   5400 x 128    K 24 marked         43.2    56.7   45.7
+//   830^2         K 24 marked         49.8    48.0   41.0
+//   900^2         K 24 marked         43.1    50.4   43.5
+//   1200^2        K 20                39.2    41.7   42.5
+//   1448^2        K 14 marked         67.9    53.1   36.1
+//   700 x 3010    K 20 marked         51.1           54.0
+//   16500 x 128   K 20                55.0           57.9
+//   1800 x 1801   K 20 marked         69.6    99.6   66.8
 // Small grids are bound by launches and by the chain of one wavefront's stages,
-// large ones by memory, which deep launches pass less often; between them
-// neither leads and one column stays, unless K only divides by 2 or 3.
+// large ones by memory, which deep launches pass less often.  Small is measured
+// in the cells that the strips cover (of 128 columns two strips cover 232); the
+// lines with Few are for K that only divides by 2 or 3, whose other choice is
+// shallower launches.  Between the lines those K take 6 (2), and the others one
+// column, as they do on large grids of which the strips cover an eighth twice.
 constexpr int kDeepStages = 10, kDeepStagesSmall = 6, kDeepUnroll = 3;
-constexpr int64_t kDeepSmall = 700000, kDeepLarge = int64_t{1} << 21;
+constexpr int64_t kDeepSmall = 780000, kDeepSmallFew = 600000;
+constexpr int64_t kDeepLarge = 3000000, kDeepLargeFew = int64_t{1} << 21;
 
 // Strip decomposition of an l1 x l2 grid for S stages per launch.
 struct StripGrid {

@@ -3710,8 +3710,7 @@ hipError_t launch_sweep(bool c128, const GraphView &g, const void *P, const void
 StripGrid deep_strips(int l1, int l2, int K, int block_depth, int *depth) {
   StripGrid sg;
   const int64_t cells = static_cast<int64_t>(l1) * l2;
-  const bool large = cells >= kDeepLarge, small = cells <= kDeepSmall;
-  if (!large && !small && block_depth > 3) return sg;
+  const bool large = cells >= (block_depth > 3 ? kDeepLarge : kDeepLargeFew);
   const int most = large ? kDeepStages : kDeepStagesSmall;
   const int launches = (K + most - 1) / most, S = (K + launches - 1) / launches;
   if (l2 < 128 || S < 2) return sg;
@@ -3719,6 +3718,10 @@ StripGrid deep_strips(int l1, int l2, int K, int block_depth, int *depth) {
   sg.halo = S + (S & 1);
   sg.core = 128 - 2 * sg.halo - 2 * (l2 & 1);
   sg.tiles_c = (l2 + sg.core - 1) / sg.core;
+  const int64_t covered = static_cast<int64_t>(sg.tiles_c) * sg.core * l1;  // the last strip overlaps
+  const bool small = !large && covered <= (block_depth > 3 ? kDeepSmall : kDeepSmallFew);
+  const bool narrow = 8 * covered > 9 * cells;
+  if (!small && (!large || narrow) && block_depth > 3) return StripGrid{};
   const int want = std::max(1, (small ? 1 : 2) * kSimds / sg.tiles_c);
   sg.rows = std::min((l1 + want - 1) / want, l1 - 2 * sg.halo);
   if (sg.rows < 1) return StripGrid{};

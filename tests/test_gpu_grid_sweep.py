@@ -46,9 +46,10 @@ def _check(l1, l2, K, steps):
 @pytest.mark.parametrize("l1,l2,K,columns", [
     (300, 300, 9, [*range(14), *range(112, 131)]), (300, 300, 14, [*range(14), *range(112, 131)]),
     (40, 229, 9, [*range(14), *range(110, 131)]), (61, 232, 14, [*range(4, 12), *range(116, 128)]),
-    (300, 131, 14, [*range(4, 12), *range(116, 128)]), (1449, 1449, 25, [12, 13, 118, 119])])
+    (300, 131, 14, [*range(4, 12), *range(116, 128)]), (1449, 1449, 25, [12, 13, 118, 119]),
+    (1449, 1449, 26, [12, 13, 118, 119]), (1740, 1740, 25, [10, 11, 118, 119])])
 def test_marks_around_strip_edges(l1, l2, K, columns):
-    """A time step of launches of unequal depth (5, 4; 5, 5, 4; 9, 8, 8): one mark at a time at
+    """A time step of launches of unequal depth (5, 4; 5, 5, 4; 9, 8, 8; 9, 9, 8): one mark at a time at
     every column around the ends of a strip and of its halo.  A mark term of the last launch
     lost in one strip is 2.7e-4 of an amplitude or more at this step length; FP32 rounds each of
     the last stages' values once, 6e-8 each."""
