@@ -2670,32 +2670,6 @@ template <> struct Mfma<float> {
   }
 };
 
-// A wavefront's 16 x 16 NT results z(t, r): y_out = psi + c (b - i a), or the
-// raw products where k is split over workgroups.
-template <typename R, int NT, typename Z>
-__device__ __forceinline__ void dense_store(Z z_of, int row0, int col0, int l, int n, int c2, int split, const R *psi,
-                                            R *out, double c, double *partial) {
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const double z = z_of(t, r);
-      const double zp = __shfl_xor(z, 1, 64);
-      const int row = row0 + Mfma<R>::row(l, r);
-      const int col = col0 + t * 16 + (l & 15);
-      if (partial) {  // split k: hand the raw product to the reduction kernel
-        if (row < n && col < c2) partial[(static_cast<int64_t>(split) * n + row) * c2 + col] = z;
-        continue;
-      }
-      if (row < n && col < c2) {
-        const int64_t idx = static_cast<int64_t>(row) * c2 + col;
-        const double ps = static_cast<double>(psi[idx]);
-        out[idx] = static_cast<R>((col & 1) ? ps - c * zp : ps + c * zp);
-      }
-    }
-  }
-}
-
 template <typename R, int NT, int KC>
 __global__ __launch_bounds__(256) void k_dense_stage(const R *__restrict__ H, int ld, int n, int c2,
                                                      const R *__restrict__ yin, const R *psi, R *out,
@@ -2775,8 +2749,25 @@ __global__ __launch_bounds__(256) void k_dense_stage(const R *__restrict__ H, in
       }
     }
   }
-  dense_store<R, NT>([&](int t, int r) { return wide[t][r] + static_cast<double>(acc[t][r]); }, row0 + wave * 16, 0, l,
-                     n, c2, split, psi, out, c, partial);
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const double z = wide[t][r] + static_cast<double>(acc[t][r]);
+      const double zp = __shfl_xor(z, 1, 64);
+      const int row = row0 + wave * 16 + M::row(l, r);
+      const int col = t * 16 + (l & 15);
+      if (partial) {  // split k: hand the raw product to the reduction kernel
+        if (row < n && col < c2) partial[(static_cast<int64_t>(split) * n + row) * c2 + col] = z;
+        continue;
+      }
+      if (row < n && col < c2) {
+        const int64_t idx = static_cast<int64_t>(row) * c2 + col;
+        const double ps = static_cast<double>(psi[idx]);
+        out[idx] = static_cast<R>((col & 1) ? ps - c * zp : ps + c * zp);
+      }
+    }
+  }
 }
 
 // FP64 H times 33 or more real columns: bound by the FP64 matrix rate (78.6
@@ -2879,8 +2870,24 @@ __global__ __launch_bounds__(512) void k_dense_stage_f64(const double *__restric
     chunk(std::integral_constant<int, 0>{}, k0);
     if (k0 + KC < kend) chunk(std::integral_constant<int, 1>{}, k0 + KC);
   }
-  dense_store<double, NW>([&](int t, int r) { return acc[t][r]; }, row0, half * NW * 16, l, n, c2, split, psi, out,
-                          c, partial);
+#pragma unroll
+  for (int t = 0; t < NW; ++t) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const double z = acc[t][r];
+      const double zp = __shfl_xor(z, 1, 64);
+      const int row = row0 + M::row(l, r);
+      const int col = (half * NW + t) * 16 + (l & 15);
+      if (partial) {
+        if (row < n && col < c2) partial[(static_cast<int64_t>(split) * n + row) * c2 + col] = z;
+        continue;
+      }
+      if (row < n && col < c2) {
+        const int64_t idx = static_cast<int64_t>(row) * c2 + col;
+        out[idx] = (col & 1) ? psi[idx] - c * zp : psi[idx] + c * zp;
+      }
+    }
+  }
 }
 
 // One walk with FP32 H: H y is bound by streaming H once, so it runs on the
