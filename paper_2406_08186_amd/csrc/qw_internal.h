@@ -63,6 +63,29 @@ constexpr int small_row(bool c128, int per_thread, int i) {
   if (per_thread == 2) return c128 ? (i == 0 ? 16 : 8) : (i == 0 ? 24 : 16);
   return c128 ? 8 : (i == 0 ? 16 : 8);
 }
+// Arcs lane, lane + G, ... of the row [lo, hi), M at a time.  Plans have up to
+// 2^31 - 1 arcs, so an index past hi is never formed.
+template <int G, int M> struct LaneArcs {
+  int hi, left;
+  constexpr LaneArcs(int lo, int hi_, int lane) : hi(hi_), left(hi_ - lo - lane) {}
+  constexpr bool more() const { return left > 0; }
+  constexpr bool has(int m) const { return m * G < left; }
+  constexpr int at(int m) const { return hi - left + m * G; }
+  constexpr void next() { left -= M * G; }
+};
+// The lane's arcs of a row, counted as the kernels walk them (an overflow in a
+// constant expression does not compile).
+template <int G, int M> constexpr int lane_arcs(int lo, int hi, int lane) {
+  int n = 0;
+  for (LaneArcs<G, M> a(lo, hi, lane); a.more(); a.next())
+    for (int m = 0; m < M; ++m)
+      if (a.has(m) && a.at(m) == lo + lane + n * G) ++n;
+  return n;
+}
+static_assert(lane_arcs<2, 8>(0, 35, 1) == 17 && lane_arcs<64, 8>(7, 8, 1) == 0 && lane_arcs<4, 8>(9, 9, 0) == 0);
+static_assert(lane_arcs<2, 8>(0x7fffffff - 21, 0x7fffffff, 0) == 11 && lane_arcs<64, 8>(0x7fffffff - 600, 0x7fffffff, 63) == 9 &&
+              lane_arcs<64, 8>(0x7fffffff - 1, 0x7fffffff, 63) == 0);
+
 // Largest hypercube dimension the structured kernels handle.
 constexpr int kMaxHypercubeDim = 30;
 

@@ -498,8 +498,9 @@ __global__ __launch_bounds__(kCoinedTileThreads) void k_coined_tile(GraphView g,
     if (!mk) {
       double sx = 0.0, sy = 0.0;
       // summed by the first kTileThreads threads, whatever the block
-      for (int i = ab + threadIdx.x; i < ae && threadIdx.x < kTileThreads; i += kTileThreads) {
-        double2 x = ld(in, GATHER ? g.rev[i] : i);
+      // (unsigned: ab + na may near 2^31)
+      for (unsigned i = ab + threadIdx.x; i < static_cast<unsigned>(ae) && threadIdx.x < kTileThreads; i += kTileThreads) {
+        double2 x = ld(in, GATHER ? g.rev[i] : static_cast<int64_t>(i));
         const double wt = g.sqrtp ? g.sqrtp[i] : 1.0;
         sx += wt * x.x;
         sy += wt * x.y;
@@ -508,11 +509,11 @@ __global__ __launch_bounds__(kCoinedTileThreads) void k_coined_tile(GraphView g,
       sy = block_sum(sy, red);
       m = g.sqrtp ? make_double2(sx, sy) : grover_mean(make_double2(sx, sy), na);
     }
-    for (int i = ab + threadIdx.x; i < ae; i += blockDim.x) {
-      double2 x = ld(in, GATHER ? g.rev[i] : i);
+    for (unsigned i = ab + threadIdx.x; i < static_cast<unsigned>(ae); i += kCoinedTileThreads) {
+      double2 x = ld(in, GATHER ? g.rev[i] : static_cast<int64_t>(i));
       double2 phi = mk ? scale(x, -1.0)
                        : (g.sqrtp ? sub(scale(m, 2.0 * g.sqrtp[i]), x) : sub(add(m, m), x));
-      st(out, SCATTER ? g.rev[i] : i, phi);
+      st(out, SCATTER ? g.rev[i] : static_cast<int64_t>(i), phi);
     }
   }
 }
@@ -951,18 +952,18 @@ __global__ __launch_bounds__(kBlock) void k_ctqw_csr(GraphView g, const T *__res
       // eight of the lane's arcs at a time: their indices and then their
       // gathers are all issued before the first add, so a row of up to 8 G
       // arcs pays two memory latencies instead of two per arc
-      for (int a0 = lo + lane; a0 < hi; a0 += 8 * G) {
+      for (LaneArcs<G, 8> a(lo, hi, lane); a.more(); a.next()) {
         int c[8];
 #pragma unroll
         for (int m = 0; m < 8; ++m)
-          if (a0 + m * G < hi) c[m] = g.col[a0 + m * G];
+          if (a.has(m)) c[m] = g.col[a.at(m)];
         T x[8];
 #pragma unroll
         for (int m = 0; m < 8; ++m)
-          if (a0 + m * G < hi) x[m] = y[c[m]];
+          if (a.has(m)) x[m] = y[c[m]];
 #pragma unroll
         for (int m = 0; m < 8; ++m)
-          if (a0 + m * G < hi) {
+          if (a.has(m)) {
             sx += cvt(x[m]).x;
             sy += cvt(x[m]).y;
           }
