@@ -63,6 +63,14 @@ constexpr int small_row(bool c128, int per_thread, int i) {
   if (per_thread == 2) return c128 ? (i == 0 ? 16 : 8) : (i == 0 ? 24 : 16);
   return c128 ? 8 : (i == 0 ? 16 : 8);
 }
+// CSR stages with 16 lanes a row and more (rows of 3 to 6 arcs a lane) have eight of
+// a lane's arcs in flight up to this many threads.  Few wavefronts wait for
+// memory, and the loads in flight serve them; many hide it, and the tests for
+// arcs that are not there cost more.  us for two steps, in flight and one by one:
+// 3000 vertices of mean degree 80 (48000 threads) 106 and 135, of 250 (192000)
+// 125 and 145; 20000 of 80 (320000) 236 and 217, of 150 (640000) 376 and 331.
+constexpr int kCsrBatchedThreads = 1 << 18;
+
 // Arcs lane, lane + G, ... of the row [lo, hi), M at a time.  Plans have up to
 // 2^31 - 1 arcs, so an index past hi is never formed.
 template <int G, int M> struct LaneArcs {

@@ -948,7 +948,7 @@ __global__ __launch_bounds__(kBlock) void k_ctqw_csr(GraphView g, const T *__res
       const double2 t = gather_sum(y, g.col, lo, hi);
       sx = t.x;
       sy = t.y;
-    } else {
+    } else if (G <= 8 || g.n <= kCsrBatchedThreads / G) {
       // eight of the lane's arcs at a time: their indices and then their
       // gathers are all issued before the first add, so a row of up to 8 G
       // arcs pays two memory latencies instead of two per arc
@@ -967,6 +967,12 @@ __global__ __launch_bounds__(kBlock) void k_ctqw_csr(GraphView g, const T *__res
             sx += cvt(x[m]).x;
             sy += cvt(x[m]).y;
           }
+      }
+    } else {
+      for (LaneArcs<G, 1> a(lo, hi, lane); a.more(); a.next()) {
+        const double2 x = ld(y, g.col[a.at(0)]);
+        sx += x.x;
+        sy += x.y;
       }
     }
   }
