@@ -156,12 +156,13 @@ def timed_passes(plan, psi, steps, warmup, spp):
 
 
 def grid_launches(plan, cells):
-    """Launches of one complex64 time step on the grid: K / block_depth, or, on
-    grids of at least 3000000 cells, those of the two-column sweep's ten stages
-    (its launches on small grids are of K / 4 stages, as many).
+    """Launches of one time step on the grid: K / block_depth, or, for complex64
+    on grids of at least 3000000 cells, those of the two-column sweep's ten
+    stages (its launches on small grids are of K / 4 stages, as many).
     """
     depth = max(1, int(plan.info.block_depth))
-    return -(-K_ORDER // 10) if depth > 1 and cells >= 3_000_000 else K_ORDER // depth
+    deep = plan.dtype == "c64" and depth > 1 and cells >= 3_000_000
+    return -(-K_ORDER // 10) if deep else K_ORDER // depth
 
 
 def stage_launch_ms(per_pass_ms, steps_per_pass, launches_per_step):
@@ -272,17 +273,16 @@ def run_grid(args):
         wall, per, (p, norm, _) = timed_passes(pl, psi, args.steps, args.warmup, spp)
         total_steps = (args.steps + args.warmup) * spp
         state = psi.cpu().numpy().astype(np.complex128)
-        # complex128 runs groups of steps as one series: no launches of a step to time
-        lps = grid_launches(pl, g.n) if dtype == "c64" else None
-        launch_ms = stage_launch_ms(per, spp, lps) if lps else None
+        lps = grid_launches(pl, g.n)
+        launch_ms = stage_launch_ms(per, spp, lps)
         es = 8 if dtype == "c64" else 16
         # algorithmic bytes of one row-stage of the matrix-free grid stencil: read y,
         # read psi, write y' (3 S); one launch runs `depth` stages of every row
-        depth = K_ORDER // lps if lps else int(pl.info.block_depth)
+        depth = K_ORDER // lps
         # bytes a launch must move: read y_in and psi, write y_out (3 S per row);
         # the first launch of a time step reads psi as y_in (2 S).  Averaged over
         # the K / depth launches of a step.
-        bytes_per_launch = (3 * lps - 1) / lps * es * g.n if lps else None
+        bytes_per_launch = (3 * lps - 1) / lps * es * g.n
         stage_model_bytes = depth * 3 * es * g.n
         res[dtype] = dict(plan=pl, wall=wall, per=per, norm=float(norm), state=state,
                           total_steps=total_steps, launch_ms=launch_ms,
@@ -333,6 +333,9 @@ def run_grid(args):
         "p50_ms": pct(r64["per"], 50), "p99_ms": pct(r64["per"], 99),
         "c128": {"value": rate(r128), "ms_per_step": r128["wall"] / args.steps * 1e3,
                  "p50_ms": pct(r128["per"], 50), "p99_ms": pct(r128["per"], 99),
+                 "stage_launch_ms": r128["launch_ms"],
+                 "launch_gbs": r128["bytes_per_launch"] / (r128["launch_ms"] * 1e-3) / 1e9,
+                 "launch_frac": r128["bytes_per_launch"] / (r128["launch_ms"] * 1e-3) / 1e9 / HBM_PEAK_GBS,
                  "l2_vs_closed_form": l2_128},
         "speedup_c64_vs_c128": rate(r64) / rate(r128),
         "l2_c64_vs_closed_form": l2_64,
@@ -1126,12 +1129,11 @@ def run_sparse(args):
             ms = a.elapsed_time(b)
             es = 8 if dtype == "c64" else 16
             per_launch = (4 * g.n if pl.structure == "general" else 0) + 4 * g.n_arcs + 3 * es * g.n
-            res[dtype] = {"path": pl.structure, "K": K, "arc_steps_per_s": g.n_arcs * steps / (ms * 1e-3)}
-            if dtype == "c64":  # K stages per step; complex128 runs groups of steps as one series
-                launch_ms = ms / (steps * K)
-                gbs = per_launch / (launch_ms * 1e-3) / 1e9
-                res[dtype].update({"arc_spmv_per_s": g.n_arcs * steps * K / (ms * 1e-3), "stage_us": launch_ms * 1e3,
-                                   "bytes_per_stage": per_launch, "achieved_gbs": gbs, "frac": gbs / HBM_PEAK_GBS})
+            launch_ms = ms / (steps * K)
+            gbs = per_launch / (launch_ms * 1e-3) / 1e9
+            res[dtype] = {"path": pl.structure, "K": K, "arc_steps_per_s": g.n_arcs * steps / (ms * 1e-3),
+                          "arc_spmv_per_s": g.n_arcs * steps * K / (ms * 1e-3), "stage_us": launch_ms * 1e3,
+                          "bytes_per_stage": per_launch, "achieved_gbs": gbs, "frac": gbs / HBM_PEAK_GBS}
             del psi
             pl.close()
         out[name] = res

@@ -858,7 +858,7 @@ int evolve_coined(const qw_plan *p, void *psi, unsigned char *work, int64_t step
       std::swap(cur, oth);
     }
     if (cur != psi) {
-      if (hold) QW_TRY(coined_shift(c128, g, cur, psi, s), "coined shift kernel");
+      if (hold) QW_TRY(coined_shift(g, cur, psi, s), "coined shift kernel");
       else QW_TRY(copy_state(c128, p->n_arcs, cur, psi, s), "state copy kernel");
     }
     return readout_only(p, psi, ro, s);

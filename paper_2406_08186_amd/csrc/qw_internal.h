@@ -328,10 +328,10 @@ size_t coined_small_lds(bool c128, int n, int n_arcs);
 
 // One step in CSR arc order.  gather: `in` holds the previous step's coin output,
 // still to be shifted; scatter: shift on the way out (else `out` needs the next
-// step's gather, or coined_shift).
+// step's gather, or coined_shift).  complex128 steps scatter.
 hipError_t coined_tile_step(bool c128, const GraphView &g, const void *in, void *out, int hadamard, bool gather,
                             bool scatter, hipStream_t s);
-hipError_t coined_shift(bool c128, const GraphView &g, const void *phi, void *out, hipStream_t s);
+hipError_t coined_shift(const GraphView &g, const void *phi, void *out, hipStream_t s);
 hipError_t coined_struct_step(bool c128, const GraphView &g, const void *in, void *out,
                               int hadamard, hipStream_t s);
 // Grid walks: how many of `left` steps the next launch takes (1: one step by

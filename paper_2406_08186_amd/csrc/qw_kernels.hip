@@ -519,8 +519,7 @@ __global__ __launch_bounds__(kCoinedTileThreads) void k_coined_tile(GraphView g,
 }
 
 // out[a] = phi[rev[a]]: the shift that the last of an odd number of steps left out.
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_coined_shift(const T *__restrict__ phi, T *__restrict__ out,
+__global__ __launch_bounds__(kBlock) void k_coined_shift(const float2 *__restrict__ phi, float2 *__restrict__ out,
                                                          const int32_t *__restrict__ rev, int na) {
   const int i = blockIdx.x * kBlock + threadIdx.x;
   if (i < na) out[i] = phi[rev[i]];
@@ -3370,39 +3369,32 @@ hipError_t coined_small(bool c128, const GraphView &g, void *psi, int hadamard, 
               : launch_coined_small<float2>(g, psi, hadamard, steps, ro, s);
 }
 
-template <typename T>
-hipError_t launch_coined_tile(const GraphView &g, const void *in, void *out, int hadamard, bool gather, bool scatter,
-                              hipStream_t s) {
-  const T *x = static_cast<const T *>(in);
-  T *y = static_cast<T *>(out);
-  const dim3 grid(g.n_tiles), block(kCoinedTileThreads);
-  if (scatter && !gather)
-    hipLaunchKernelGGL((k_coined_tile<T, false, true>), grid, block, 0, s, g, x, y, hadamard);
-  else if (!gather)
-    hipLaunchKernelGGL((k_coined_tile<T, false, false>), grid, block, 0, s, g, x, y, hadamard);
-  else if (scatter)
-    hipLaunchKernelGGL((k_coined_tile<T, true, true>), grid, block, 0, s, g, x, y, hadamard);
-  else
-    hipLaunchKernelGGL((k_coined_tile<T, true, false>), grid, block, 0, s, g, x, y, hadamard);
-  return hipGetLastError();
+template <typename T, bool GATHER, bool SCATTER>
+void launch_coined_tile(const GraphView &g, const void *in, void *out, int hadamard, hipStream_t s) {
+  hipLaunchKernelGGL((k_coined_tile<T, GATHER, SCATTER>), dim3(g.n_tiles), dim3(kCoinedTileThreads), 0, s, g,
+                     static_cast<const T *>(in), static_cast<T *>(out), hadamard);
 }
 
 hipError_t coined_tile_step(bool c128, const GraphView &g, const void *in, void *out, int hadamard, bool gather,
                             bool scatter, hipStream_t s) {
   if (g.n_tiles == 0) return hipSuccess;
-  return c128 ? launch_coined_tile<double2>(g, in, out, hadamard, gather, scatter, s)
-              : launch_coined_tile<float2>(g, in, out, hadamard, gather, scatter, s);
+  if (c128) {
+    if (gather || !scatter) return hipErrorInvalidValue;
+    launch_coined_tile<double2, false, true>(g, in, out, hadamard, s);
+  } else if (gather) {
+    scatter ? launch_coined_tile<float2, true, true>(g, in, out, hadamard, s)
+            : launch_coined_tile<float2, true, false>(g, in, out, hadamard, s);
+  } else {  // the first step, which writes to the workspace
+    if (scatter) return hipErrorInvalidValue;
+    launch_coined_tile<float2, false, false>(g, in, out, hadamard, s);
+  }
+  return hipGetLastError();
 }
 
-hipError_t coined_shift(bool c128, const GraphView &g, const void *phi, void *out, hipStream_t s) {
+hipError_t coined_shift(const GraphView &g, const void *phi, void *out, hipStream_t s) {
   if (g.n_arcs == 0) return hipSuccess;
-  const dim3 grid(blocks_for(g.n_arcs, kBlock));
-  if (c128)
-    hipLaunchKernelGGL(k_coined_shift<double2>, grid, dim3(kBlock), 0, s, static_cast<const double2 *>(phi),
-                       static_cast<double2 *>(out), g.rev, g.n_arcs);
-  else
-    hipLaunchKernelGGL(k_coined_shift<float2>, grid, dim3(kBlock), 0, s, static_cast<const float2 *>(phi),
-                       static_cast<float2 *>(out), g.rev, g.n_arcs);
+  hipLaunchKernelGGL(k_coined_shift, dim3(blocks_for(g.n_arcs, kBlock)), dim3(kBlock), 0, s,
+                     static_cast<const float2 *>(phi), static_cast<float2 *>(out), g.rev, g.n_arcs);
   return hipGetLastError();
 }
 
