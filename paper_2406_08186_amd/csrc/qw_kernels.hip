@@ -2785,7 +2785,9 @@ __global__ __launch_bounds__(256) void k_dense_stage(const R *__restrict__ H, in
 // state block goes through LDS, in chunks of KC rows whose stride of NC + 4 puts
 // the rows of neighbouring groups on different banks.  Eight wavefronts, two
 // per SIMD; a chunk's state rows are loaded while the chunk before multiplies,
-// H's two chunks ahead, an MFMA's state values one MFMA step ahead.  Per stage,
+// H's two chunks ahead, an MFMA's state values one MFMA step ahead.  Even and odd
+// chunks have sums of their own: k ranges are up to twice as long as the kernel's
+// below, and one sum over them erred 4-7% more at N = 2500 (two: 1-7% less).  Per stage,
 // with the reduction, against the LDS-staged kernel below: N = 2500, 32 walks
 // 29.4 us (37.7 before), N = 5000, 32 walks 83 (94), N = 4000, 128 walks 154
 // (235); 16 walks 58 (53), so those stay there.
@@ -2804,9 +2806,9 @@ __global__ __launch_bounds__(512) void k_dense_stage_f64(const double *__restric
   const int split = blockIdx.x / rblocks;
   const int row0 = (blockIdx.x - split * rblocks) * kDenseRows + wave * 16;
   const int kbeg = split * ksplit, kend = min(n, kbeg + ksplit);
-  typename M::acc acc[NW];
+  typename M::acc acc[2][NW];  // the even and the odd chunks' sums
 #pragma unroll
-  for (int t = 0; t < NW; ++t) acc[t] = M::zero();
+  for (int t = 0; t < NW; ++t) acc[0][t] = acc[1][t] = M::zero();
   // rows and columns of H are padded with zeros to kDenseRows and kDenseK, and k ranges are whole kDenseK
   const double *hrow = H + static_cast<int64_t>(row0 + (l & 15)) * ld + 4 * q;
   double2 hn[2][SUB][2], xn[XP];
@@ -2858,7 +2860,7 @@ __global__ __launch_bounds__(512) void k_dense_stage_f64(const double *__restric
       const double2 hp = hn[b][m >> 2][(m >> 1) & 1];
       const double h = (m & 1) ? hp.y : hp.x;
 #pragma unroll
-      for (int t = 0; t < NW; ++t) acc[t] = M::mma(h, y[m & 1][t], acc[t]);
+      for (int t = 0; t < NW; ++t) acc[b][t] = M::mma(h, y[m & 1][t], acc[b][t]);
       if (m + 1 < 4 * SUB) __builtin_amdgcn_sched_group_barrier(0x100, (NW + 1) / 2, 0);  // LDS reads of the next step,
       __builtin_amdgcn_sched_group_barrier(0x008, NW, 0);            // then this step's MFMAs
     }
@@ -2880,7 +2882,7 @@ __global__ __launch_bounds__(512) void k_dense_stage_f64(const double *__restric
   for (int t = 0; t < NW; ++t) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const double z = acc[t][r];
+      const double z = acc[0][t][r] + acc[1][t][r];
       const double zp = __shfl_xor(z, 1, 64);
       const int row = row0 + M::row(l, r);
       const int col = (half * NW + t) * 16 + (l & 15);
