@@ -307,8 +307,8 @@ bool stag_square_lattice(const qw_walk_desc *w, int64_t n, int32_t *l1o, int32_t
 }
 
 // Per strip of a grid's blocked kernels: 1 if a marked vertex lies in its
-// window (halo included).
-std::vector<uint8_t> strip_marks(const StripGrid &sg, int l1, int l2, const std::vector<int32_t> &mlist) {
+// window (halo included; `early`: the window may start a column earlier).
+std::vector<uint8_t> strip_marks(const StripGrid &sg, int l1, int l2, int early, const std::vector<int32_t> &mlist) {
   std::vector<uint8_t> mark(static_cast<size_t>(sg.count()), 0);
   const int S = sg.halo;
   const double cost = static_cast<double>(mlist.size()) * (sg.tiles_r + sg.tiles_c);
@@ -326,9 +326,8 @@ std::vector<uint8_t> strip_marks(const StripGrid &sg, int l1, int l2, const std:
       if ((gr - lo + l1) % l1 < sg.rows + 2 * S) rows_hit.push_back(t);
     }
     for (int t = 0; t < sg.tiles_c; ++t) {
-      // a column more: two-column windows on odd grids may start one early
-      const int lo = ((std::min(t * sg.core, l2 - sg.core) - S - 1) % l2 + l2) % l2;
-      if ((gc - lo + l2) % l2 < sg.width + 1) cols_hit.push_back(t);
+      const int lo = ((std::min(t * sg.core, l2 - sg.core) - S - early) % l2 + l2) % l2;
+      if ((gc - lo + l2) % l2 < sg.width + early) cols_hit.push_back(t);
     }
     for (int a : rows_hit)
       for (int b : cols_hit) mark[static_cast<size_t>(a) * sg.tiles_c + b] = 1;
@@ -648,7 +647,7 @@ int build_plan(const qw_csr *g, const qw_walk_desc *w, qw_plan *p) {
         p->strip_core = dg.core;
       }
       p->strip_rows = sg.rows;
-      tmark = strip_marks(sg, p->dims[0], p->dims[1], mlist);
+      tmark = strip_marks(sg, p->dims[0], p->dims[1], p->strip_core ? p->dims[1] & 1 : 0, mlist);
       p->has_tmark = true;
     }
   }
