@@ -43,6 +43,10 @@ METRIC = "arc-steps/s (c64 batched vs c128 plain, L2 err<=1e-4); p50/p99 latency
 # 256 MiB copy (x2.00 / x1.00).  Each entry holds only for the kernel version
 # and launch configuration named in its key and source; any other reports None.
 MEASURED_TRAFFIC = {
+    # profiles/batch4096_ctqw_search_lds.md: mean over the 5120 timed launches of the
+    # default command, FETCH_SIZE 3,110,454.9 KiB x 2.00 + WRITE_SIZE 1,164,456.9 KiB x 1.00
+    # (768 threads, 9 to 12 rows each by degree, 19968-entry blocks)
+    "k_batch_ell_lds<float2,768,19968> batch4096 seed1 launches1280-6400": (3110454.9 * 2 + 1164456.9) * 1024,
     # profiles/ctqw_torus1024_sweep.md: the FP32 complex64 sweep, averaged over the four
     # launches of a step, FETCH_SIZE (4543.1 + 3 x 8942.0) / 4 KiB x 2.00 + WRITE_SIZE 8193.3 KiB
     "k_ctqw_torus_sweep<float2,5> 1024x1024": ((4543.1 + 3 * 8942.0) / 4 * 2 + 8193.3) * 1024,
@@ -990,10 +994,10 @@ def run_staggered(args):
         ms = a.elapsed_time(b)
         es = 8 if dtype == "c64" else 16
         if pl.structure == "stag_lattice":
-            # the fused square-lattice kernels: per step, read and write every
-            # amplitude once (2 S), no index; two steps run per launch, so the
-            # DRAM traffic is half of this model and frac can pass 0.5 of it
-            per_vertex = 2 * es
+            # the fused square-lattice kernel: per launch, read and write every
+            # amplitude once (2 S), no index; launches take up to 4 (complex64)
+            # or 6 (complex128) steps
+            per_vertex = 2 * es * -(-steps // (4 if dtype == "c64" else 6)) / steps
         else:
             # one launch per tessellation: read and write every amplitude (2 S)
             # and read its vertex index (4 B; the squares are one size, so no
@@ -1063,12 +1067,15 @@ def run_lattice(args):
         torch.cuda.synchronize()
         ms = a.elapsed_time(b)
         es = 8 if dtype == "c64" else 16
-        # algorithmic bytes per arc-step of the slot-major kernel: read and write
-        # the state (2S); the coin is 16 complex numbers read by every workgroup
+        # algorithmic bytes per launch: read and write the state (2S); the coin is
+        # 16 complex numbers read by every workgroup.  On grids of at least 300000
+        # (complex64) or 150000 cells a launch takes up to 5 or 4 steps.
         step_ms = ms / steps
-        gbs = 2 * es * g.n_arcs / (step_ms * 1e-3) / 1e9
+        most = (5 if g.n >= 300_000 else 1) if dtype == "c64" else (4 if g.n >= 150_000 else 1)
+        per_arc = 2 * es * -(-steps // most) / steps
+        gbs = per_arc * g.n_arcs / (step_ms * 1e-3) / 1e9
         res[dtype] = {"arc_steps_per_s": g.n_arcs * steps / (ms * 1e-3), "ms": ms, "step_us": step_ms * 1e3,
-                      "bytes_per_arc_step": 2 * es, "achieved_gbs": gbs, "frac": gbs / HBM_PEAK_GBS,
+                      "bytes_per_arc_step": per_arc, "achieved_gbs": gbs, "frac": gbs / HBM_PEAK_GBS,
                       "norm": float(norm), "path": pl.structure,
                       ("max_abs_err_3_steps" if dtype == "c128" else "l2_err_3_steps"): err3}
         del psi
