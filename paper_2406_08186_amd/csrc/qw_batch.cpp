@@ -161,6 +161,8 @@ struct Item {
   int32_t slot;
   int64_t load;
   std::vector<TileEntry> tiles;
+  int64_t row_load = 0;  // LDS-staged kernel: what a row of a tile adds to `load`
+  int64_t cost(const TileEntry &t) const { return load + row_load * (t.end - t.begin); }
 };
 std::vector<TileEntry> lay_out(std::vector<Item> &items, bool xcd_aware) {
   std::vector<TileEntry> table;
@@ -187,14 +189,23 @@ std::vector<TileEntry> lay_out(std::vector<Item> &items, bool xcd_aware) {
 // Table of the LDS-staged kernel for a grid of `*grid` workgroups, one per
 // compute unit, that take entries grid-stride: every walk's tiles on one XCD
 // (or anywhere, without placement), each tile on the workgroup that has the
-// least to do so far, dearest tiles first.  A tile costs its passes over the
-// vector (staging, then the sums) and a constant, whatever its rows.  Taken in
-// turn instead, 192 walks kept the fullest workgroup busy 1.25 times as long as
-// the mean one (1.04 so), and a few walks left most units idle.
+// least to do so far, dearest walks first.  A tile costs a constant, its rows'
+// tables and state (bound by the unit's share of memory when all units have one),
+// and its passes over the vector (staging, then the sums), whatever its rows.  In
+// units of 1/26 us, from batches of 1 and 256 equal walks of one tile and walks of
+// 21 to 32 tiles: 60, 0.8 per KB of 4 d + 3 S bytes a row, and 40 + slots per
+// block.  Taken in turn instead, 192 walks kept the fullest workgroup busy 1.25
+// times as long as the mean one (1.04 so), and a few walks left most units idle.
+// With the constant and the passes alone, a unit could get ten small tiles: 96
+// complex128 walks of degree 8 took 7.9 ms for 4 steps, 6.4 so.
 std::vector<TileEntry> lay_out_lds(const std::vector<Item> &items, bool xcd_aware, int *grid) {
   const int groups = xcd_aware ? 8 : 1, most = kLdsMaxGrid / groups;
   std::vector<std::pair<int64_t, const Item *>> walks;  // by what all their tiles cost, then by one's cost
-  for (const Item &it : items) walks.emplace_back(-it.load * static_cast<int64_t>(it.tiles.size()), &it);
+  for (const Item &it : items) {
+    int64_t all = 0;
+    for (const TileEntry &t : it.tiles) all += it.cost(t);
+    walks.emplace_back(-all, &it);
+  }
   std::sort(walks.begin(), walks.end());
   std::vector<std::vector<std::pair<int64_t, const Item *>>> of(static_cast<size_t>(groups));
   std::vector<int64_t> load(static_cast<size_t>(groups), 0);
@@ -205,7 +216,7 @@ std::vector<TileEntry> lay_out_lds(const std::vector<Item> &items, bool xcd_awar
     load[x] -= cost;
     count[x] += it->tiles.size();
     tiles += it->tiles.size();
-    of[x].emplace_back(-it->load, it);
+    of[x].emplace_back(-it->cost(it->tiles[0]), it);
   }
   const int per = static_cast<int>(
       std::min<size_t>(static_cast<size_t>(most), std::max<size_t>(1, *std::max_element(count.begin(), count.end()))));
@@ -217,11 +228,11 @@ std::vector<TileEntry> lay_out_lds(const std::vector<Item> &items, bool xcd_awar
   for (int x = 0; x < groups; ++x) {
     std::sort(of[x].begin(), of[x].end());
     std::iota(heap.begin(), heap.end(), int64_t{0});
-    for (const auto &[cost, it] : of[x])
-      for (const TileEntry &t : it->tiles) {
+    for (const auto &walk : of[x])
+      for (const TileEntry &t : walk.second->tiles) {
         const size_t b = static_cast<size_t>(groups * (heap[0] & 255) + x);
         placed.emplace_back(rounds[b]++ * rounds.size() + b, &t);
-        const int64_t key = heap[0] - 256 * cost;
+        const int64_t key = heap[0] + 256 * walk.second->cost(t);
         size_t h = 0;  // the least workgroup's load grew: sift it down
         for (size_t c; (c = 2 * h + 1) < heap.size(); h = c) {
           c += c + 1 < heap.size() && heap[c + 1] < heap[c];
@@ -255,7 +266,8 @@ int build_table(qw_batch *b) {
         const bool c128 = b->dtype == QW_C128;
         const int64_t block = c128 ? kLdsBlockBytes128 / 16 : kLdsBlockBytes64 / 8;
         const int64_t slots = static_cast<int64_t>(lds_rows_per_thread(c128, w.ell_d)) * w.ell_d;
-        it.load = 40 + (p->n + block - 1) / block * (40 + slots);
+        it.load = 256 * (60 + (p->n + block - 1) / block * (40 + slots));
+        it.row_load = (4 * w.ell_d + 3 * (c128 ? 16 : 8)) / 5;
         litems.push_back(std::move(it));
         continue;
       }

@@ -17,10 +17,11 @@ constexpr int kCoinedTileThreads = 512;  // single coined walks: four gathers in
 // The LDS-staged batch stage, per state type: workgroup size, the LDS block of
 // the input vector it stages (whole rounds of 1 KiB direct loads by every
 // wavefront) and rows per thread for walks of degree d (1..8).  A row takes d
-// index and four sum registers, so sparser walks fit more rows; one row more
-// than here spills (96 walks of one degree, complex64, ms a pass: degree 3 with
-// 12, 13, 14 rows 7.7, 8.6, 9.2; degree 4 with 11, 12 8.4, 8.7; degree 5 with
-// 10, 11, 12 10.0, 9.4, 9.7).
+// index and four sum registers, so sparser walks fit more rows.  Chosen on the
+// kernel as it was before its last loads were cut, where one row more than here
+// spilled (96 walks of one degree, complex64, ms a pass: degree 3 with 12, 13, 14
+// rows 7.7, 8.6, 9.2; degree 4 with 11, 12 8.4, 8.7; degree 5 with 10, 11, 12
+// 10.0, 9.4, 9.7).
 constexpr int kLdsTileThreads64 = 768;
 constexpr int kLdsBlockBytes64 = 156 * 1024;
 constexpr int kLdsTileThreads128 = 1024;

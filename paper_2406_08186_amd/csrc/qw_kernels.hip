@@ -430,8 +430,10 @@ __global__ __launch_bounds__(1024) void k_coined_small(GraphView g, T *psi, int 
 // order and the next one reads phi[rev[a]] (GATHER), cheaper than scattered
 // 8-byte stores; only an even last step scatters (SCATTER), into the caller's
 // buffer.  complex128 scatters at every step: its 16-byte gathers cost more.
-// Bound by these accesses (9 us) and the latency of a tile's chain of loads, coin
-// and stores (11 us at two tiles per compute unit).  60 steps on 120000 vertices
+// Bound by these accesses: an 8-byte gather brings a line, 90 MB per step for 13 MB of
+// amplitudes and indices on 120000 vertices of mean degree 9, at 5.0 TB/s with the
+// stores, the rate of a large copy (without the gather, the first step, 10.8 us of
+// 19.8).  60 steps on 120000 vertices
 // of mean degree 9 complex64: 1282 us with 256 threads and scatters, 1200 so (1388
 // with 1024 threads; degree-wide register copies of the rows 1354); 110000
 // vertices complex128: 1173, 1115 so, 1290 gathering.
@@ -2463,9 +2465,10 @@ __global__ __launch_bounds__(kTileThreads) void k_batch_stage(BatchCtl *ctl, con
 // rows' D neighbour slots in every block (branch-free; a slot outside the block
 // adds -0), and the registers that shorter rows leave hold more rows
 // (lds_rows_per_thread).  With eight slots and 9 rows (complex64) for every
-// degree, 96 walks of up to 2e5 vertices took, ms for 4 steps by degree 3 to 8,
-// 11.0 11.3 11.6 12.0 12.4 12.7; so, and on the balanced table, 7.3 8.3 9.3
-// 10.7 11.7 12.5.  Memory is reached through global-address-space views of
+// degree and tiles in turn, 96 walks of up to 2e5 vertices took, ms for 4 steps by
+// degree 3 to 8, 5.1 5.9 6.0 6.8 5.8 4.6 (complex128, 6 rows: 7.2 10.3 10.7 11.5
+// 8.8 6.5); so, and on the balanced table, 3.0 4.2 4.8 5.3 4.7 4.3 (4.4 6.7 7.6 9.6
+// 7.4 6.4).  Memory is reached through global-address-space views of
 // the slot table's pointers, and every load is unconditional (indices clamped
 // into range, unused values dropped by a select).  Tiles are taken
 // grid-stride (the host lays out the table by XCD); the last workgroup of the
