@@ -44,9 +44,9 @@ METRIC = "arc-steps/s (c64 batched vs c128 plain, L2 err<=1e-4); p50/p99 latency
 # and launch configuration named in its key and source; any other reports None.
 MEASURED_TRAFFIC = {
     # profiles/batch4096_ctqw_search_lds.md: mean over the 5120 timed launches of the
-    # default command, FETCH_SIZE 3,110,454.9 KiB x 2.00 + WRITE_SIZE 1,164,456.9 KiB x 1.00
+    # default command, FETCH_SIZE 3,055,193.2 KiB x 2.00 + WRITE_SIZE 1,164,456.9 KiB x 1.00
     # (768 threads, 9 to 12 rows each by degree, 19968-entry blocks)
-    "k_batch_ell_lds<float2,768,19968> batch4096 seed1 launches1280-6400": (3110454.9 * 2 + 1164456.9) * 1024,
+    "k_batch_ell_lds<float2,768,19968> batch4096 seed1 launches1280-6400": (3055193.2 * 2 + 1164456.9) * 1024,
     # profiles/ctqw_torus1024_sweep.md: the FP32 complex64 sweep, averaged over the four
     # launches of a step, FETCH_SIZE (4543.1 + 3 x 8942.0) / 4 KiB x 2.00 + WRITE_SIZE 8193.3 KiB
     "k_ctqw_torus_sweep<float2,5> 1024x1024": ((4543.1 + 3 * 8942.0) / 4 * 2 + 8193.3) * 1024,

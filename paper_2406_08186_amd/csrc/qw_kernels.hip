@@ -2469,7 +2469,7 @@ __global__ __launch_bounds__(kTileThreads) void k_batch_stage(BatchCtl *ctl, con
 // degree 3 to 8, 5.1 5.9 6.0 6.8 5.8 4.6 (complex128, 6 rows: 7.2 10.3 10.7 11.5
 // 8.8 6.5); so, and on the balanced table, 3.0 4.2 4.8 5.3 4.7 4.3 (4.4 6.7 7.6 9.6
 // 7.4 6.4).  Memory is reached through global-address-space views of
-// the slot table's pointers, and every load is unconditional (indices clamped
+// the slot table's pointers, and every load but a marked vertex's own is unconditional (indices clamped
 // into range, unused values dropped by a select).  Tiles are taken
 // grid-stride (the host lays out the table by XCD); the last workgroup of the
 // launch advances the launch counter when `advance` is set.  The host sends
