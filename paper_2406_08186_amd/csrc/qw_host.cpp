@@ -619,9 +619,10 @@ int build_plan(const qw_csr *g, const qw_walk_desc *w, qw_plan *p) {
   std::vector<int32_t> by_degree;
   if (ctqw && structure == kSmall && p->K >= 2 && n <= 4096 && n + na >= 12) {
     by_degree.resize(static_cast<size_t>(n));
-    std::iota(by_degree.begin(), by_degree.end(), 0);
-    std::stable_sort(by_degree.begin(), by_degree.end(),
-                     [&](int32_t x, int32_t y) { return rp[x + 1] - rp[x] > rp[y + 1] - rp[y]; });
+    std::vector<int32_t> at(static_cast<size_t>(maxd) + 2, 0);  // at[i]: where degree maxd - i starts
+    for (int64_t v = 0; v < n; ++v) ++at[static_cast<size_t>(maxd - (rp[v + 1] - rp[v])) + 1];
+    std::partial_sum(at.begin(), at.end(), at.begin());
+    for (int64_t v = 0; v < n; ++v) by_degree[at[static_cast<size_t>(maxd - (rp[v + 1] - rp[v]))]++] = static_cast<int32_t>(v);
     const int per = n <= 1024 ? 1 : n <= 2048 ? 2 : 4;
     p->small_regs = true;
     for (int i = 0; i < per && 1024 * i < n; ++i) {
